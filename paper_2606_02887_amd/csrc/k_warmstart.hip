@@ -435,44 +435,37 @@ template void launch_ws_spa_only<float>(const BInst*, int, const float*, float*,
 template void launch_ws_spa_only<double>(const BInst*, int, const double*, double*, hipStream_t);
 
 // ----------------------------------------------------------------------------- network
-// Weights staged in LDS as FP32 (dequantised BF16): M1 (H x r) and M2^T (H x r), so row
-// k of each is contiguous.  One thread per row: o = c + b2, then for every hidden unit
-// a_k = M1_k c + b1_k, h_k = relu(a_k), o += h_k M2[:, k]; y = relu(o).
-template <int RP>
-struct MlpSmem {
-  float M1[kMlpHidden * RP];
-  float M2t[kMlpHidden * RP];
-  float b1[kMlpHidden];
-  float b2[RP];
-};
-
-template <int RP>
-__device__ __forceinline__ void mlp_stage(const MlpDev& m, MlpSmem<RP>& sm) {
-  const int r = m.r;
-  for (int e = threadIdx.x; e < kMlpHidden * RP; e += kThreads) {
-    const int k = e / RP, c = e % RP;
-    sm.M1[e] = c < r ? bf16f(m.M1h[k * r + c]) : 0.f;
-    sm.M2t[e] = c < r ? bf16f(m.M2h[c * kMlpHidden + k]) : 0.f;
-  }
-  for (int e = threadIdx.x; e < kMlpHidden; e += kThreads) sm.b1[e] = m.b1[e];
-  for (int e = threadIdx.x; e < RP; e += kThreads) sm.b2[e] = e < r ? m.b2[e] : 0.f;
-  __syncthreads();
-}
-
 // Forward over rows of a plain N x r array, or (bm.blk_inst != null) over the rows of the
-// instances of one rank class, scaled by each instance's s.  Optional cache for training:
-// pre-activations a (N x H) and outputs o (N x r).
+// instances of one rank class, scaled by each instance's s:
+//   a = M1 c + b1, h = relu(a), o = c + b2 + M2 h, y = s relu(o)
+// with the BF16 weights dequantised to FP32 and every sum one FMA chain in index order.
+// Optional cache for training: pre-activations a (N x H) and outputs o (N x r); with T set
+// also this workgroup's FP64 partial sums of (y - t)^2, y^2 and t^2.
+//
+// A workgroup takes tiles of 32 rows.  Hidden units: thread t owns unit t % 128 of 16 rows,
+// its weights in registers, c broadcast from LDS.  Outputs: thread t owns column t % RP, h
+// and M2 read four hidden units at a time.  What bounds it is latency: one thread per row
+// and all of its 2 H r FMAs gave a minibatch of 4096 rows 16 workgroups, 42.8 us at r = 16;
+// 32-row tiles give it 128, 13.7 us with the loss sums of a former kernel of its own.
+constexpr int kMlpRows = 32;           // rows of a tile
+constexpr int kMlpPitch = kMlpHidden + 4;
+
 template <int RP>
 __global__ __launch_bounds__(kThreads) void k_mlp_fwd(MlpDev m, int64_t N,
                                                       const float* __restrict__ C,
                                                       const float* __restrict__ row_scale,
                                                       float* __restrict__ Y, BMap bm,
                                                       const int32_t* __restrict__ idx,
-                                                      int64_t pool,
+                                                      int64_t pool, const float* __restrict__ T,
                                                       float* __restrict__ cache_a,
-                                                      float* __restrict__ cache_o) {
-  __shared__ MlpSmem<RP> sm;
-  const int r = m.r;
+                                                      float* __restrict__ cache_o,
+                                                      double* __restrict__ part) {
+  constexpr int H = kMlpHidden;
+  __shared__ __attribute__((aligned(16))) float sM2[RP][kMlpPitch];
+  __shared__ __attribute__((aligned(16))) float sH[kMlpRows][kMlpPitch];
+  __shared__ __attribute__((aligned(16))) float sC[kMlpRows][RP];
+  __shared__ double sred[kThreads / kWave * 3];
+  const int r = m.r, tid = threadIdx.x;
   int64_t off = 0, rows = N, bid = blockIdx.x, nb = gridDim.x;
   float sc = 1.f;
   if (bm.blk_inst) {
@@ -484,151 +477,243 @@ __global__ __launch_bounds__(kThreads) void k_mlp_fwd(MlpDev m, int64_t N,
     nb = d->nblk;
     sc = (float)sqrt(sqrt((double)r) * sqrt(d->normA2) / ((double)d->n * r));
   }
-  mlp_stage<RP>(m, sm);
-  for (int64_t t = bid; t * kThreads < rows; t += nb) {
-    const int64_t q = t * kThreads + threadIdx.x;
-    if (q >= rows) continue;
-    const int64_t row = idx ? pool_row(idx, q, pool) : q;
-    float c[RP], o[RP];
-#pragma unroll
-    for (int j = 0; j < RP; ++j) {
-      c[j] = j < r ? C[off + row * r + j] : 0.f;
-      o[j] = sm.b2[j] + c[j];  // the residual: o = c + M2 h + b2
-    }
-    for (int k = 0; k < kMlpHidden; ++k) {
-      float a = sm.b1[k];
-#pragma unroll
-      for (int j = 0; j < RP; ++j) a = fmaf(sm.M1[k * RP + j], c[j], a);
-      if (cache_a) cache_a[q * kMlpHidden + k] = a;
-      const float h = fmaxf(a, 0.f);
-#pragma unroll
-      for (int j = 0; j < RP; ++j) o[j] = fmaf(sm.M2t[k * RP + j], h, o[j]);
-    }
-    const float s = row_scale ? row_scale[row] : sc;
-    for (int j = 0; j < r; ++j) {
-      if (cache_o) cache_o[q * r + j] = o[j];
-      Y[off + q * r + j] = s * fmaxf(o[j], 0.f);
-    }
+  for (int e = tid; e < RP * H; e += kThreads) {
+    const int j = e / H, k = e % H;
+    sM2[j][k] = j < r ? bf16f(m.M2h[j * H + k]) : 0.f;
   }
-}
-
-// Loss pieces of a minibatch: per-workgroup FP64 partial sums of (y - t)^2, y^2, t^2.
-__global__ __launch_bounds__(kThreads) void k_mlp_loss_parts(int64_t B, int r,
-                                                             const float* __restrict__ y,
-                                                             const float* __restrict__ T,
-                                                             const int32_t* __restrict__ idx,
-                                                             int64_t pool,
-                                                             double* __restrict__ part) {
-  __shared__ double sred[kThreads / kWave * kNumPart];
+  const int k = tid % H, r0 = (tid / H) * (kMlpRows / 2);
+  float w1[RP];
+#pragma unroll
+  for (int j = 0; j < RP; ++j) w1[j] = j < r ? bf16f(m.M1h[k * r + j]) : 0.f;
+  const float bias1 = m.b1[k];
+  const int j = tid % RP, rq = tid / RP;  // output column, first row
+  const float bias2 = j < r ? m.b2[j] : 0.f;
   double v[3] = {0.0, 0.0, 0.0};
-  for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < B * r;
-       e += (int64_t)gridDim.x * kThreads) {
-    const int64_t q = e / r;
-    const int j = (int)(e - q * r);
-    const double yy = y[e], tt = T[pool_row(idx, q, pool) * r + j];
-    v[0] += (yy - tt) * (yy - tt);
-    v[1] += yy * yy;
-    v[2] += tt * tt;
-  }
-  block_sum<3>(v, sred);
-  if (threadIdx.x == 0)
-    for (int j = 0; j < 3; ++j) part[(size_t)blockIdx.x * kNumPart + j] = v[j];
-}
-
-// do = dL/dy * [o > 0] with dL/dy = 2 (y - t) / N + mu 2 dlt 2 y / N; then
-// da = (M2^T do) * [a > 0].  scal: {sum (y-t)^2, sum y^2, sum t^2} after reduction.
-template <int RP>
-__global__ __launch_bounds__(kThreads) void k_mlp_back_rows(MlpDev m, int64_t B,
-                                                            const float* __restrict__ y,
-                                                            const float* __restrict__ T,
-                                                            const int32_t* __restrict__ idx,
-                                                            int64_t pool,
-                                                            const float* __restrict__ cache_a,
-                                                            const float* __restrict__ cache_o,
-                                                            double* __restrict__ part,
-                                                            int nparts, float mu,
-                                                            float* __restrict__ dO,
-                                                            float* __restrict__ dA) {
-  __shared__ MlpSmem<RP> sm;
-  __shared__ double sred[kThreads / kWave * kNumPart];
-  const int r = m.r;
-  double sums[3] = {0.0, 0.0, 0.0};
-  for (int b = threadIdx.x; b < nparts; b += kThreads)
-    for (int j = 0; j < 3; ++j) sums[j] += part[(size_t)b * kNumPart + j];
-  block_sum<3>(sums, sred);
-  const double N = (double)B * r;
-  const float dlt = (float)((sums[1] - sums[2]) / N);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {  // the minibatch loss
-    const double dd = (sums[1] - sums[2]) / N;
-    part[(size_t)kMaxGrid * kNumPart] = sums[0] / N + (double)mu * dd * dd;
-  }
-  mlp_stage<RP>(m, sm);
-  const int64_t q = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (q >= B) return;
-  const int64_t row = pool_row(idx, q, pool);
-  float dov[RP];
-#pragma unroll
-  for (int j = 0; j < RP; ++j) {
-    float g = 0.f;
-    if (j < r) {
-      const float yy = y[q * r + j], tt = T[row * r + j];
-      const float dy = (float)(2.0 / N) * (yy - tt) + mu * 2.f * dlt * (float)(2.0 / N) * yy;
-      g = cache_o[q * r + j] > 0.f ? dy : 0.f;
-      dO[q * r + j] = g;
+  for (int64_t t = bid; t * kMlpRows < rows; t += nb) {
+    const int64_t q0 = t * kMlpRows;
+    __syncthreads();  // the last tile's readers of sC and sH
+    for (int e = tid; e < kMlpRows * RP; e += kThreads) {
+      const int64_t q = q0 + e / RP;
+      const int c = e % RP;
+      float x = 0.f;
+      if (q < rows && c < r) x = C[off + (idx ? pool_row(idx, q, pool) : q) * r + c];
+      sC[e / RP][c] = x;
     }
-    dov[j] = g;
-  }
-  for (int k = 0; k < kMlpHidden; ++k) {
-    float s = 0.f;
+    __syncthreads();
+    for (int i = r0; i < r0 + kMlpRows / 2; i += 4) {  // four rows' chains side by side
+      float a[4] = {bias1, bias1, bias1, bias1};
 #pragma unroll
-    for (int j = 0; j < RP; ++j) s = fmaf(sm.M2t[k * RP + j], dov[j], s);
-    dA[q * kMlpHidden + k] = cache_a[q * kMlpHidden + k] > 0.f ? s : 0.f;
+      for (int c = 0; c < RP; c += 4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float4 x = *(const float4*)&sC[i + u][c];
+          a[u] = fmaf(w1[c], x.x, a[u]);
+          a[u] = fmaf(w1[c + 1], x.y, a[u]);
+          a[u] = fmaf(w1[c + 2], x.z, a[u]);
+          a[u] = fmaf(w1[c + 3], x.w, a[u]);
+        }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (cache_a && q0 + i + u < rows) cache_a[(q0 + i + u) * H + k] = a[u];
+        sH[i + u][k] = fmaxf(a[u], 0.f);
+      }
+    }
+    __syncthreads();
+    constexpr int RS = kThreads / RP;                  // rows between a thread's outputs
+    constexpr int G = RP >= 32 ? 4 : RP >= 16 ? 2 : 1;  // outputs side by side, one read of M2
+    for (int i = rq; i < kMlpRows; i += G * RS) {
+      float o[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) o[g] = bias2 + sC[i + g * RS][j];
+#pragma unroll 8
+      for (int u = 0; u < H; u += 4) {
+        const float4 w = *(const float4*)&sM2[j][u];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const float4 h = *(const float4*)&sH[i + g * RS][u];
+          o[g] = fmaf(w.x, h.x, o[g]);
+          o[g] = fmaf(w.y, h.y, o[g]);
+          o[g] = fmaf(w.z, h.z, o[g]);
+          o[g] = fmaf(w.w, h.w, o[g]);
+        }
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int64_t q = q0 + i + g * RS;
+        if (q < rows && j < r) {
+          const int64_t row = idx ? pool_row(idx, q, pool) : q;
+          const float y = (row_scale ? row_scale[row] : sc) * fmaxf(o[g], 0.f);
+          if (cache_o) cache_o[q * r + j] = o[g];
+          Y[off + q * r + j] = y;
+          if (T) {
+            const double yy = y, tt = T[row * r + j];
+            v[0] += (yy - tt) * (yy - tt);
+            v[1] += yy * yy;
+            v[2] += tt * tt;
+          }
+        }
+      }
+    }
+  }
+  if (T) {
+    block_sum<3>(v, sred);
+    if (tid == 0)
+      for (int q = 0; q < 3; ++q) part[(size_t)blockIdx.x * kNumPart + q] = v[q];
   }
 }
 
-// Weight gradients as fixed-order sums over the B minibatch rows (FP64 accumulation),
-// one thread per parameter: gM1[k][c] = sum_q dA[q][k] C[row_q][c], gb1[k] = sum dA,
-// gM2[j][k] = sum_q dO[q][j] relu(a[q][k]), gb2[j] = sum dO.  Parameters are numbered
-// M1 (H r), b1 (H), M2 (r H), b2 (r).
-__global__ __launch_bounds__(kThreads) void k_mlp_grad(int r, int64_t B,
+// Backward of a minibatch.  With the loss sums {sum (y-t)^2, sum y^2, sum t^2} of the
+// forward's workgroups: do = dL/dy [o > 0], dL/dy = 2 (y - t) / N + mu 2 dlt 2 y / N, and
+// da = (M2^T do) [a > 0] (FP32), then the weight gradients
+//   gM1 = da^T C, gb1 = sum da, gM2 = do^T h, gb2 = sum do
+// as FP64 sums over the rows.  Grid: x = slabs of `rows_per` rows (a multiple of 32), y =
+// blocks of 32 hidden units.  A workgroup forms do and da of 32 rows at a time in LDS and
+// adds them on the FP64 matrix cores (16x16x4, rows as K): wave w takes the product w / 2
+// (da^T C or h^T do) of 16 hidden units, r columns.  One slab writes FP32 gradients, more
+// write FP64 partials (nslab x P) that the update adds in slab order.
+// Bound by latency: 10.1 us at B = 4096, r = 16 (256 workgroups).  One thread per row for do
+// and da and one per parameter with all B rows in its chain took 35.5 + 1158 us (17
+// workgroups, two dependent loads per row).
+template <int RP>
+__global__ __launch_bounds__(kThreads) void k_mlp_back(MlpDev m, int64_t B, int64_t rows_per,
+                                                       const float* __restrict__ y,
                                                        const float* __restrict__ C,
+                                                       const float* __restrict__ T,
                                                        const int32_t* __restrict__ idx,
                                                        int64_t pool,
                                                        const float* __restrict__ cache_a,
-                                                       const float* __restrict__ dO,
-                                                       const float* __restrict__ dA,
-                                                       float* __restrict__ grad) {
-  const int H = kMlpHidden;
-  const int np = H * r + H + r * H + r;
-  const int e = blockIdx.x * kThreads + threadIdx.x;
-  if (e >= np) return;
-  double s = 0.0;
-  if (e < H * r) {
-    const int k = e / r, c = e % r;
-    for (int64_t q = 0; q < B; ++q) s += (double)dA[q * H + k] * (double)C[pool_row(idx, q, pool) * r + c];
-  } else if (e < H * r + H) {
-    const int k = e - H * r;
-    for (int64_t q = 0; q < B; ++q) s += (double)dA[q * H + k];
-  } else if (e < H * r + H + r * H) {
-    const int f = e - H * r - H;
-    const int j = f / H, k = f % H;
-    for (int64_t q = 0; q < B; ++q) s += (double)dO[q * r + j] * (double)fmaxf(cache_a[q * H + k], 0.f);
-  } else {
-    const int j = e - H * r - H - r * H;
-    for (int64_t q = 0; q < B; ++q) s += (double)dO[q * r + j];
+                                                       const float* __restrict__ cache_o,
+                                                       double* __restrict__ part, int nparts,
+                                                       float mu, float* __restrict__ grad,
+                                                       double* __restrict__ gpart) {
+  constexpr int H = kMlpHidden, KB = 32, PC = RP + 4, NB = RP >= 16 ? RP / 16 : 1;
+  typedef double d4 __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(16))) float sX[2][kMlpRows][PC];       // C, do
+  __shared__ float sA[2][kMlpRows][KB + 1];                                // da, h
+  __shared__ double sred[kThreads / kWave * 3];
+  const int r = m.r, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double sums[3] = {0.0, 0.0, 0.0};
+  for (int b = tid; b < nparts; b += kThreads)
+    for (int q = 0; q < 3; ++q) sums[q] += part[(size_t)b * kNumPart + q];
+  block_sum<3>(sums, sred);
+  const double N = (double)B * r;
+  const float dlt = (float)((sums[1] - sums[2]) / N);
+  if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {  // the minibatch loss
+    const double dd = (sums[1] - sums[2]) / N;
+    part[(size_t)kMaxGrid * kNumPart] = sums[0] / N + (double)mu * dd * dd;
   }
-  grad[e] = (float)s;
+  const int k0 = blockIdx.y * KB, kk = tid % KB, rg = tid / KB;
+  float w2[RP];
+#pragma unroll
+  for (int j = 0; j < RP; ++j) w2[j] = j < r ? bf16f(m.M2h[j * H + k0 + kk]) : 0.f;
+  const int prod = wave >> 1, mt = wave & 1, c16 = lane & 15, kr = lane >> 4;
+  d4 acc[NB];
+#pragma unroll
+  for (int q = 0; q < NB; ++q) acc[q] = d4{0.0, 0.0, 0.0, 0.0};
+  double bsum = 0.0;  // thread kk < 32: gb1; threads 64 .. 64 + r of the first hidden block: gb2
+  const int64_t qb = (int64_t)blockIdx.x * rows_per;
+  const int64_t qe = qb + rows_per < B ? qb + rows_per : B;
+  for (int64_t q0 = qb; q0 < qe; q0 += kMlpRows) {
+    __syncthreads();
+    for (int e = tid; e < kMlpRows * RP; e += kThreads) {
+      const int i = e / RP, j = e % RP;
+      const int64_t q = q0 + i;
+      float x = 0.f, g = 0.f;
+      if (q < qe && j < r) {
+        const int64_t row = pool_row(idx, q, pool);
+        x = C[row * r + j];
+        const float yy = y[q * r + j], tt = T[row * r + j];
+        const float dy = (float)(2.0 / N) * (yy - tt) + mu * 2.f * dlt * (float)(2.0 / N) * yy;
+        g = cache_o[q * r + j] > 0.f ? dy : 0.f;
+      }
+      sX[0][i][j] = x;
+      sX[1][i][j] = g;
+    }
+    float a[kMlpRows / 8];
+#pragma unroll
+    for (int u = 0; u < kMlpRows / 8; ++u) {
+      const int64_t q = q0 + rg + 8 * u;
+      a[u] = cache_a[(q < qe ? q : qe - 1) * H + k0 + kk];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kMlpRows / 8; ++u) {
+      const int i = rg + 8 * u;
+      float s = 0.f;
+#pragma unroll
+      for (int j = 0; j < RP; j += 4) {
+        const float4 g = *(const float4*)&sX[1][i][j];
+        s = fmaf(w2[j], g.x, s);
+        s = fmaf(w2[j + 1], g.y, s);
+        s = fmaf(w2[j + 2], g.z, s);
+        s = fmaf(w2[j + 3], g.w, s);
+      }
+      const bool in = q0 + i < qe;
+      sA[0][i][kk] = in && a[u] > 0.f ? s : 0.f;
+      sA[1][i][kk] = in ? fmaxf(a[u], 0.f) : 0.f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < kMlpRows / 4; ++s) {
+      const int i = 4 * s + kr;
+      const double av = (double)sA[prod][i][16 * mt + c16];
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        const double bv = RP >= 16 || c16 < RP ? (double)sX[prod][i][(16 * q + c16) % RP] : 0.0;
+        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[q], 0, 0, 0);
+      }
+    }
+    if (tid < KB) {
+      for (int i = 0; i < kMlpRows; ++i) bsum += (double)sA[0][i][tid];
+    } else if (tid >= 64 && tid < 64 + RP && blockIdx.y == 0) {
+      for (int i = 0; i < kMlpRows; ++i) bsum += (double)sX[1][i][tid - 64];
+    }
+  }
+  const int np = H * r + H + r * H + r;
+  auto put = [&](int e, double g) {
+    if (gpart) gpart[(size_t)blockIdx.x * np + e] = g;
+    else grad[e] = (float)g;
+  };
+#pragma unroll
+  for (int q = 0; q < NB; ++q)
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int k = k0 + 16 * mt + kr + 4 * w, j = 16 * q + c16;
+      if (j < r) put(prod ? H * r + H + j * H + k : k * r + j, acc[q][w]);
+    }
+  if (tid < KB) put(H * r + k0 + tid, bsum);
+  else if (tid >= 64 && tid < 64 + r && blockIdx.y == 0) put(H * r + H + r * H + tid - 64, bsum);
 }
 
-// Adam on the FP32 master weights, then the BF16 copies.  step counts from 1.
+// Adam on the FP32 master weights, then the BF16 copies.  step counts from 1.  64
+// parameters per workgroup; with gpart set, four threads per parameter add its slab
+// partials (slabs q, q + 4, ... each, then (s0 + s1) + s2 + s3), else grad is the gradient.
 __global__ __launch_bounds__(kThreads) void k_mlp_adam(MlpDev m, const float* __restrict__ grad,
-                                                       float* __restrict__ mom,
+                                                       const double* __restrict__ gpart,
+                                                       int nslab, float* __restrict__ mom,
                                                        float* __restrict__ vel, int step, float lr,
                                                        float beta1, float beta2, float eps) {
+  __shared__ double sq[4][64];
   const int H = kMlpHidden, r = m.r;
   const int np = H * r + H + r * H + r;
-  const int e = blockIdx.x * kThreads + threadIdx.x;
-  if (e >= np) return;
+  const int t = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + t;
+  double s = 0.0;
+  if (gpart) {
+    const double* p = gpart + (e < np ? e : 0);
+    for (int b = q; b < nslab; b += 32) {
+      double v[8];  // eight slabs per round trip; those past the last read a valid one
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        v[u] = p[(size_t)(b + 4 * u < nslab ? b + 4 * u : b) * np];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (b + 4 * u < nslab) s += v[u];
+    }
+    sq[q][t] = s;
+    __syncthreads();
+  }
+  if (q != 0 || e >= np) return;
   float* w;
   uint16_t* wh = nullptr;
   int at;
@@ -647,7 +732,7 @@ __global__ __launch_bounds__(kThreads) void k_mlp_adam(MlpDev m, const float* __
     w = m.b2;
     at = e - H * r - H - r * H;
   }
-  const float g = grad[e];
+  const float g = gpart ? (float)(((sq[0][t] + sq[1][t]) + sq[2][t]) + sq[3][t]) : grad[e];
   const float mm = beta1 * mom[e] + (1.f - beta1) * g;
   const float vv = beta2 * vel[e] + (1.f - beta2) * g * g;
   mom[e] = mm;
@@ -683,36 +768,45 @@ void launch_mlp_sync(const MlpDev& m, hipStream_t s) {
                      dim3(kThreads), 0, s, m);
 }
 
+// Workgroups of a forward over N plain rows: one per 32-row tile up to the loss partials'
+// rows (1024; also about what is resident at once).
+static int mlp_fwd_grid(int64_t N) {
+  const int64_t g = (N + kMlpRows - 1) / kMlpRows;
+  return (int)(g < 1 ? 1 : (g > kMaxGrid ? kMaxGrid : g));
+}
+
 void launch_mlp_forward(const MlpDev& m, int64_t N, const float* C, const float* row_scale,
-                        float* Y, const BMap& bm, int grid, const int32_t* idx, int64_t pool,
-                        float* cache_a, float* cache_o, hipStream_t s) {
-  if (!bm.blk_inst) {
-    int64_t g = (N + kThreads - 1) / kThreads;
-    grid = (int)(g < 1 ? 1 : (g > 65535 ? 65535 : g));
-  }
+                        float* Y, const BMap& bm, int grid, hipStream_t s) {
+  if (!bm.blk_inst) grid = mlp_fwd_grid(N);
   SNMF_DISPATCH_MLP(rank_pad(m.r),
                     hipLaunchKernelGGL((k_mlp_fwd<RP>), dim3(grid), dim3(kThreads), 0, s, m, N, C,
-                                       row_scale, Y, bm, idx, pool, cache_a, cache_o))
+                                       row_scale, Y, bm, nullptr, 0, nullptr, nullptr, nullptr,
+                                       nullptr))
 }
 
 void launch_mlp_train_step(const MlpDev& m, int64_t pool, int64_t B, const float* C,
                            const float* T, const int32_t* idx, float mu, float lr, int step,
                            const MlpWork& w, hipStream_t s) {
-  launch_mlp_forward(m, B, C, nullptr, w.y, BMap{}, 0, idx, pool, w.cache_a, w.cache_o, s);
-  const int np = (int)((B * m.r + kThreads - 1) / kThreads);
-  const int nparts = np < 1 ? 1 : (np > kMaxGrid ? kMaxGrid : np);
-  hipLaunchKernelGGL(k_mlp_loss_parts, dim3(nparts), dim3(kThreads), 0, s, B, m.r, w.y, T, idx,
-                     pool, w.part);
-  const int gb = (int)((B + kThreads - 1) / kThreads);
+  const int nparts = mlp_fwd_grid(B);
   SNMF_DISPATCH_MLP(rank_pad(m.r),
-                    hipLaunchKernelGGL((k_mlp_back_rows<RP>), dim3(gb), dim3(kThreads), 0, s, m,
-                                       B, w.y, T, idx, pool, w.cache_a, w.cache_o, w.part, nparts,
-                                       mu, w.dO, w.dA))
+                    hipLaunchKernelGGL((k_mlp_fwd<RP>), dim3(nparts), dim3(kThreads), 0, s, m, B,
+                                       C, nullptr, w.y, BMap{}, idx, pool, T, w.cache_a,
+                                       w.cache_o, w.part))
+  // Row slabs of the gradient: as many as their FP64 partials fit the scratch (64 rows a
+  // slab at r <= 16, 192 at r = 64) up to 128, whole 32-row tiles each.
   const int P = mlp_params(m.r);
-  hipLaunchKernelGGL(k_mlp_grad, dim3((P + kThreads - 1) / kThreads), dim3(kThreads), 0, s, m.r,
-                     B, C, idx, pool, w.cache_a, w.dO, w.dA, w.grad);
-  hipLaunchKernelGGL(k_mlp_adam, dim3((P + kThreads - 1) / kThreads), dim3(kThreads), 0, s, m,
-                     w.grad, m.mom, m.vel, step, lr, 0.9f, 0.999f, 1e-8f);
+  int64_t ns = (int64_t)(w.gpart_bytes / ((size_t)P * 8));
+  if (ns > 128) ns = 128;
+  if (ns < 1) ns = 1;
+  int64_t rows_per = ((B + ns - 1) / ns + kMlpRows - 1) / kMlpRows * kMlpRows;
+  ns = (B + rows_per - 1) / rows_per;
+  double* gpart = ns > 1 ? w.gpart : nullptr;
+  SNMF_DISPATCH_MLP(rank_pad(m.r),
+                    hipLaunchKernelGGL((k_mlp_back<RP>), dim3((unsigned)ns, kMlpHidden / 32),
+                                       dim3(kThreads), 0, s, m, B, rows_per, w.y, C, T, idx, pool,
+                                       w.cache_a, w.cache_o, w.part, nparts, mu, w.grad, gpart))
+  hipLaunchKernelGGL(k_mlp_adam, dim3((P + 63) / 64), dim3(kThreads), 0, s, m, w.grad, gpart,
+                     (int)ns, m.mom, m.vel, step, lr, 0.9f, 0.999f, 1e-8f);
 }
 
 }  // namespace snmf

@@ -40,14 +40,15 @@ struct MlpDev {                  // device view of a warm-start network r -> 128
   float *mom, *vel;              // Adam moments (order M1, b1, M2, b2)
 };
 struct MlpWork {                 // per-minibatch scratch of a training step
-  float *y, *cache_a, *cache_o, *dO, *dA, *grad;
+  float *y, *cache_a, *cache_o, *grad;
+  double* gpart;                 // FP64 gradient partials of the row slabs, gpart_bytes of room
+  size_t gpart_bytes;
   double* part;                  // kMaxGrid x kNumPart loss partials; part[kMaxGrid*kNumPart]: loss
 };
 int mlp_params(int r);
 void launch_mlp_sync(const MlpDev& m, hipStream_t s);
 void launch_mlp_forward(const MlpDev& m, int64_t N, const float* C, const float* row_scale,
-                        float* Y, const BMap& bm, int grid, const int32_t* idx, int64_t pool,
-                        float* cache_a, float* cache_o, hipStream_t s);
+                        float* Y, const BMap& bm, int grid, hipStream_t s);
 void launch_mlp_train_step(const MlpDev& m, int64_t pool, int64_t B, const float* C,
                            const float* T, const int32_t* idx, float mu, float lr, int step,
                            const MlpWork& w, hipStream_t s);

@@ -46,7 +46,7 @@ MlpDev dev_of(const snmf_mlp* m) {
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct WorkLayout {
-  size_t y, a, o, dO, dA, grad, part, total;
+  size_t y, a, o, slabs, grad, part, total;
 };
 WorkLayout work_layout(int r, int64_t B) {
   WorkLayout w{};
@@ -57,10 +57,8 @@ WorkLayout work_layout(int r, int64_t B) {
   at += align256((size_t)B * kMlpHidden * 4);
   w.o = at;
   at += align256((size_t)B * r * 4);
-  w.dO = at;
-  at += align256((size_t)B * r * 4);
-  w.dA = at;
-  at += align256((size_t)B * kMlpHidden * 4);
+  w.slabs = at;  // the gradient's row slabs
+  at += align256((size_t)B * r * 4) + align256((size_t)B * kMlpHidden * 4);
   w.grad = at;
   at += align256((size_t)mlp_params(r) * 4);
   w.part = at;
@@ -164,8 +162,7 @@ snmf_status snmf_mlp_forward(const snmf_mlp* m, int64_t rows, const float* C,
   if (rows < 0) return fail(SNMF_E_SHAPE, "rows < 0");
   if (rows == 0) return SNMF_OK;
   if (!C || !Y) return fail(SNMF_E_ARG, "C and Y are required");
-  launch_mlp_forward(dev_of(m), rows, C, row_scale, Y, BMap{}, 0, nullptr, 0, nullptr, nullptr,
-                     (hipStream_t)stream);
+  launch_mlp_forward(dev_of(m), rows, C, row_scale, Y, BMap{}, 0, (hipStream_t)stream);
   HIP_TRY(hipGetLastError());
   return SNMF_OK;
 }
@@ -192,8 +189,8 @@ snmf_status snmf_mlp_train_step(const snmf_mlp* m, int64_t pool_rows, const floa
   mw.y = (float*)(w + L.y);
   mw.cache_a = (float*)(w + L.a);
   mw.cache_o = (float*)(w + L.o);
-  mw.dO = (float*)(w + L.dO);
-  mw.dA = (float*)(w + L.dA);
+  mw.gpart = (double*)(w + L.slabs);
+  mw.gpart_bytes = L.grad - L.slabs;
   mw.grad = (float*)(w + L.grad);
   mw.part = (double*)(w + L.part);
   hipStream_t s = (hipStream_t)stream;
@@ -263,7 +260,7 @@ snmf_status snmf_batch_warmstart(snmf_batch* b, int32_t nmodels, const snmf_mlp*
   SNMF_TRY(frame_async(b, Omega, b->B, b->C, nullptr));
   for (const auto& c : b->cls) {
     launch_mlp_forward(dev_of(pick[c.r]), 0, (const float*)b->C, nullptr, (float*)W0, b->bmap(c),
-                       c.blocks, nullptr, 0, nullptr, nullptr, b->s);
+                       c.blocks, b->s);
     HIP_TRY(hipGetLastError());
   }
   HIP_TRY(hipStreamSynchronize(b->s));

@@ -326,3 +326,28 @@ def test_warm_start_gain_on_detectable_graphs(S):
     assert gap[("learned", 1)] < gap[("random", 1)]
     assert gap[("frame", 1)] < gap[("random", 1)]
     assert its["learned"] <= its["frame"]
+
+
+@pytest.mark.parametrize("r,B", [(1, 1), (3, 31), (5, 33), (17, 32), (33, 200), (64, 1000),
+                                 (8, 9000), (16, 4096)])
+def test_mlp_train_step_slabs(S, r, B):
+    """Gradients at the edges of the backward's tiles: one row, partial 32-row tiles, ranks
+    that are no multiple of 16, one gradient slab and many."""
+    m = S.Mlp(_rand_init(r, 300 + r))
+    prm0 = m.params()
+    rng = np.random.default_rng(31 * r + B)
+    N, mu = B + 57, 0.7
+    C, T = rng.standard_normal((N, r)), rng.random((N, r))
+    idx = rng.choice(N, size=B, replace=False).astype(np.int32)
+    Ct = torch.from_numpy(C).to(DEV, torch.float32)
+    Tt = torch.from_numpy(T).to(DEV, torch.float32)
+    loss = m.train_step(Ct, Tt, torch.from_numpy(idx).to(DEV), mu, 1e-3, want_loss=True)
+    lo, go = WS.loss_and_grad(prm0, Ct.double().cpu().numpy()[idx],
+                              Tt.double().cpu().numpy()[idx], mu)
+    assert abs(loss - lo) <= 1e-5 * abs(lo)
+    g = m.adam_m.double().cpu().numpy() / float(np.float32(1) - np.float32(0.9))
+    at = 0
+    for k in ("M1", "b1", "M2", "b2"):
+        n = go[k].size
+        assert nrel(g[at: at + n].reshape(go[k].shape), go[k]) <= 1e-4, k
+        at += n
