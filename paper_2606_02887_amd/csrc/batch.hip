@@ -56,9 +56,11 @@ snmf_status bcheck_csr(snmf_batch* b, const snmf_matrix* M, const std::string& w
   if (f[0] || f[1]) return fail(SNMF_E_SHAPE, what + ": malformed CSR structure");
   if (b->p.validate && f[2] == 0) {
     if (b->prec == SNMF_F64)
-      launch_csr_symmetry<double>(M->rowptr, M->col, (const double*)M->val, M->n, b->flags, b->s);
+      launch_csr_symmetry<double>(M->rowptr, M->col, (const double*)M->val, M->n, M->nnz,
+                                  b->flags, b->s);
     else
-      launch_csr_symmetry<float>(M->rowptr, M->col, (const float*)M->val, M->n, b->flags, b->s);
+      launch_csr_symmetry<float>(M->rowptr, M->col, (const float*)M->val, M->n, M->nnz,
+                                 b->flags, b->s);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(f, b->flags, sizeof(f), hipMemcpyDeviceToHost, b->s));
     HIP_TRY(hipStreamSynchronize(b->s));

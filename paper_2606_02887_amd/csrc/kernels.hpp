@@ -176,7 +176,7 @@ void launch_csr_structure(const int64_t* rowptr, const int32_t* col, int64_t n, 
                           unsigned* flags, hipStream_t s);
 template <typename T>
 void launch_csr_symmetry(const int64_t* rowptr, const int32_t* col, const T* val, int64_t n,
-                         unsigned* flags, hipStream_t s);
+                         int64_t nnz, unsigned* flags, hipStream_t s);
 void launch_reset_state(State* st, double normA2, hipStream_t s);
 void launch_split_flat(const float* x, int64_t count, uint16_t* hi, uint16_t* lo, hipStream_t s);
 
@@ -193,12 +193,13 @@ int sketch_slabs(int64_t n, int64_t* rows_per);
 template <typename T>
 void launch_tsgram(const T* X, const T* Y, int64_t n, int w, double* part, double* C,
                    hipStream_t s);
-void launch_chol_inv(const double* G, int w, double shift_rel, double* R, double* Rinv,
-                     int32_t* flag, hipStream_t s);
+void launch_chol_inv(const double* G, int w, double shift_rel, double* Rinv, int32_t* flag,
+                     hipStream_t s);
 template <typename T>
 void launch_tsmm(const T* Y, int64_t n, int w, const double* M, int c, int absval, T* Q,
                  hipStream_t s);
-void launch_jacobi(const double* Tin, int w, double* A, double* V, double* ev, hipStream_t s);
+size_t jacobi_rot_bytes(int w);  // scratch of launch_jacobi: the recorded rotations
+void launch_jacobi(const double* Tin, int w, void* rot, double* V, double* ev, hipStream_t s);
 void launch_sketch_select(const double* ev, const double* V, int w, int k, int sqrt_scale,
                           double* lam, double* M, hipStream_t s);
 

@@ -24,8 +24,9 @@ namespace {
 struct SketchBufs {
   void* pool = nullptr;
   void *Y = nullptr, *Q = nullptr;
-  double *part = nullptr, *G = nullptr, *R = nullptr, *Rinv = nullptr, *Tm = nullptr,
-         *Aj = nullptr, *V = nullptr, *ev = nullptr, *M = nullptr;
+  double *part = nullptr, *G = nullptr, *Rinv = nullptr, *Tm = nullptr, *V = nullptr,
+         *ev = nullptr, *M = nullptr;
+  void* rot = nullptr;
   int32_t* flag = nullptr;
   unsigned* cflags = nullptr;
   ~SketchBufs() {
@@ -62,10 +63,9 @@ snmf_status sketch_run(const snmf_matrix* A, int k, int ell, int q, const T* Ome
   add(&b.Q, (size_t)n * ell * sizeof(T));
   add((void**)&b.part, (size_t)nslab * ww * 8);
   add((void**)&b.G, ww * 8);
-  add((void**)&b.R, ww * 8);
   add((void**)&b.Rinv, ww * 8);
   add((void**)&b.Tm, ww * 8);
-  add((void**)&b.Aj, ww * 8);
+  add(&b.rot, jacobi_rot_bytes(ell));
   add((void**)&b.V, ww * 8);
   add((void**)&b.ev, (size_t)ell * 8);
   add((void**)&b.M, ww * 8);
@@ -90,7 +90,7 @@ snmf_status sketch_run(const snmf_matrix* A, int k, int ell, int q, const T* Ome
     HIP_TRY(hipStreamSynchronize(s));
     if (f[0] || f[1]) return fail(SNMF_E_SHAPE, "A: malformed CSR structure");
     if (f[2] == 0) {
-      launch_csr_symmetry<T>(A->rowptr, A->col, (const T*)A->val, n, b.cflags, s);
+      launch_csr_symmetry<T>(A->rowptr, A->col, (const T*)A->val, n, A->nnz, b.cflags, s);
       HIP_TRY(hipGetLastError());
       HIP_TRY(hipMemcpyAsync(f, b.cflags, sizeof(f), hipMemcpyDeviceToHost, s));
       HIP_TRY(hipStreamSynchronize(s));
@@ -110,7 +110,7 @@ snmf_status sketch_run(const snmf_matrix* A, int k, int ell, int q, const T* Ome
   const double shift = 11.0 * ((double)n * ell + (double)ell * (ell + 1)) * 0x1p-53;
   auto chol_pass = [&](const T* X, T* Out, double sh) {
     launch_tsgram<T>(X, X, n, ell, b.part, b.G, s);
-    launch_chol_inv(b.G, ell, sh, b.R, b.Rinv, b.flag, s);
+    launch_chol_inv(b.G, ell, sh, b.Rinv, b.flag, s);
     launch_tsmm<T>(X, n, ell, b.Rinv, ell, 0, Out, s);
   };
   auto orth = [&]() {  // Y -> Q (Y is overwritten)
@@ -128,7 +128,7 @@ snmf_status sketch_run(const snmf_matrix* A, int k, int ell, int q, const T* Ome
   }
   apply(Q, Y);                                   // Y = A Q
   launch_tsgram<T>(Q, Y, n, ell, b.part, b.Tm, s);  // T = Q^T A Q
-  launch_jacobi(b.Tm, ell, b.Aj, b.V, b.ev, s);
+  launch_jacobi(b.Tm, ell, b.rot, b.V, b.ev, s);
   launch_sketch_select(b.ev, b.V, ell, k, svd ? 1 : 0, lam_out, b.M, s);
   launch_tsmm<T>(Q, n, ell, b.M, k, svd ? 1 : 0, out, s);
   HIP_TRY(hipGetLastError());

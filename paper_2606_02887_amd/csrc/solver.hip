@@ -214,9 +214,11 @@ snmf_status check_csr(snmf_plan* pl, const snmf_matrix* M, const char* what, boo
   if (f[0] || f[1]) return fail(SNMF_E_SHAPE, std::string(what) + ": malformed CSR structure");
   if (pl->p.validate && f[2] == 0) {
     if (pl->prec == SNMF_F64)
-      launch_csr_symmetry<double>(M->rowptr, M->col, (const double*)M->val, M->n, pl->flags, pl->s);
+      launch_csr_symmetry<double>(M->rowptr, M->col, (const double*)M->val, M->n, M->nnz,
+                                  pl->flags, pl->s);
     else
-      launch_csr_symmetry<float>(M->rowptr, M->col, (const float*)M->val, M->n, pl->flags, pl->s);
+      launch_csr_symmetry<float>(M->rowptr, M->col, (const float*)M->val, M->n, M->nnz,
+                                 pl->flags, pl->s);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(f, pl->flags, sizeof(f), hipMemcpyDeviceToHost, pl->s));
     HIP_TRY(hipStreamSynchronize(pl->s));

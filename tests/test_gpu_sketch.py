@@ -144,3 +144,14 @@ def test_sketch_error_codes(S):
     with pytest.raises(S.SnmfError) as e:
         S.svd_start(S.dense(A), 65, 0, torch.ones((50, 65), dtype=torch.float64, device=DEV))
     assert e.value.name == "E_SHAPE"
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("kind,n,rank,over,q", [("csr", 257, 1, 0, 1), ("csr", 300, 15, 2, 1),
+                                               ("csr", 999, 32, 1, 1), ("csr", 700, 64, 0, 1),
+                                               ("csr", 4097, 90, 6, 2), ("csr", 3333, 100, 27, 2),
+                                               ("csr", 2000, 118, 10, 2), ("dense", 130, 60, 68, 1)])
+def test_lai_sketch_widths(S, prec, kind, n, rank, over, q):
+    """The widths where the kernels change blocks (one column, 17, 33, 64, 96, 127, 128) and
+    row counts that end inside their tiles, against the oracle as above."""
+    test_lai_sketch_matches_oracle(S, prec, kind, n, rank, over, q)
