@@ -114,11 +114,15 @@ snmf_status bapass(snmf_batch* b, const T* P, T* B, hipStream_t s,
     const BInst& d = b->hinst[i];
     const snmf_matrix& A = b->A[d.prob];
     const int64_t nr = d.n * d.r;
+    const DenseSplit& sp = b->ds[d.prob];
     if (b->prec == SNMF_F64) {
-      launch_apass_f64((const double*)A.dense, A.ld, (const double*)(P + d.off), d.n, d.r,
-                       (double*)(B + d.off), b->states + i, s);
+      const bool one = sp.ksplit == 1;
+      launch_apass_f64((const double*)A.dense, A.ld, (const double*)(P + d.off), d.n, d.r, sp,
+                       one ? (double*)(B + d.off) : (double*)b->Bpart, nr, b->states + i, s);
+      if (!one)
+        launch_sum_parts<double>((const double*)b->Bpart, sp.ksplit, nr, (double*)(B + d.off), nr,
+                                 s);
     } else {
-      const DenseSplit& sp = b->ds[d.prob];
       launch_apass_f32((const float*)A.dense, A.ld, (const float*)(P + d.off), d.n, d.r, sp,
                        (float*)b->Bpart, nr, b->states + i, s);
       launch_sum_parts<float>((const float*)b->Bpart, sp.ksplit, nr, (float*)(B + d.off), nr, s);
@@ -354,10 +358,11 @@ snmf_status batch_create(int32_t nprob, const snmf_matrix* A, const int32_t* r, 
       sblk += G.nblk;
     }
     b->sblocks = sblk;
-  } else if (b->prec == SNMF_F32) {
+  } else if (b->prec != SNMF_BF16X3) {
     b->ds.resize(nprob);
     for (int g = 0; g < nprob; ++g) {
-      b->ds[g] = plan_dense_f32(b->n[g], A[g].ld, b->r[g], A[g].dense);
+      b->ds[g] = b->prec == SNMF_F64 ? plan_dense_f64(b->n[g])
+                                     : plan_dense_f32(b->n[g], A[g].ld, b->r[g], A[g].dense);
       b->ksplit_max = std::max(b->ksplit_max, b->ds[g].ksplit);
     }
   }
@@ -401,7 +406,8 @@ snmf_status batch_create(int32_t nprob, const snmf_matrix* A, const int32_t* r, 
   add(&b->Z, tb);
   add(&b->D, tb);
   add(&b->B, tb);
-  if (dense && b->prec == SNMF_F32) add(&b->Bpart, (size_t)b->ksplit_max * b->max_nr * b->esz);
+  if (dense && b->prec != SNMF_BF16X3)
+    add(&b->Bpart, (size_t)b->ksplit_max * b->max_nr * b->esz);
   if (dense && b->prec == SNMF_BF16X3) {
     for (int g = 0; g < nprob; ++g) {
       add((void**)&b->Ahi[g], (size_t)b->n[g] * b->ldb[g] * 2);

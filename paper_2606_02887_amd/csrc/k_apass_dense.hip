@@ -1,7 +1,7 @@
 // The A-pass B = A P for dense symmetric A: the product that dominates the per-iteration
 // cost O(n^2 r) of SNMPBB (Section 4.1 complexity list).  A is streamed once per call.
 //
-// * FP64: LDS-tiled VALU kernel (parity mode, small n).
+// * FP64: MFMA v_mfma_f64_16x16x4_f64, A and P read where they lie.
 // * FP32: MFMA v_mfma_f32_32x32x2f32.  Because A = A^T the kernel computes
 //   B^T = P^T A: rows of A feed the MFMA "B" operand, so every lane reads consecutive
 //   columns of one row of A and a wave touches two full 128-byte row segments per load.
@@ -23,48 +23,152 @@ typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
 // ----------------------------------------------------------------------------- FP64
+// B = A P on the FP64 matrix cores (16x16x4).  Grid: x = tiles of 16 MT output rows, y = K
+// splits of kchunk columns of A (a multiple of 64; panel y at Bpart + y pstride); the four
+// wavefronts of a workgroup take contiguous quarters of the split and are added as
+// (w0 + w1) + (w2 + w3) in LDS.  Lane l (row l % 16 of a tile, group g = l / 16) loads four
+// consecutive values k = k0 + 4 g .. + 3 of its row per 16 columns of A (a wavefront covers
+// whole 128-byte lines); MFMA s pairs them with the rows k0 + 4 g + s of P, NB = ceil(r / 16)
+// blocks of columns, read where they lie (every tile reads P, which stays in L2).
+// With rj.G set, grid column 0 is rho's: one workgroup computes rho = ||G||_2 beside the
+// tiles, dispatched first because it sets the launch's length at small n.
+// Bound by latency up to n of some thousand, then by the FP64 matrix rate (2 n^2 r: 121 us
+// at n = 8192, r = 64).  The former kernel (32 rows per workgroup on the vector units, all of
+// K in one workgroup, rho in a launch of its own) took 145 + 20 us at n = 1000, r = 20 and
+// 48 + 9 us at n = 200, r = 5; so 5.9 and 5.4 us, 19.0 and 8.8 us with rho beside it.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));  // 8-byte aligned pair
+
+template <int MT, int NB>
 __global__ __launch_bounds__(256) void k_apass_f64(const double* __restrict__ A, int64_t lda,
                                                    const double* __restrict__ P, int64_t n, int r,
-                                                   double* __restrict__ B,
-                                                   const State* __restrict__ st) {
+                                                   int64_t kchunk, double* __restrict__ Bpart,
+                                                   int64_t pstride, const State* __restrict__ st,
+                                                   RhoJob rj) {
   if (st->done) return;
-  constexpr int TR = 32, TK = 64;
-  __shared__ double sA[TR][TK + 1];
-  __shared__ double sP[TK][kMaxRank];
-  const int tid = threadIdx.x, c = tid & 63, rs = tid >> 6;
-  const int64_t row0 = (int64_t)blockIdx.x * TR;
-  double acc[8];
+  if (rj.G && blockIdx.x == 0) {
+    if (blockIdx.y == 0) rho_body(rj.G, rj.r, rj.st);
+    return;
+  }
+  constexpr int U = MT * NB <= 2 ? 3 : MT * NB <= 4 ? 2 : 1;  // 16-column blocks per batch
+  __shared__ double sacc[2][MT * NB][4][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c16 = lane & 15, g = lane >> 4;
+  const int64_t row0 = (int64_t)(blockIdx.x - (rj.G ? 1 : 0)) * 16 * MT;
+  const int64_t kb = (int64_t)blockIdx.y * kchunk + wave * (kchunk / 4);
+  const int64_t ke = kb + kchunk / 4 < n ? kb + kchunk / 4 : n;
+  f64x4 acc[MT][NB];
 #pragma unroll
-  for (int p = 0; p < 8; ++p) acc[p] = 0.0;
-  for (int64_t k0 = 0; k0 < n; k0 += TK) {
-    __syncthreads();
-    for (int e = tid; e < TR * TK; e += 256) {
-      const int i = e / TK, kk = e % TK;
-      const int64_t row = row0 + i, col = k0 + kk;
-      sA[i][kk] = (row < n && col < n) ? A[row * lda + col] : 0.0;
-    }
-    for (int e = tid; e < TK * kMaxRank; e += 256) {
-      const int kk = e / kMaxRank, cc = e % kMaxRank;
-      const int64_t k = k0 + kk;
-      sP[kk][cc] = (k < n && cc < r) ? P[k * r + cc] : 0.0;
-    }
-    __syncthreads();
-    if (c < r) {
-#pragma unroll 4
-      for (int kk = 0; kk < TK; ++kk) {
-        const double pv = sP[kk][c];
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int p = 0; p < 8; ++p) acc[p] = __builtin_fma(sA[rs + 4 * p][kk], pv, acc[p]);
+    for (int q = 0; q < NB; ++q) acc[mt][q] = f64x4{0.0, 0.0, 0.0, 0.0};
+  // rows past n and columns past r repeat a valid one: they feed only what is never stored
+  const double* ar[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int64_t row = row0 + 16 * mt + c16;
+    ar[mt] = A + (row < n ? row : n - 1) * lda;
+  }
+  int pc[NB];
+#pragma unroll
+  for (int q = 0; q < NB; ++q) pc[q] = 16 * q + c16 < r ? 16 * q + c16 : r - 1;
+  struct Batch {
+    double a[U][MT][4], p[U][4][NB];
+  };
+  auto load = [&](Batch& x, int64_t k0) {
+    if (k0 + 16 * U <= ke) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t k = k0 + 16 * u + 4 * g;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          const f64x2u v0 = *(const f64x2u*)(ar[mt] + k), v1 = *(const f64x2u*)(ar[mt] + k + 2);
+          x.a[u][mt][0] = v0[0];
+          x.a[u][mt][1] = v0[1];
+          x.a[u][mt][2] = v1[0];
+          x.a[u][mt][3] = v1[1];
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int q = 0; q < NB; ++q) x.p[u][s][q] = P[(k + s) * r + pc[q]];
       }
-    }
-  }
-  if (c < r) {
+    } else {  // the range's end: columns past it are zeros of A against a valid row of P
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      const int64_t row = row0 + rs + 4 * p;
-      if (row < n) B[row * r + c] = acc[p];
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int64_t k = k0 + 16 * u + 4 * g + s;
+          const int64_t kk = k < ke ? k : ke - 1;
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            const double v = ar[mt][kk];
+            x.a[u][mt][s] = k < ke ? v : 0.0;
+          }
+#pragma unroll
+          for (int q = 0; q < NB; ++q) x.p[u][s][q] = P[kk * r + pc[q]];
+        }
+    }
+  };
+  auto mma = [&](const Batch& x) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int q = 0; q < NB; ++q)
+            acc[mt][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.a[u][mt][s], x.p[u][s][q],
+                                                              acc[mt][q], 0, 0, 0);
+  };
+  if (kb < ke) {
+    Batch x, y;
+    load(x, kb);
+    for (int64_t k0 = kb; k0 < ke; k0 += 32 * U) {
+      const bool two = k0 + 16 * U < ke;
+      if (two) load(y, k0 + 16 * U);
+      mma(x);
+      if (!two) break;
+      if (k0 + 32 * U < ke) load(x, k0 + 32 * U);
+      mma(y);
     }
   }
+  auto put = [&](int slot) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) sacc[slot][mt * NB + q][v][lane] = acc[mt][q][v];
+  };
+  auto add = [&](int slot) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[mt][q][v] += sacc[slot][mt * NB + q][v][lane];
+  };
+  if (wave & 1) put(wave >> 1);
+  __syncthreads();
+  if (!(wave & 1)) add(wave >> 1);
+  __syncthreads();
+  if (wave == 2) put(0);
+  __syncthreads();
+  if (wave != 0) return;
+  add(0);
+  // D[l / 16 + 4 v][l % 16]
+  double* __restrict__ out = Bpart + (int64_t)blockIdx.y * pstride;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t row = row0 + 16 * mt + g + 4 * v;
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+        if (row < n && 16 * q + c16 < r) out[row * r + 16 * q + c16] = acc[mt][q][v];
+    }
 }
 
 // ----------------------------------------------------------------------------- FP32 MFMA
@@ -552,10 +656,40 @@ template void launch_sum_parts<float>(const float*, int, int64_t, float*, int64_
 template void launch_sum_parts<double>(const double*, int, int64_t, double*, int64_t, hipStream_t);
 
 // ----------------------------------------------------------------------------- launchers
-void launch_apass_f64(const double* A, int64_t lda, const double* P, int64_t n, int r, double* B,
-                      const State* st, hipStream_t s) {
-  const unsigned gx = (unsigned)((n + 31) / 32);
-  hipLaunchKernelGGL(k_apass_f64, dim3(gx), dim3(256), 0, s, A, lda, P, n, r, B, st);
+// Tiles of 16 rows (32 from n = 4096: half the reads of P, 256 tiles still fill the chip) and
+// K splits up to two workgroups per CU, of at least 128 columns (two 16-column blocks per
+// wavefront: a shorter one is all pipeline start) and at most 8 (their panels are read back).
+DenseSplit plan_dense_f64(int64_t n) {
+  DenseSplit d;
+  d.wide = n >= 4096;
+  d.gx = d.wide ? (n + 31) / 32 : (n + 15) / 16;
+  int64_t ks = 512 / d.gx;
+  if (ks > n / 128) ks = n / 128;
+  if (ks > 8) ks = 8;
+  if (ks < 1) ks = 1;
+  d.kchunk = ((n + ks - 1) / ks + 63) / 64 * 64;
+  d.ksplit = (int)((n + d.kchunk - 1) / d.kchunk);
+  return d;
+}
+
+void launch_apass_f64(const double* A, int64_t lda, const double* P, int64_t n, int r,
+                      const DenseSplit& d, double* Bpart, int64_t pstride, const State* st,
+                      hipStream_t s, const RhoJob& rj) {
+  const dim3 grid((unsigned)d.gx + (rj.G ? 1u : 0u), (unsigned)d.ksplit), blk(256);
+#define SNMF_F64_GO(MT, NB)                                                                     \
+  hipLaunchKernelGGL((k_apass_f64<MT, NB>), grid, blk, 0, s, A, lda, P, n, r, d.kchunk, Bpart,  \
+                     pstride, st, rj)
+  switch ((r + 15) / 16 + (d.wide ? 4 : 0)) {
+    case 1: SNMF_F64_GO(1, 1); break;
+    case 2: SNMF_F64_GO(1, 2); break;
+    case 3: SNMF_F64_GO(1, 3); break;
+    case 4: SNMF_F64_GO(1, 4); break;
+    case 5: SNMF_F64_GO(2, 1); break;
+    case 6: SNMF_F64_GO(2, 2); break;
+    case 7: SNMF_F64_GO(2, 3); break;
+    default: SNMF_F64_GO(2, 4);
+  }
+#undef SNMF_F64_GO
 }
 
 bool dense_f32_wide(int64_t n, int64_t lda, int r, const void* A) {

@@ -59,25 +59,29 @@ struct TileCfg {
 
 // Element ownership and the tile product.  Every thread owns 8 elements of a TM x RP
 // tile (TM * RP = 2048).
-//  * MFMA layout (FP32, RP >= 16): the tile is cut into 8 blocks of 16 x 16 (row-major
-//    block order, RP/16 blocks per row); wave w owns blocks 2w and 2w+1; in block b lane l
-//    owns rows 4(l/16) + v, v = 0..3, column l%16 -- exactly the output layout of
-//    v_mfma_f32_16x16x4f32, so the products land in the owner's registers.
-//  * VALU layout (FP64 or RP < 16): thread owns rows tid/RP + p * 256/RP, column tid%RP.
+//  * MFMA layout (RP >= 16): the tile is cut into 8 blocks of 16 x 16 (row-major block
+//    order, RP/16 blocks per row); wave w owns blocks 2w and 2w+1; in block b lane l owns
+//    column l%16 and, v = 0..3, rows 4(l/16) + v (FP32) or l/16 + 4 v (FP64) -- exactly the
+//    output layouts of v_mfma_f32_16x16x4f32 and v_mfma_f64_16x16x4f64, so the products land
+//    in the owner's registers.  Both instructions are one FMA chain over their four k, so
+//    the products have the bits of the vector loop below.
+//  * VALU layout (RP < 16): thread owns rows tid/RP + p * 256/RP, column tid%RP.
 // LDS tiles are zero-padded to RP columns and G to RP x RP; pitches are padded against
-// bank conflicts of the MFMA operand reads.
+// bank conflicts of the MFMA operand reads (FP64, n = 1000, r = 20: a fused kernel 12.4 us
+// and the init 17.3 us on the vector units, 8.4 and 11.5 us on the matrix cores).
 template <typename T, int RP>
 struct Lay {
-  static constexpr bool MF = sizeof(T) == 4 && RP >= 16;
+  static constexpr bool MF = RP >= 16;
+  static constexpr bool F8 = sizeof(T) == 8;
   static constexpr int TM = TileCfg<RP>::TM;
-  static constexpr int YP = MF ? RP + 1 : RP;   // tile pitch
-  static constexpr int GP = MF ? RP + 16 : RP;  // G pitch
+  static constexpr int YP = MF ? (F8 ? RP + 2 : RP + 1) : RP;                // tile pitch
+  static constexpr int GP = MF ? (F8 && RP == 16 ? RP : RP + 16) : RP;       // G pitch
   __device__ static __forceinline__ void rc(int p, int& lr, int& col) {
     if constexpr (MF) {
       const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
       const int blk = 2 * w + (p >> 2), v = p & 3;
       constexpr int NBC = RP / 16;
-      lr = 16 * (blk / NBC) + 4 * (l >> 4) + v;
+      lr = 16 * (blk / NBC) + (F8 ? (l >> 4) + 4 * v : 4 * (l >> 4) + v);
       col = 16 * (blk % NBC) + (l & 15);
     } else {
       lr = (int)threadIdx.x / RP + p * (kThreads / RP);
@@ -98,7 +102,6 @@ template <>
 struct Vec4<double> {
   typedef double type __attribute__((ext_vector_type(4)));
 };
-typedef float f32x4m __attribute__((ext_vector_type(4)));
 
 // acc[p] = sum_j sY[row_p][j] * sG[j][col_p] for the owned elements.
 template <typename T, int RP>
@@ -112,12 +115,15 @@ __device__ __forceinline__ void tile_gemm(const T* __restrict__ sY, const T* __r
     for (int b = 0; b < 2; ++b) {
       const int blk = 2 * w + b;
       const int r0 = 16 * (blk / NBC), c0 = 16 * (blk % NBC);
-      f32x4m d = {0.f, 0.f, 0.f, 0.f};
+      typename Vec4<T>::type d = {T(0), T(0), T(0), T(0)};
 #pragma unroll
       for (int kk = 0; kk < RP; kk += 4) {
-        const float a = sY[(r0 + (l & 15)) * L::YP + kk + (l >> 4)];
-        const float bb = sG[(kk + (l >> 4)) * L::GP + c0 + (l & 15)];
-        d = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bb, d, 0, 0, 0);
+        const T a = sY[(r0 + (l & 15)) * L::YP + kk + (l >> 4)];
+        const T bb = sG[(kk + (l >> 4)) * L::GP + c0 + (l & 15)];
+        if constexpr (sizeof(T) == 8)
+          d = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bb, d, 0, 0, 0);
+        else
+          d = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bb, d, 0, 0, 0);
       }
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[4 * b + v] = d[v];

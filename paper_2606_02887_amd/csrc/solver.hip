@@ -237,21 +237,17 @@ constexpr int kGraphRun = 8;
 
 // ------------------------------------------------------------------ one half-step
 // B = A P (partials in Bpart).  With rj.G set, rho = ||G||_2 as well: in one more
-// workgroup of the A-pass launch (FP64 dense: a launch of its own just before it).
+// workgroup of the A-pass launch.
 template <typename T>
 snmf_status apass(snmf_plan* pl, const T* P, hipStream_t s, const RhoJob& rj = RhoJob{}) {
   const int64_t n = pl->n;
   const int r = pl->r;
   const int32_t* gate = &pl->st->done;
-  if (rj.G && pl->A.fmt == SNMF_DENSE && pl->prec == SNMF_F64) {
-    launch_rho(rj.G, rj.r, rj.st, s);
-    HIP_TRY(hipGetLastError());
-  }
   switch (pl->A.fmt) {
     case SNMF_DENSE:
       if (pl->prec == SNMF_F64) {
-        launch_apass_f64((const double*)pl->A.dense, pl->A.ld, (const double*)P, n, r,
-                         (double*)pl->Bpart, pl->st, s);
+        launch_apass_f64((const double*)pl->A.dense, pl->A.ld, (const double*)P, n, r, pl->ds,
+                         (double*)pl->Bpart, n * r, pl->st, s, rj);
       } else if (pl->prec == SNMF_F32) {
         launch_apass_f32((const float*)pl->A.dense, pl->A.ld, (const float*)P, n, r, pl->ds,
                          (float*)pl->Bpart, n * r, pl->st, s, rj);
@@ -275,7 +271,7 @@ snmf_status apass(snmf_plan* pl, const T* P, hipStream_t s, const RhoJob& rj = R
 }
 
 int ksplit_of(const snmf_plan* pl) {
-  return (pl->A.fmt == SNMF_DENSE && pl->prec != SNMF_F64) ? pl->ds.ksplit : 1;
+  return pl->A.fmt == SNMF_DENSE ? pl->ds.ksplit : 1;
 }
 
 // Start of a half-step up to and including init: G, rho (in or just before the A-pass,
@@ -487,12 +483,13 @@ snmf_status plan_init(snmf_plan* pl, const snmf_matrix* A, int32_t r, const snmf
   const int64_t n = pl->n;
   const size_t nr = (size_t)n * r * pl->esz;
   int ksplit = 1;
+  if (A->fmt == SNMF_DENSE && pl->prec == SNMF_F64) pl->ds = plan_dense_f64(n);
   if (A->fmt == SNMF_DENSE && pl->prec == SNMF_F32) pl->ds = plan_dense_f32(n, A->ld, r, A->dense);
   if (A->fmt == SNMF_DENSE && pl->prec == SNMF_BF16X3) {
     pl->ds = plan_dense_bf16(n);
     pl->ldb = (n + 63) / 64 * 64;
   }
-  if (A->fmt == SNMF_DENSE && pl->prec != SNMF_F64) ksplit = pl->ds.ksplit;
+  if (A->fmt == SNMF_DENSE) ksplit = pl->ds.ksplit;
   pl->gram_blocks = gram_blocks(n);
   const int lai_nb = lai_blocks(n);
   // carve one allocation (a fixed table: the allocation-free path allocates nothing on the

@@ -179,3 +179,24 @@ def test_lai_apass(S, prec, n, ell, r):
     mag = Ua @ (np.abs(lam)[:, None] * (Ua.T @ np.abs(Pt.double().cpu().numpy())))
     assert comp_rel(B.cpu().numpy(), ref, mag) <= (1e-13 if prec == "f64" else 2e-6)
     pl.close()
+
+
+@pytest.mark.parametrize("n,r,pad", [(16, 16, 0), (17, 17, 1), (127, 3, 0), (128, 32, 3),
+                                     (129, 33, 0), (257, 48, 1), (1000, 49, 0), (2500, 20, 7),
+                                     (4095, 5, 0), (4097, 64, 1), (4100, 17, 0)])
+def test_dense_apass_f64_edges(S, n, r, pad):
+    """The FP64 product at the edges of its tiles (16 and 32 rows, 16 columns), its K splits
+    and the wavefronts' quarters; padding columns (odd leading dimensions among them) hold
+    NaN and must not be read into the result.  The product adds n terms in FP64:
+    |error| <= n 2^-53 sum |a| |p| entrywise (both sides), 1e-12 normwise."""
+    rng = np.random.default_rng(n + r)
+    A = rng.random((n, n))
+    A = 0.5 * (A + A.T)
+    buf = torch.full((n, n + pad), float("nan"), dtype=torch.float64, device=DEV)
+    buf[:, :n] = torch.from_numpy(A).to(DEV)
+    P = rng.random((n, r))
+    Pt = torch.from_numpy(P).to(DEV)
+    with S.Plan(S.dense(buf[:, :n]), r, S.params(prec=S.F64, max_outer=1)) as pl:
+        B = torch.empty_like(Pt)
+        pl.apass(Pt, B)
+    assert nrel(B.cpu().numpy(), A @ P) <= 1e-12
