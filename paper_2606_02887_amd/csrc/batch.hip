@@ -34,10 +34,9 @@ namespace {
 snmf_status bstats(snmf_batch* b, const void* x, int64_t rows, int64_t cols, int64_t ld,
                    double* out3) {
   if (b->prec == SNMF_F64)
-    launch_stats2d<double>((const double*)x, rows, cols, ld, b->part, b->dots,
-                           b->counters + C_NORM, b->s);
+    launch_stats2d<double>((const double*)x, rows, cols, ld, b->part, b->dots, b->s);
   else
-    launch_stats2d<float>((const float*)x, rows, cols, ld, b->part, b->dots, b->counters + C_NORM,
+    launch_stats2d<float>((const float*)x, rows, cols, ld, b->part, b->dots,
                           b->s);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipMemcpyAsync(out3, b->dots, 3 * sizeof(double), hipMemcpyDeviceToHost, b->s));
@@ -428,9 +427,9 @@ snmf_status batch_create(int32_t nprob, const snmf_matrix* A, const int32_t* r, 
   add((void**)&b->traces, (size_t)b->ninst * b->trace_stride * 8);
   add((void**)&b->states, (size_t)b->ninst * sizeof(State));
   add((void**)&b->flag, sizeof(int32_t));
+  add((void**)&b->bout, (size_t)b->ninst * sizeof(BOut));
   add((void**)&b->part, (size_t)2 * kMaxGrid * kNumPart * 8);
   add((void**)&b->dots, 64 * 8);
-  add((void**)&b->counters, C_COUNT * sizeof(unsigned));
   add((void**)&b->flags, 4 * sizeof(unsigned));
   add((void**)&b->dinst, (size_t)b->ninst * sizeof(BInst));
   add((void**)&b->blk_tab, btab.size() * 4);
@@ -447,7 +446,6 @@ snmf_status batch_create(int32_t nprob, const snmf_matrix* A, const int32_t* r, 
     *q.first = (char*)b->pool + o;
     o += q.second;
   }
-  HIP_TRY(hipMemsetAsync(b->counters, 0, C_COUNT * sizeof(unsigned), b->s));
   HIP_TRY(hipMemsetAsync(b->states, 0, (size_t)b->ninst * sizeof(State), b->s));
 
   // ---- input checks and ||A_g||^2
@@ -505,20 +503,42 @@ snmf_status batch_solve(snmf_batch* b, const void* const* W0, void* const* W_out
     HIP_TRY(hipStreamWaitEvent(b->s, b->ev_in, 0));
   }
   const int S = b->S;
-  for (int g = 0; g < b->nprob; ++g) {
-    const int64_t cnt = (int64_t)S * b->n[g] * b->r[g];
-    if (b->p.validate) {
-      double st3[3];
-      SNMF_TRY(bstats(b, W0[g], 1, cnt, cnt, st3));
-      if (st3[2] > 0) return fail(SNMF_E_NONFINITE, "W0 has NaN/Inf entries");
-      if (st3[1] > 0) return fail(SNMF_E_NEGATIVE, "W0 has negative entries");
+  // the starts in and the results out, kCopySegs arrays per launch
+  auto copy = [&](bool in) {
+    CopyTab t{};
+    for (int g = 0; g < b->nprob; ++g) {
+      const int64_t cnt = (int64_t)S * b->n[g] * b->r[g];
+      const size_t off = (size_t)b->hinst[g * S].off * b->esz;
+      void* const W = (char*)b->Wb + off;
+      void* const H = (char*)b->Hb + off;
+      if (in) {
+        t.s[t.n++] = {W0[g], W, H, cnt};
+      } else {
+        t.s[t.n++] = {W, W_out[g], nullptr, cnt};
+        t.s[t.n++] = {H, Ht_out[g], nullptr, cnt};
+      }
+      if (t.n < kCopySegs && g + 1 < b->nprob) continue;
+      unsigned* const bad = b->p.validate ? b->flags : nullptr;
+      if (b->prec == SNMF_F64) launch_copy<double>(t, in, bad, b->s);
+      else launch_copy<float>(t, in, bad, b->s);
+      t.n = 0;
+      t.base = g + 1;
     }
-    const size_t off = (size_t)b->hinst[g * S].off * b->esz;
-    HIP_TRY(hipMemcpyAsync((char*)b->Wb + off, W0[g], cnt * b->esz, hipMemcpyDeviceToDevice, b->s));
-    HIP_TRY(hipMemcpyAsync((char*)b->Hb + off, W0[g], cnt * b->esz, hipMemcpyDeviceToDevice, b->s));
-  }
-  launch_breset(b->states, b->dinst, b->ninst, b->s);
+  };
+  auto check = [&](unsigned bad) -> snmf_status {
+    if (bad == kCopyOk) return SNMF_OK;
+    if ((bad & 1u) == 0) return fail(SNMF_E_NONFINITE, "W0 has NaN/Inf entries");
+    return fail(SNMF_E_NEGATIVE, "W0 has negative entries");
+  };
+  launch_breset(b->states, b->dinst, b->ninst, b->s, b->flags);
+  copy(true);
   HIP_TRY(hipGetLastError());
+  unsigned bad = kCopyOk;
+  if (b->p.validate) {  // one host wait for all starts
+    HIP_TRY(hipMemcpyAsync(&bad, b->flags, sizeof(bad), hipMemcpyDeviceToHost, b->s));
+    HIP_TRY(hipStreamSynchronize(b->s));
+    SNMF_TRY(check(bad));
+  }
   const int every = std::max(1, b->p.check_every);
   if (b->p.use_graph && !b->gexec) {
     HIP_TRY(hipStreamBeginCapture(b->s, hipStreamCaptureModeThreadLocal));
@@ -549,25 +569,19 @@ snmf_status batch_solve(snmf_batch* b, const void* const* W0, void* const* W_out
     }
   }
   SNMF_TRY(b->prec == SNMF_F64 ? bfinalize<double>(b, b->s) : bfinalize<float>(b, b->s));
-  for (int g = 0; g < b->nprob; ++g) {
-    const int64_t cnt = (int64_t)S * b->n[g] * b->r[g];
-    const size_t off = (size_t)b->hinst[g * S].off * b->esz;
-    HIP_TRY(hipMemcpyAsync(W_out[g], (char*)b->Wb + off, cnt * b->esz, hipMemcpyDeviceToDevice, b->s));
-    HIP_TRY(hipMemcpyAsync(Ht_out[g], (char*)b->Hb + off, cnt * b->esz, hipMemcpyDeviceToDevice, b->s));
-  }
-  std::vector<State> hs(b->ninst);
-  HIP_TRY(hipMemcpyAsync(hs.data(), b->states, hs.size() * sizeof(State), hipMemcpyDeviceToHost,
+  copy(false);
+  launch_bout(b->states, b->ninst, b->bout, b->s);
+  HIP_TRY(hipGetLastError());
+  std::vector<BOut> hs(b->ninst);
+  HIP_TRY(hipMemcpyAsync(hs.data(), b->bout, hs.size() * sizeof(BOut), hipMemcpyDeviceToHost,
                          b->s));
   if (traces)
     HIP_TRY(hipMemcpyAsync(traces, b->traces, (size_t)b->ninst * b->trace_stride * 8,
                            hipMemcpyDeviceToHost, b->s));
   HIP_TRY(hipStreamSynchronize(b->s));
   const double hz = snmf_clock_rate_hz();
-  bool broke = false;
-  for (int i = 0; i < b->ninst; ++i) {
-    const State& h = hs[i];
-    broke = broke || h.status != 0;
-    if (!infos) continue;
+  for (int i = 0; infos && i < b->ninst; ++i) {
+    const BOut& h = hs[i];
     snmf_info& info = infos[i];
     std::memset(&info, 0, sizeof(info));
     info.status = h.status;
@@ -576,13 +590,13 @@ snmf_status batch_solve(snmf_batch* b, const void* const* W0, void* const* W_out
     info.inner_total = h.inner_total;
     info.ls_evals = h.ls_evals;
     info.ls_exhausted = h.ls_exhausted;
-    info.res_WH = h.res_last;
-    info.res_WWt = h.resww_last;
-    info.sym_gap = h.sym_last;
-    info.pg_norm = h.pg_last;
-    info.objective = h.f_last;
+    info.res_WH = h.res;
+    info.res_WWt = h.resww;
+    info.sym_gap = h.sym;
+    info.pg_norm = h.pg;
+    info.objective = h.f;
     info.normA2 = h.normA2;
-    info.seconds = (double)(h.t_hstep - h.t0) / hz;
+    info.seconds = (double)h.t_last / hz;
     info.seconds_to_target = h.converged_at > 0 ? (double)h.t_conv / hz : -1.0;
   }
   if (user) {
@@ -591,7 +605,6 @@ snmf_status batch_solve(snmf_batch* b, const void* const* W0, void* const* W_out
   }
   // an instance that broke down (e.g. its factor collapsed to zero, rho = 0) is reported
   // in its own record; the batch call itself succeeds
-  (void)broke;
   return SNMF_OK;
 }
 

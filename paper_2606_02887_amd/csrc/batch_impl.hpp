@@ -54,8 +54,9 @@ struct snmf_batch {
   double *gpart = nullptr, *partsA = nullptr, *partsB = nullptr, *partsC = nullptr;
   double *traces = nullptr, *part = nullptr, *dots = nullptr;
   State* states = nullptr;
+  snmf::BOut* bout = nullptr;        // every instance's results, for the read back
   int32_t* flag = nullptr;
-  unsigned *counters = nullptr, *flags = nullptr;
+  unsigned* flags = nullptr;
   BInst* dinst = nullptr;
   int32_t *blk_tab = nullptr, *gblk_tab = nullptr, *sblk_tab = nullptr;
   BGraph* dgraph = nullptr;

@@ -18,9 +18,6 @@ constexpr int kSketchMaxW = 128;     // widest sketch (rank + oversampling) of t
 constexpr int kKnnMaxDim = 64;       // largest point dimension of the K-nearest-neighbour search
 constexpr int kKnnMaxK = 64;         // largest K of the K-nearest-neighbour search
 
-// Counters of the setup kernels that finish a reduction in their last workgroup.
-enum Counter { C_GRAM = 0, C_INIT, C_STEP1, C_STEP2, C_NORM, C_LAI, C_LAPRED, C_MISC, C_COUNT };
-
 // Scalars of the iteration that live on the device for the whole solve.
 // Hot-path kernels never finish a reduction inside themselves: each writes FP64 partial
 // sums per workgroup, and the NEXT kernel re-reduces those partials in every workgroup in
@@ -51,6 +48,33 @@ struct State {
   int32_t converged_at;        // first outer iteration meeting the target (1-based), 0 none
   int32_t trace_len;
   int64_t ls_evals, ls_exhausted, inner_total;
+};
+
+// Start and end of a solve: up to kCopySegs arrays copied by one launch (segment q takes the
+// workgroups blk0[q] .. blk0[q + 1] - 1).
+constexpr int kCopySegs = 32;
+struct CopySeg {
+  const void* src;
+  void* d0;
+  void* d1;        // second copy, or nullptr
+  int64_t count;   // elements
+};
+struct CopyTab {
+  CopySeg s[kCopySegs];
+  int32_t blk0[kCopySegs + 1];
+  int32_t n;       // segments
+  int32_t base;    // number of the first one over all launches
+};
+// What a check of copied values found: kCopyOk, or 2 q + (0: non-finite, 1: negative) for the
+// first segment q with such a value.
+constexpr unsigned kCopyOk = ~0u;
+
+// Results of one instance of a batched solve, gathered for one small read back.
+struct BOut {
+  int32_t status, outer, converged_at, pad;
+  int64_t inner_total, ls_evals, ls_exhausted;
+  double res, resww, sym, pg, f, normA2;
+  uint64_t t_last, t_conv;
 };
 
 // Scalar parameters passed by value to every kernel that needs them.
@@ -212,23 +236,6 @@ __device__ __forceinline__ void block_sum_emit(const double (&v)[K], double* sta
   int s;
   const double a = slot_sum<K>(v, stage, s);
   if (s < K && (threadIdx.x & 15) == 15) emit(s, a);
-}
-
-// Release this block's partials; returns true in every thread of the last block to
-// arrive (which then sees all partials).  The last block resets the counter.
-__device__ __forceinline__ bool arrive_last(unsigned int* counter, unsigned int nblocks) {
-  __shared__ int s_last;
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned int prev = atomicAdd(counter, 1u);
-    s_last = (prev == nblocks - 1) ? 1 : 0;
-    if (s_last) atomicExch(counter, 0u);
-  }
-  __syncthreads();
-  const bool last = s_last != 0;
-  if (last) __threadfence();
-  return last;
 }
 
 // Fixed-order reduction of nb rows of K partials (row-major [nb][kNumPart]) by one

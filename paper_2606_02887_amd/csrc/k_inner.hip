@@ -81,7 +81,10 @@ struct Lay {
       const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
       const int blk = 2 * w + (p >> 2), v = p & 3;
       constexpr int NBC = RP / 16;
-      lr = 16 * (blk / NBC) + (F8 ? (l >> 4) + 4 * v : 4 * (l >> 4) + v);
+      if constexpr (F8)
+        lr = 16 * (blk / NBC) + (l >> 4) + 4 * v;
+      else
+        lr = 16 * (blk / NBC) + 4 * (l >> 4) + v;
       col = 16 * (blk % NBC) + (l & 15);
     } else {
       lr = (int)threadIdx.x / RP + p * (kThreads / RP);
@@ -102,6 +105,8 @@ template <>
 struct Vec4<double> {
   typedef double type __attribute__((ext_vector_type(4)));
 };
+typedef float f32x4m __attribute__((ext_vector_type(4)));
+typedef double f64x4m __attribute__((ext_vector_type(4)));
 
 // acc[p] = sum_j sY[row_p][j] * sG[j][col_p] for the owned elements.
 template <typename T, int RP>
@@ -115,18 +120,27 @@ __device__ __forceinline__ void tile_gemm(const T* __restrict__ sY, const T* __r
     for (int b = 0; b < 2; ++b) {
       const int blk = 2 * w + b;
       const int r0 = 16 * (blk / NBC), c0 = 16 * (blk % NBC);
-      typename Vec4<T>::type d = {T(0), T(0), T(0), T(0)};
+      if constexpr (L::F8) {
+        f64x4m d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int kk = 0; kk < RP; kk += 4) {
-        const T a = sY[(r0 + (l & 15)) * L::YP + kk + (l >> 4)];
-        const T bb = sG[(kk + (l >> 4)) * L::GP + c0 + (l & 15)];
-        if constexpr (sizeof(T) == 8)
+        for (int kk = 0; kk < RP; kk += 4) {
+          const double a = sY[(r0 + (l & 15)) * L::YP + kk + (l >> 4)];
+          const double bb = sG[(kk + (l >> 4)) * L::GP + c0 + (l & 15)];
           d = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bb, d, 0, 0, 0);
-        else
-          d = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bb, d, 0, 0, 0);
-      }
+        }
 #pragma unroll
-      for (int v = 0; v < 4; ++v) acc[4 * b + v] = d[v];
+        for (int v = 0; v < 4; ++v) acc[4 * b + v] = d[v];
+      } else {
+        f32x4m d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < RP; kk += 4) {
+          const float a = sY[(r0 + (l & 15)) * L::YP + kk + (l >> 4)];
+          const float bb = sG[(kk + (l >> 4)) * L::GP + c0 + (l & 15)];
+          d = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bb, d, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[4 * b + v] = d[v];
+      }
     }
   } else {
     constexpr int RS = TileCfg<RP>::RS;

@@ -1,6 +1,6 @@
 // Small kernels of the SNMPBB hot path: the Gram matrix G = P^T P, its spectral norm
-// rho = ||G||_2 (the first-projection scale of Algorithm 1, Section 2.4), ||A||_F^2 with
-// input validation counts, and the BF16 hi/lo split of the precision form.
+// rho = ||G||_2 (the first-projection scale of Algorithm 1, Section 2.4) and the BF16 hi/lo
+// split of the precision form.
 #include "common.hpp"
 #include "kernels.hpp"
 #include "rho.hpp"
@@ -251,37 +251,6 @@ __global__ __launch_bounds__(kThreads) void k_brho(const BInst* __restrict__ ins
   rho_body(G64 + inst[i].goff, inst[i].r, states + i);
 }
 
-// ----------------------------------------------------------------------------- ||A||^2
-// Sum of squares in FP64 plus counts of negative and non-finite entries of an array of
-// N values; the last workgroup writes {sum, negatives, nonfinite} to out.
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_norm2(const T* __restrict__ x, int64_t N,
-                                                    double* __restrict__ part,
-                                                    double* __restrict__ out,
-                                                    unsigned* __restrict__ counter) {
-  __shared__ double sred[kThreads / kWave * 3];
-  double v[3] = {0.0, 0.0, 0.0};
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < N;
-       i += (int64_t)gridDim.x * kThreads) {
-    const double a = (double)x[i];
-    if (!(a - a == 0.0)) {
-      v[2] += 1.0;
-    } else {
-      v[0] = __builtin_fma(a, a, v[0]);
-      v[1] += a < 0.0 ? 1.0 : 0.0;
-    }
-  }
-  block_sum<3>(v, sred);
-  if (threadIdx.x == 0)
-    for (int j = 0; j < 3; ++j) part[(size_t)blockIdx.x * kNumPart + j] = v[j];
-  if (arrive_last(counter, gridDim.x)) {
-    double t[3];
-    reduce_partials<3>(part, gridDim.x, t, sred);
-    if (threadIdx.x == 0)
-      for (int j = 0; j < 3; ++j) out[j] = t[j];
-  }
-}
-
 // ----------------------------------------------------------------------------- BF16 split
 __device__ __forceinline__ uint16_t bf16_rne(float f) {
   uint32_t u = __float_as_uint(f);
@@ -459,19 +428,6 @@ template void launch_bgram_reduce<double>(const BInst*, int, int, const State*, 
 void launch_brho(const BInst* inst, int ninst, State* states, const double* G64, hipStream_t s) {
   hipLaunchKernelGGL(k_brho, dim3(ninst), dim3(kThreads), 0, s, inst, states, G64);
 }
-
-template <typename T>
-void launch_norm2(const T* x, int64_t N, double* part, double* out, unsigned* counter,
-                  hipStream_t s) {
-  int64_t nb = (N + kThreads * 8 - 1) / (kThreads * 8);
-  if (nb < 1) nb = 1;
-  if (nb > kMaxGrid) nb = kMaxGrid;
-  hipLaunchKernelGGL(k_norm2<T>, dim3((unsigned)nb), dim3(kThreads), 0, s, x, N, part, out,
-                     counter);
-}
-template void launch_norm2<float>(const float*, int64_t, double*, double*, unsigned*, hipStream_t);
-template void launch_norm2<double>(const double*, int64_t, double*, double*, unsigned*,
-                                   hipStream_t);
 
 void launch_split_rows(const float* A, int64_t n, int64_t lda, int64_t ldb, uint16_t* hi,
                        uint16_t* lo, hipStream_t s) {

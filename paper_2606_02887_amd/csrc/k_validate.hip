@@ -5,36 +5,50 @@
 
 namespace snmf {
 
-// {sum of squares, negatives, non-finite} over rows x cols with leading dimension ld.
+// {sum of squares, negatives, non-finite} over rows x cols with leading dimension ld, in
+// pieces of kStatSeg elements of a row (a contiguous array is one row), eight loads in flight
+// per thread and no division per element; k_stats_sum adds the workgroups' sums.  Bound by
+// the copy rate: 8192 x 4096 floats 30 us (179 us with one load in flight, a 64-bit division
+// per element and the sums finished by the last workgroup to arrive; 128 us with that
+// finish alone, whose device-scope fence every workgroup pays for).
+constexpr int kStatSeg = kThreads * 8;
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_stats2d(const T* __restrict__ x, int64_t rows,
-                                                      int64_t cols, int64_t ld,
-                                                      double* __restrict__ part,
-                                                      double* __restrict__ out,
-                                                      unsigned* __restrict__ counter) {
+                                                      int64_t cols, int64_t ld, int64_t nseg,
+                                                      double* __restrict__ part) {
   __shared__ double sred[kThreads / kWave * 3];
   double v[3] = {0.0, 0.0, 0.0};
-  const int64_t total = rows * cols;
-  for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * kThreads) {
-    const int64_t i = e / cols, j = e - i * cols;
-    const double a = (double)x[i * ld + j];
-    if (!(a - a == 0.0)) {
-      v[2] += 1.0;
-    } else {
-      v[0] = __builtin_fma(a, a, v[0]);
-      v[1] += a < 0.0 ? 1.0 : 0.0;
+  for (int64_t it = blockIdx.x; it < rows * nseg; it += gridDim.x) {
+    const int64_t row = it / nseg, c0 = (it - row * nseg) * kStatSeg;
+    const int left = (int)(cols - c0 < kStatSeg ? cols - c0 : kStatSeg);
+    const T* __restrict__ p = x + row * ld + c0;
+    T a[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int e = u * kThreads + (int)threadIdx.x;
+      a[u] = p[e < left ? e : 0];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const double d = (double)a[u];
+      const bool in = u * kThreads + (int)threadIdx.x < left, fin = d - d == 0.0;
+      const double ok = in && fin ? d : 0.0;
+      v[0] = __builtin_fma(ok, ok, v[0]);
+      v[1] += in && d < 0.0 && fin ? 1.0 : 0.0;
+      v[2] += in && !fin ? 1.0 : 0.0;
     }
   }
   block_sum<3>(v, sred);
   if (threadIdx.x == 0)
     for (int j = 0; j < 3; ++j) part[(size_t)blockIdx.x * kNumPart + j] = v[j];
-  if (arrive_last(counter, gridDim.x)) {
-    double t[3];
-    reduce_partials<3>(part, gridDim.x, t, sred);
-    if (threadIdx.x == 0)
-      for (int j = 0; j < 3; ++j) out[j] = t[j];
-  }
+}
+__global__ __launch_bounds__(kThreads) void k_stats_sum(const double* __restrict__ part, int nb,
+                                                        double* __restrict__ out) {
+  __shared__ double sred[kThreads / kWave * 3];
+  double t[3];
+  reduce_partials<3>(part, nb, t, sred);
+  if (threadIdx.x == 0)
+    for (int j = 0; j < 3; ++j) out[j] = t[j];
 }
 
 // CSR structure: flags[0] += bad rowptr, flags[1] += column out of range,
@@ -151,12 +165,18 @@ template void launch_dense_symmetry<double>(const double*, int64_t, int64_t, dou
 
 template <typename T>
 void launch_stats2d(const T* x, int64_t rows, int64_t cols, int64_t ld, double* part, double* out,
-                    unsigned* counter, hipStream_t s) {
-  int64_t nb = (rows * cols + kThreads * 8 - 1) / (kThreads * 8);
+                    hipStream_t s) {
+  if (ld == cols) {
+    cols *= rows;
+    rows = 1;
+  }
+  const int64_t nseg = (cols + kStatSeg - 1) / kStatSeg;
+  int64_t nb = rows * nseg;
   if (nb < 1) nb = 1;
   if (nb > kMaxGrid) nb = kMaxGrid;
   hipLaunchKernelGGL(k_stats2d<T>, dim3((unsigned)nb), dim3(kThreads), 0, s, x, rows, cols, ld,
-                     part, out, counter);
+                     nseg, part);
+  hipLaunchKernelGGL(k_stats_sum, dim3(1), dim3(kThreads), 0, s, (const double*)part, (int)nb, out);
 }
 
 void launch_csr_structure(const int64_t* rowptr, const int32_t* col, int64_t n, int64_t nnz,
@@ -179,40 +199,126 @@ void launch_csr_symmetry(const int64_t* rowptr, const int32_t* col, const T* val
 }
 
 template void launch_stats2d<float>(const float*, int64_t, int64_t, int64_t, double*, double*,
-                                    unsigned*, hipStream_t);
+                                    hipStream_t);
 template void launch_stats2d<double>(const double*, int64_t, int64_t, int64_t, double*, double*,
-                                     unsigned*, hipStream_t);
+                                     hipStream_t);
 template void launch_csr_symmetry<float>(const int64_t*, const int32_t*, const float*, int64_t,
                                          int64_t, unsigned*, hipStream_t);
 template void launch_csr_symmetry<double>(const int64_t*, const int32_t*, const double*, int64_t,
                                           int64_t, unsigned*, hipStream_t);
 
-// Solve start: clear the device state, store ||A||^2 and the start time.
-__global__ void k_reset_state(State* st, double normA2) {
+// Solve start: clear the device state, store ||A||^2 and the start time; one wavefront (one
+// thread storing the whole struct took 41 us).
+static_assert(sizeof(State) % 8 == 0, "State is cleared in 8-byte words");
+__device__ __forceinline__ void reset_state(State* st, double normA2) {
+  uint64_t* const w = (uint64_t*)st;
+  for (int e = threadIdx.x; e < (int)(sizeof(State) / 8); e += kWave) w[e] = 0;
+  __syncthreads();
   if (threadIdx.x == 0) {
-    State z = {};
-    z.normA2 = normA2;
-    z.t0 = wall_clock64();
-    *st = z;
+    st->normA2 = normA2;
+    st->t0 = wall_clock64();
   }
 }
-void launch_reset_state(State* st, double normA2, hipStream_t s) {
-  hipLaunchKernelGGL(k_reset_state, dim3(1), dim3(64), 0, s, st, normA2);
+__global__ __launch_bounds__(kWave) void k_reset_state(State* st, double normA2, unsigned* bad) {
+  reset_state(st, normA2);
+  if (bad && threadIdx.x == 0) *bad = kCopyOk;
+}
+void launch_reset_state(State* st, double normA2, hipStream_t s, unsigned* bad) {
+  hipLaunchKernelGGL(k_reset_state, dim3(1), dim3(kWave), 0, s, st, normA2, bad);
 }
 
 // Batched solve start: one State per instance.
-__global__ void k_breset(State* states, const BInst* inst, int ninst) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < ninst) {
-    State z = {};
-    z.normA2 = inst[i].normA2;
-    z.t0 = wall_clock64();
-    states[i] = z;
+__global__ __launch_bounds__(kWave) void k_breset(State* states, const BInst* inst,
+                                                  unsigned* bad) {
+  reset_state(states + blockIdx.x, inst[blockIdx.x].normA2);
+  if (bad && blockIdx.x == 0 && threadIdx.x == 0) *bad = kCopyOk;
+}
+void launch_breset(State* states, const BInst* inst, int ninst, hipStream_t s, unsigned* bad) {
+  hipLaunchKernelGGL(k_breset, dim3(ninst), dim3(kWave), 0, s, states, inst, bad);
+}
+
+// Batched solve end: every instance's results in one compact array.
+__global__ __launch_bounds__(kThreads) void k_bout(const State* __restrict__ states, int ninst,
+                                                   BOut* __restrict__ out) {
+  const int i = blockIdx.x * kThreads + threadIdx.x;
+  if (i >= ninst) return;
+  const State& h = states[i];
+  BOut o;
+  o.status = h.status;
+  o.outer = h.outer;
+  o.converged_at = h.converged_at;
+  o.pad = 0;
+  o.inner_total = h.inner_total;
+  o.ls_evals = h.ls_evals;
+  o.ls_exhausted = h.ls_exhausted;
+  o.res = h.res_last;
+  o.resww = h.resww_last;
+  o.sym = h.sym_last;
+  o.pg = h.pg_last;
+  o.f = h.f_last;
+  o.normA2 = h.normA2;
+  o.t_last = h.t_hstep - h.t0;
+  o.t_conv = h.t_conv;
+  out[i] = o;
+}
+void launch_bout(const State* states, int ninst, BOut* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_bout, dim3((ninst + kThreads - 1) / kThreads), dim3(kThreads), 0, s, states,
+                     ninst, out);
+}
+
+// The starts of a solve copied in (to both factors) and checked, or its results copied out,
+// in one launch: sixteen elements per thread, all loaded before the first is stored.  The
+// checks and copies they replace were a launch each, and a host wait per array.
+constexpr int kCopyPer = 16;
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_copy(CopyTab t, int check, unsigned* bad) {
+  if (bad && !check && *bad != kCopyOk) return;
+  int q = 0;
+  while (q + 1 < t.n && (int)blockIdx.x >= t.blk0[q + 1]) ++q;
+  const CopySeg& g = t.s[q];
+  const int64_t at = (int64_t)((int)blockIdx.x - t.blk0[q]) * (kThreads * kCopyPer);
+  const int left = (int)(g.count - at < kThreads * kCopyPer ? g.count - at : kThreads * kCopyPer);
+  const T* __restrict__ src = (const T*)g.src + at;
+  T* __restrict__ d0 = (T*)g.d0 + at;
+  T v[kCopyPer];
+#pragma unroll
+  for (int u = 0; u < kCopyPer; ++u) {
+    const int e = u * kThreads + (int)threadIdx.x;
+    v[u] = src[e < left ? e : 0];
   }
+  bool neg = false, nonfin = false;
+#pragma unroll
+  for (int u = 0; u < kCopyPer; ++u) {
+    const int e = u * kThreads + (int)threadIdx.x;
+    if (e < left) d0[e] = v[u];
+    const bool fin = v[u] - v[u] == T(0);
+    nonfin = nonfin || !fin;
+    neg = neg || (fin && v[u] < T(0));
+  }
+  if (g.d1) {
+    T* __restrict__ d1 = (T*)g.d1 + at;
+#pragma unroll
+    for (int u = 0; u < kCopyPer; ++u) {
+      const int e = u * kThreads + (int)threadIdx.x;
+      if (e < left) d1[e] = v[u];
+    }
+  }
+  if (bad && check && (neg || nonfin))
+    atomicMin(bad, 2u * (unsigned)(t.base + q) + (nonfin ? 0u : 1u));
 }
-void launch_breset(State* states, const BInst* inst, int ninst, hipStream_t s) {
-  hipLaunchKernelGGL(k_breset, dim3((ninst + 63) / 64), dim3(64), 0, s, states, inst, ninst);
+template <typename T>
+void launch_copy(CopyTab& t, bool check, unsigned* bad, hipStream_t s) {
+  int64_t nb = 0;
+  for (int q = 0; q < t.n; ++q) {
+    t.blk0[q] = (int32_t)nb;
+    nb += (t.s[q].count + kThreads * kCopyPer - 1) / (kThreads * kCopyPer);
+  }
+  t.blk0[t.n] = (int32_t)nb;
+  if (nb < 1) return;
+  hipLaunchKernelGGL(k_copy<T>, dim3((unsigned)nb), dim3(kThreads), 0, s, t, check ? 1 : 0, bad);
 }
+template void launch_copy<float>(CopyTab&, bool, unsigned*, hipStream_t);
+template void launch_copy<double>(CopyTab&, bool, unsigned*, hipStream_t);
 
 // flag = 1 when every instance of a batched solve is done.
 __global__ __launch_bounds__(256) void k_all_done(const State* states, int ninst, int32_t* flag) {

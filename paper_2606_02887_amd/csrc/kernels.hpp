@@ -77,9 +77,6 @@ template <typename T>
 void launch_bgram_reduce(const BInst* inst, int ninst, int max_r, const State* states,
                          const double* gpart, double* G64, T* GT, hipStream_t s);
 void launch_brho(const BInst* inst, int ninst, State* states, const double* G64, hipStream_t s);
-template <typename T>
-void launch_norm2(const T* x, int64_t N, double* part, double* out, unsigned* counter,
-                  hipStream_t s);
 void launch_split_rows(const float* A, int64_t n, int64_t lda, int64_t ldb, uint16_t* hi,
                        uint16_t* lo, hipStream_t s);
 void launch_split_pt(const float* P, int64_t n, int r, int64_t ldp, uint16_t* hi, uint16_t* lo,
@@ -127,7 +124,9 @@ int spmm_dot_grid(int64_t n);
 template <typename T>
 void launch_bspmm(const BGraph* graphs, const int32_t* sblk_graph, int sblocks,
                   const State* states, const T* P, T* B, hipStream_t s);
-void launch_breset(State* states, const BInst* inst, int ninst, hipStream_t s);
+void launch_breset(State* states, const BInst* inst, int ninst, hipStream_t s,
+                   unsigned* bad = nullptr);  // bad: also set to kCopyOk
+void launch_bout(const State* states, int ninst, BOut* out, hipStream_t s);
 void launch_all_done(const State* states, int ninst, int32_t* flag, hipStream_t s);
 template <typename T>
 void launch_lai(const T* U, int ell, const double* lam, const T* P, int64_t n, int r,
@@ -171,7 +170,7 @@ constexpr int64_t kRecomputeDBytes = 4 << 20;
 
 template <typename T>
 void launch_stats2d(const T* x, int64_t rows, int64_t cols, int64_t ld, double* part, double* out,
-                    unsigned* counter, hipStream_t s);
+                    hipStream_t s);
 template <typename T>
 void launch_dense_symmetry(const T* A, int64_t n, int64_t ld, double tol, unsigned* flags,
                            hipStream_t s);
@@ -180,7 +179,12 @@ void launch_csr_structure(const int64_t* rowptr, const int32_t* col, int64_t n, 
 template <typename T>
 void launch_csr_symmetry(const int64_t* rowptr, const int32_t* col, const T* val, int64_t n,
                          int64_t nnz, unsigned* flags, hipStream_t s);
-void launch_reset_state(State* st, double normA2, hipStream_t s);
+void launch_reset_state(State* st, double normA2, hipStream_t s, unsigned* bad = nullptr);
+// Copies the segments of t; with bad set, check: true looks for negative and non-finite
+// values (atomicMin of the code above into bad), false leaves everything alone unless *bad is
+// kCopyOk.
+template <typename T>
+void launch_copy(CopyTab& t, bool check, unsigned* bad, hipStream_t s);
 void launch_split_flat(const float* x, int64_t count, uint16_t* hi, uint16_t* lo, hipStream_t s);
 
 

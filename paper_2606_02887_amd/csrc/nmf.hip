@@ -40,7 +40,7 @@ struct NmfPlan {
   double *partsA = nullptr, *partsB = nullptr, *partsC = nullptr, *partsD = nullptr;
   double* trace = nullptr;
   State* st = nullptr;
-  unsigned *counters = nullptr, *flags = nullptr, *cnt = nullptr;
+  unsigned *flags = nullptr, *cnt = nullptr;
   unsigned long long* cursor = nullptr;
   int64_t* rowptrT = nullptr;
   int32_t* colT = nullptr;
@@ -53,7 +53,7 @@ struct NmfPlan {
 
 template <typename T>
 snmf_status stats(NmfPlan& pl, const T* x, int64_t rows, int64_t cols, int64_t ld, double* out3) {
-  launch_stats2d<T>(x, rows, cols, ld, pl.part, pl.dots, pl.counters + C_NORM, pl.s);
+  launch_stats2d<T>(x, rows, cols, ld, pl.part, pl.dots, pl.s);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipMemcpyAsync(out3, pl.dots, 3 * sizeof(double), hipMemcpyDeviceToHost, pl.s));
   HIP_TRY(hipStreamSynchronize(pl.s));
@@ -142,13 +142,10 @@ void half_step(NmfPlan& pl, T* X, int64_t nX, const T* P, int64_t nP, int is_hst
 }
 
 template <typename T>
-snmf_status run(NmfPlan& pl, const void* W0, const void* Ht0, void* W_out, void* Ht_out,
-                snmf_info* info, double* trace) {
+snmf_status run(NmfPlan& pl, void* W_out, void* Ht_out, snmf_info* info, double* trace) {
   const int64_t m = pl.m, n = pl.n;
   const int r = pl.r;
   hipStream_t s = pl.s;
-  HIP_TRY(hipMemcpyAsync(pl.Wb, W0, (size_t)m * r * sizeof(T), hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(pl.Hb, Ht0, (size_t)n * r * sizeof(T), hipMemcpyDeviceToDevice, s));
   launch_reset_state(pl.st, pl.normV2, s);
   HIP_TRY(hipGetLastError());
   T* W = (T*)pl.Wb;
@@ -167,29 +164,28 @@ snmf_status run(NmfPlan& pl, const void* W0, const void* Ht0, void* W_out, void*
   }
   half_step<T>(pl, W, m, H, n, 0, false, false, s);  // the last outer iteration's record
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync(W_out, pl.Wb, (size_t)m * r * sizeof(T), hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(Ht_out, pl.Hb, (size_t)n * r * sizeof(T), hipMemcpyDeviceToDevice, s));
+  CopyTab out{};
+  out.n = 2;
+  out.s[0] = {pl.Wb, W_out, nullptr, m * r};
+  out.s[1] = {pl.Hb, Ht_out, nullptr, n * r};
+  launch_copy<T>(out, false, nullptr, s);
+  HIP_TRY(hipGetLastError());
   State hs;
   HIP_TRY(hipMemcpyAsync(&hs, pl.st, sizeof(State), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   const double hz = snmf_clock_rate_hz();
-  double ticks_last = 0.0, ticks_conv = 0.0;
-  if (hs.trace_len > 0) {
-    if (trace) {
-      HIP_TRY(hipMemcpyAsync(trace, pl.trace, (size_t)hs.trace_len * kTraceFields * 8,
-                             hipMemcpyDeviceToHost, s));
-    }
-    HIP_TRY(hipMemcpyAsync(&ticks_last, pl.trace + (size_t)(hs.trace_len - 1) * kTraceFields + 5,
-                           8, hipMemcpyDeviceToHost, s));
-    if (hs.converged_at > 0)
-      HIP_TRY(hipMemcpyAsync(&ticks_conv, pl.trace + (size_t)(hs.converged_at - 1) * kTraceFields + 5,
-                             8, hipMemcpyDeviceToHost, s));
+  // the clock of the last record (its H-step is the last that finished) and of the record
+  // that met the target
+  const double ticks_last = (double)(hs.t_hstep - hs.t0), ticks_conv = (double)hs.t_conv;
+  if (hs.trace_len > 0 && trace) {
+    HIP_TRY(hipMemcpyAsync(trace, pl.trace, (size_t)hs.trace_len * kTraceFields * 8,
+                           hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    if (trace)  // the symmetric measures have no meaning for W (m x r) and Ht (n x r)
-      for (int q = 0; q < hs.trace_len; ++q) {
-        trace[(size_t)q * kTraceFields + 1] = NAN;
-        trace[(size_t)q * kTraceFields + 2] = NAN;
-      }
+    // the symmetric measures have no meaning for W (m x r) and Ht (n x r)
+    for (int q = 0; q < hs.trace_len; ++q) {
+      trace[(size_t)q * kTraceFields + 1] = NAN;
+      trace[(size_t)q * kTraceFields + 2] = NAN;
+    }
   }
   if (info) {
     std::memset(info, 0, sizeof(*info));
@@ -277,7 +273,6 @@ snmf_status nmf_solve(const snmf_matrix* V, int64_t ncols, int32_t r, const void
   add((void**)&pl.partsD, (size_t)kInnerGrid * kNumPart * 8);
   add((void**)&pl.trace, (size_t)p->max_outer * kTraceFields * 8);
   add((void**)&pl.st, sizeof(State));
-  add((void**)&pl.counters, C_COUNT * sizeof(unsigned));
   add((void**)&pl.flags, 4 * sizeof(unsigned));
   if (V->fmt == SNMF_DENSE && p->prec == SNMF_F32) {
     if ((m + 63) / 64 > 65535 || (ncols + 63) / 64 > 65535)
@@ -302,16 +297,15 @@ snmf_status nmf_solve(const snmf_matrix* V, int64_t ncols, int32_t r, const void
     *req[q].first = (char*)pl.pool + off;
     off += req[q].second;
   }
-  HIP_TRY(hipMemsetAsync(pl.counters, 0, C_COUNT * sizeof(unsigned), s));
   HIP_TRY(hipMemsetAsync(pl.st, 0, sizeof(State), s));
   HIP_TRY(hipMemsetAsync(pl.Pz, 0, xr, s));
   double st3[3] = {0, 0, 0};
-  if (V->fmt == SNMF_DENSE) {
+  if (V->fmt == SNMF_DENSE) {  // read back below, together with the check of the starts
     if (pl.prec == SNMF_F64)
-      SNMF_TRY(stats<double>(pl, (const double*)V->dense, m, ncols, V->ld, st3));
+      launch_stats2d<double>((const double*)V->dense, m, ncols, V->ld, pl.part, pl.dots, s);
     else
-      SNMF_TRY(stats<float>(pl, (const float*)V->dense, m, ncols, V->ld, st3));
-    if (p->validate) SNMF_TRY(check_vals(st3, "V"));
+      launch_stats2d<float>((const float*)V->dense, m, ncols, V->ld, pl.part, pl.dots, s);
+    HIP_TRY(hipGetLastError());
   } else {
     HIP_TRY(hipMemsetAsync(pl.flags, 0, 4 * sizeof(unsigned), s));
     launch_csr_check_rect(V->rowptr, V->col, m, ncols, V->nnz, pl.flags, s);
@@ -337,26 +331,35 @@ snmf_status nmf_solve(const snmf_matrix* V, int64_t ncols, int32_t r, const void
                                   pl.cnt, pl.cursor, pl.rowptrT, pl.colT, (float*)pl.valT, s);
     HIP_TRY(hipGetLastError());
   }
-  pl.normV2 = st3[0];
-  if (!(pl.normV2 > 0.0)) return fail(SNMF_E_ARG, "V is zero");
   if (pl.VT) {
     launch_transpose<float>((const float*)V->dense, m, ncols, V->ld, (float*)pl.VT, s);
     HIP_TRY(hipGetLastError());
   }
-  if (p->validate) {
-    double w3[3], h3[3];
-    if (pl.prec == SNMF_F64) {
-      SNMF_TRY(stats<double>(pl, (const double*)W0, m, r, r, w3));
-      SNMF_TRY(stats<double>(pl, (const double*)Ht0, ncols, r, r, h3));
-    } else {
-      SNMF_TRY(stats<float>(pl, (const float*)W0, m, r, r, w3));
-      SNMF_TRY(stats<float>(pl, (const float*)Ht0, ncols, r, r, h3));
-    }
-    SNMF_TRY(check_vals(w3, "W0"));
-    SNMF_TRY(check_vals(h3, "Ht0"));
+  HIP_TRY(hipMemsetAsync(pl.flags, 0xff, sizeof(unsigned), s));  // kCopyOk
+  CopyTab in{};
+  in.n = 2;
+  in.s[0] = {W0, pl.Wb, nullptr, m * r};
+  in.s[1] = {Ht0, pl.Hb, nullptr, ncols * r};
+  if (pl.prec == SNMF_F64)
+    launch_copy<double>(in, true, p->validate ? pl.flags : nullptr, s);
+  else
+    launch_copy<float>(in, true, p->validate ? pl.flags : nullptr, s);
+  HIP_TRY(hipGetLastError());
+  unsigned bad = kCopyOk;
+  if (V->fmt == SNMF_DENSE)
+    HIP_TRY(hipMemcpyAsync(st3, pl.dots, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(&bad, pl.flags, sizeof(bad), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  if (V->fmt == SNMF_DENSE && p->validate) SNMF_TRY(check_vals(st3, "V"));
+  pl.normV2 = st3[0];
+  if (!(pl.normV2 > 0.0)) return fail(SNMF_E_ARG, "V is zero");
+  if (bad != kCopyOk) {
+    const std::string what = bad < 2 ? "W0" : "Ht0";
+    if ((bad & 1u) == 0) return fail(SNMF_E_NONFINITE, what + " has NaN/Inf entries");
+    return fail(SNMF_E_NEGATIVE, what + " has negative entries");
   }
-  if (pl.prec == SNMF_F64) return run<double>(pl, W0, Ht0, W_out, Ht_out, info, trace);
-  return run<float>(pl, W0, Ht0, W_out, Ht_out, info, trace);
+  if (pl.prec == SNMF_F64) return run<double>(pl, W_out, Ht_out, info, trace);
+  return run<float>(pl, W_out, Ht_out, info, trace);
 }
 
 }  // namespace

@@ -56,8 +56,8 @@ struct snmf_plan {
   uint16_t *Ahi = nullptr, *Alo = nullptr, *Pthi = nullptr, *Ptlo = nullptr;
   int64_t ldb = 0;
   State* st = nullptr;
-  unsigned* counters = nullptr;
   unsigned* flags = nullptr;
+  unsigned* bad() { return (unsigned*)(st + 1); }  // what the check of W0 found
   DenseSplit ds{};
   int gram_blocks = 1;
   int grid = 1;  // workgroups of every row-tile kernel of the plan (one partial-sum layout)
@@ -160,7 +160,7 @@ namespace {
 
 template <typename T>
 snmf_status stats(snmf_plan* pl, const T* x, int64_t rows, int64_t cols, int64_t ld, double* out3) {
-  launch_stats2d<T>(x, rows, cols, ld, pl->part, pl->dots, pl->counters + C_NORM, pl->s);
+  launch_stats2d<T>(x, rows, cols, ld, pl->part, pl->dots, pl->s);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipMemcpyAsync(out3, pl->dots, 3 * sizeof(double), hipMemcpyDeviceToHost, pl->s));
   HIP_TRY(hipStreamSynchronize(pl->s));
@@ -524,8 +524,7 @@ snmf_status plan_init(snmf_plan* pl, const snmf_matrix* A, int32_t r, const snmf
   add((void**)&pl->gram_part, (size_t)pl->gram_blocks * r * r * 8);
   add((void**)&pl->dots, 64 * 8);
   add((void**)&pl->trace, (size_t)p->max_outer * kTraceFields * 8);
-  add((void**)&pl->st, sizeof(State));
-  add((void**)&pl->counters, C_COUNT * sizeof(unsigned));
+  add((void**)&pl->st, sizeof(State) + 8);  // and the word of the start's check behind it
   add((void**)&pl->flags, 4 * sizeof(unsigned));
   if (A->fmt == SNMF_LOWRANK) {
     add((void**)&pl->lai_part, (size_t)lai_nb * A->ell * r * 8);
@@ -553,7 +552,6 @@ snmf_status plan_init(snmf_plan* pl, const snmf_matrix* A, int32_t r, const snmf
     *req[q].first = (char*)pl->pool + off;
     off += req[q].second;
   }
-  HIP_TRY(hipMemsetAsync(pl->counters, 0, C_COUNT * sizeof(unsigned), pl->s));
   HIP_TRY(hipMemsetAsync(pl->st, 0, sizeof(State), pl->s));
   // input checks and ||A||^2
   double st3[3] = {0, 0, 0};
@@ -603,25 +601,36 @@ snmf_status plan_create(const snmf_matrix* A, int32_t r, const snmf_params* p, h
   return SNMF_OK;
 }
 
+snmf_status start_check(unsigned bad, const char* what) {
+  if (bad == kCopyOk) return SNMF_OK;
+  if ((bad & 1u) == 0) return fail(SNMF_E_NONFINITE, std::string(what) + " has NaN/Inf entries");
+  return fail(SNMF_E_NEGATIVE, std::string(what) + " has negative entries");
+}
+
+// Solves of at most this many outer iterations are not held up for the check of W0: its
+// result comes back with theirs, and a bad start leaves every output untouched.  Longer ones
+// wait for it first (a host wait, about 20 us of at least 64 iterations).
+constexpr int kDeferOuter = 64;
+constexpr int kDirectOuter = 64;  // snmf_solve: direct launches up to here
+
 snmf_status read_info(snmf_plan* pl, snmf_info* info, double* trace) {
-  State hs;
-  HIP_TRY(hipMemcpyAsync(&hs, pl->st, sizeof(State), hipMemcpyDeviceToHost, pl->s));
+  struct {
+    State hs;
+    unsigned bad, pad;
+  } back;
+  HIP_TRY(hipMemcpyAsync(&back, pl->st, sizeof(State) + 8, hipMemcpyDeviceToHost, pl->s));
   HIP_TRY(hipStreamSynchronize(pl->s));
+  const State& hs = back.hs;
+  SNMF_TRY(start_check(back.bad, "W0"));
   const double hz = snmf_clock_rate_hz();
-  // the clock ticks of the last record and of the record that met the target
-  double ticks_last = 0.0, ticks_conv = 0.0;
-  if (hs.trace_len > 0) {
-    if (trace)
-      HIP_TRY(hipMemcpyAsync(trace, pl->trace, (size_t)hs.trace_len * kTraceFields * 8,
-                             hipMemcpyDeviceToHost, pl->s));
-    HIP_TRY(hipMemcpyAsync(&ticks_last, pl->trace + (size_t)(hs.trace_len - 1) * kTraceFields + 5,
-                           8, hipMemcpyDeviceToHost, pl->s));
-    if (hs.converged_at > 0)
-      HIP_TRY(hipMemcpyAsync(&ticks_conv,
-                             pl->trace + (size_t)(hs.converged_at - 1) * kTraceFields + 5, 8,
-                             hipMemcpyDeviceToHost, pl->s));
+  if (hs.trace_len > 0 && trace) {
+    HIP_TRY(hipMemcpyAsync(trace, pl->trace, (size_t)hs.trace_len * kTraceFields * 8,
+                           hipMemcpyDeviceToHost, pl->s));
     HIP_TRY(hipStreamSynchronize(pl->s));
   }
+  // the clock of the last record (its H-step is the last that finished) and of the record
+  // that met the target
+  const double ticks_last = (double)(hs.t_hstep - hs.t0), ticks_conv = (double)hs.t_conv;
   if (info) {
     std::memset(info, 0, sizeof(*info));
     info->status = hs.status;
@@ -649,21 +658,27 @@ snmf_status plan_solve(snmf_plan* pl, const void* W0, void* W_out, void* Ht_out,
   if (!W0 || !W_out || !Ht_out) return fail(SNMF_E_ARG, "W0, W_out and Ht_out are required");
   const int64_t n = pl->n;
   const int r = pl->r;
-  const size_t nr = (size_t)n * r * pl->esz;
   if (pl->borrowed) user = nullptr;  // the plan already runs on the caller's stream
   if (user) {
     HIP_TRY(hipEventRecord(pl->ev_in, user));
     HIP_TRY(hipStreamWaitEvent(pl->s, pl->ev_in, 0));
   }
-  if (pl->p.validate) {
-    double st3[3];
-    SNMF_TRY(stats_any(pl, W0, n, r, r, st3));
-    SNMF_TRY(check_values(st3, "W0"));
-  }
-  HIP_TRY(hipMemcpyAsync(pl->Wb, W0, nr, hipMemcpyDeviceToDevice, pl->s));
-  HIP_TRY(hipMemcpyAsync(pl->Hb, W0, nr, hipMemcpyDeviceToDevice, pl->s));
-  launch_reset_state(pl->st, pl->normA2, pl->s);
+  auto copy = [&](CopyTab& t, bool check, unsigned* bad) {
+    if (pl->prec == SNMF_F64) launch_copy<double>(t, check, bad, pl->s);
+    else launch_copy<float>(t, check, bad, pl->s);
+  };
+  launch_reset_state(pl->st, pl->normA2, pl->s, pl->bad());
+  CopyTab in{};
+  in.n = 1;
+  in.s[0] = {W0, pl->Wb, pl->Hb, n * r};
+  copy(in, true, pl->p.validate ? pl->bad() : nullptr);
   HIP_TRY(hipGetLastError());
+  if (pl->p.validate && pl->p.max_outer > kDeferOuter) {
+    unsigned bad = kCopyOk;
+    HIP_TRY(hipMemcpyAsync(&bad, pl->bad(), sizeof(bad), hipMemcpyDeviceToHost, pl->s));
+    HIP_TRY(hipStreamSynchronize(pl->s));
+    SNMF_TRY(start_check(bad, "W0"));
+  }
   const int every = std::max(1, pl->p.check_every);
   auto capture = [&](int iters, hipGraph_t* g, hipGraphExec_t* ge) -> snmf_status {
     HIP_TRY(hipStreamBeginCapture(pl->s, hipStreamCaptureModeThreadLocal));
@@ -707,8 +722,12 @@ snmf_status plan_solve(snmf_plan* pl, const void* W0, void* W_out, void* Ht_out,
     }
   }
   SNMF_TRY(finalize_any(pl, pl->s));
-  HIP_TRY(hipMemcpyAsync(W_out, pl->Wb, nr, hipMemcpyDeviceToDevice, pl->s));
-  HIP_TRY(hipMemcpyAsync(Ht_out, pl->Hb, nr, hipMemcpyDeviceToDevice, pl->s));
+  CopyTab out{};
+  out.n = 2;
+  out.s[0] = {pl->Wb, W_out, nullptr, n * r};
+  out.s[1] = {pl->Hb, Ht_out, nullptr, n * r};
+  copy(out, false, pl->bad());
+  HIP_TRY(hipGetLastError());
   snmf_status rs = read_info(pl, info, trace);
   if (user) {
     HIP_TRY(hipEventRecord(pl->ev_out, pl->s));
@@ -808,6 +827,10 @@ snmf_status snmf_solve(const snmf_matrix* A, int32_t r, const void* W0, const sn
                        void* W_out, void* Ht_out, snmf_info* info, void* stream, double* trace) {
   snmf_plan* pl = nullptr;
   SNMF_TRY(plan_create(A, r, p, (hipStream_t)stream, &pl));
+  // a plan that lives for one solve: capturing and instantiating its graphs (300 us) pays
+  // from about this many outer iterations on (n = 1000, r = 20, FP64, graph against direct
+  // launches: 10 outer iterations 2336 / 2019 us, 40: 7156 / 7131, 160: 26356 / 26493)
+  if (p->max_outer <= kDirectOuter) pl->p.use_graph = 0;
   snmf_status s = plan_solve(pl, W0, W_out, Ht_out, info, (hipStream_t)stream, trace);
   std::string keep = snmf::err_ref();
   snmf_plan_destroy(pl);

@@ -470,8 +470,19 @@ class Mlp:
 
 
 def solve(A: MatrixRef, W0, prm: Params, L: MatrixRef | None = None, trace: bool = True):
-    with Plan(A, W0.shape[1], prm, L) as pl:
-        return pl.solve(W0, trace=trace)
+    import torch
+    if L is not None:
+        prm.L = ctypes.pointer(L.desc)
+    W_out, Ht_out = torch.empty_like(W0), torch.empty_like(W0)
+    info = Info()
+    tr = (c_double * (prm.max_outer * TRACE_FIELDS))() if trace else None
+    _check(_lib.snmf_solve(ctypes.byref(A.desc), W0.shape[1], _ptr(W0), ctypes.byref(prm),
+                           _ptr(W_out), _ptr(Ht_out), ctypes.byref(info), _stream(), tr))
+    out = info.as_dict()
+    if trace:
+        arr = np.frombuffer(tr, dtype=np.float64).reshape(prm.max_outer, TRACE_FIELDS)
+        out["trace"] = arr[: info.outer].copy()
+    return W_out, Ht_out, out
 
 
 def solve_noalloc(A: MatrixRef, W0, prm: Params, L: MatrixRef | None = None, W_out=None,

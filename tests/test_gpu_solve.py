@@ -445,3 +445,56 @@ def test_exact_stationary_start_stops_and_keeps_the_monitor(S, prec):
     assert np.array_equal(W.double().cpu().numpy(), Wt)
     assert np.array_equal(Ht.double().cpu().numpy(), Wt)
     assert info["res_WH"] == 0.0 and info["pg_norm"] == 0.0
+
+
+@pytest.mark.parametrize("max_outer", [3, 100])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_start_check_leaves_outputs_untouched(S, prec, max_outer):
+    """A start with a bad value in its last element (several copy pieces along) is refused
+    whether the check is read with the results (short solves) or before them, the outputs
+    keep their values, and the plan solves the next start as a fresh plan does."""
+    dt = torch.float64 if prec == "f64" else torch.float32
+    n, r = 1500, 7
+    g = torch.Generator(device="cpu").manual_seed(3)
+    W = torch.rand((n, r), generator=g, dtype=dt).to("cuda")
+    A = W @ W.T
+    A = 0.5 * (A + A.T)
+    W0 = torch.rand((n, r), generator=g, dtype=dt).to("cuda")
+    prm = S.params(lam=1.0, prec=S.prec_of(dt), max_outer=max_outer, check_every=1 << 30)
+    with S.Plan(S.dense(A), r, prm) as pl:
+        for bad, name in ((float("nan"), "E_NONFINITE"), (-1.0, "E_NEGATIVE")):
+            Wb = W0.clone()
+            Wb[-1, -1] = bad
+            out = [torch.full_like(W0, 7.0) for _ in range(2)]
+            with pytest.raises(S.SnmfError) as e:
+                pl.solve(Wb, *out)
+            assert e.value.name == name
+            assert all(bool((o == 7.0).all()) for o in out)
+        got = pl.solve(W0)
+    with S.Plan(S.dense(A), r, prm) as pl:
+        ref = pl.solve(W0)
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+
+
+def test_batch_start_check_many_problems(S):
+    """More problems than one copy launch takes: the first bad start decides the error."""
+    n, r, k = 40, 3, 40
+    g = torch.Generator(device="cpu").manual_seed(4)
+    W = torch.rand((n, r), generator=g).to("cuda")
+    A = W @ W.T
+    A = 0.5 * (A + A.T)
+    W0s = [torch.rand((2, n, r), generator=g).to("cuda") for _ in range(k)]
+    with S.Batch([S.dense(A)] * k, [r] * k, S.params(lam=1.0, max_outer=2), 2) as b:
+        Ws, Hs, infos, _ = b.solve(W0s)
+        for i in (0, 33, k - 1):
+            with S.Plan(S.dense(A), r, S.params(lam=1.0, max_outer=2, fuse_inner=0)) as pl:
+                W, Ht, _ = pl.solve(W0s[i][1].contiguous())
+            assert torch.equal(Ws[i][1], W) and torch.equal(Hs[i][1], Ht)
+        for first, second, name in ((-1.0, float("inf"), "E_NEGATIVE"),
+                                    (float("nan"), -1.0, "E_NONFINITE")):
+            bad = [w.clone() for w in W0s]
+            bad[34][1, 5, 1] = first
+            bad[35][0, 0, 0] = second
+            with pytest.raises(S.SnmfError) as e:
+                b.solve(bad)
+            assert e.value.name == name
