@@ -39,11 +39,12 @@ snmf_status check_finite(const void* X, int64_t count, int prec, unsigned* flag,
   return SNMF_OK;
 }
 
-void knn_any(const void* X, int64_t n, int dim, int K, int prec, int32_t* nbr, hipStream_t s) {
+void knn_any(const void* X, int64_t n, int dim, int K, int prec, double* nrm, int32_t* nbr,
+             hipStream_t s) {
   if (prec == SNMF_F64)
-    launch_knn<double>((const double*)X, n, dim, K, nbr, s);
+    launch_knn<double>((const double*)X, n, dim, K, nrm, nbr, s);
   else
-    launch_knn<float>((const float*)X, n, dim, K, nbr, s);
+    launch_knn<float>((const float*)X, n, dim, K, nrm, nbr, s);
 }
 
 }  // namespace
@@ -55,10 +56,10 @@ snmf_status snmf_knn(const void* X, int64_t n, int32_t dim, int32_t K, int32_t p
   SNMF_TRY(check_points(X, n, dim, K, prec));
   if (!nbr_out) return fail(SNMF_E_ARG, "nbr_out is required");
   hipStream_t s = (hipStream_t)stream;
-  DevBuf flag;
-  HIP_TRY(hipMalloc(&flag.p, 256));
-  SNMF_TRY(check_finite(X, n * dim, prec, (unsigned*)flag.p, s));
-  knn_any(X, n, dim, K, prec, nbr_out, s);
+  DevBuf pool;  // the flag of the check, the squared norms
+  HIP_TRY(hipMalloc(&pool.p, 256 + (size_t)n * 8));
+  SNMF_TRY(check_finite(X, n * dim, prec, (unsigned*)pool.p, s));
+  knn_any(X, n, dim, K, prec, (double*)((char*)pool.p + 256), nbr_out, s);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(s));
   return SNMF_OK;
@@ -94,10 +95,10 @@ snmf_status snmf_knn_graph(const void* X, int64_t n, int32_t dim, int32_t K, dou
   unsigned long long* cursor = (unsigned long long*)(base + b_nbr + b_cnt);
   double* deg = (double*)(base + b_nbr + b_cnt + b_cur);
   double* v = (double*)(base + b_nbr + b_cnt + b_cur + b_deg);
-  knn_any(X, n, dim, K, prec, nbr, s);
+  knn_any(X, n, dim, K, prec, deg, nbr, s);  // deg is free until the values
   HIP_TRY(hipMemsetAsync(cnt, 0, (size_t)n * 4, s));
   launch_knn_pattern_count(nbr, n, K, diag, cnt, rowptr_out, s);
-  launch_knn_pattern_fill(nbr, n, K, diag, rowptr_out, col_out, cursor, s);
+  launch_knn_pattern_fill(nbr, n, K, diag, rowptr_out, col_out, cursor, (int32_t*)v, s);
   if (prec == SNMF_F64)
     launch_knn_values<double>((const double*)X, n, dim, sigma, laplacian, rowptr_out, col_out, v,
                               deg, (double*)val_out, s);

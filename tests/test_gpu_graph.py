@@ -50,6 +50,50 @@ def test_knn_ties_go_to_the_lower_index(S):
     assert list(nbr[10]) == [9, 11, 8, 12]
 
 
+@pytest.mark.parametrize("n,dim,K", [(2, 1, 1), (2000, 3, 17), (2001, 1, 1), (2001, 4, 16),
+                                     (2032, 5, 17), (2047, 8, 32), (2100, 9, 33), (2049, 16, 10),
+                                     (2008, 17, 64), (2017, 32, 16), (2065, 33, 10), (2048, 48, 7),
+                                     (2011, 64, 2)])
+@pytest.mark.parametrize("kind", ["lattice", "equal", "tiny", "huge", "far"])
+def test_knn_edges(S, n, dim, K, kind):
+    """Identical lists at the edges of the tiles of points, of coordinates and of the lists,
+    for data that screening by |x_j|^2 - 2 <x_i, x_j> cannot separate: exact ties, equal
+    points, squares that underflow, squares near the overflow (distances below it) and
+    a cloud far from the origin."""
+    rng = np.random.default_rng(n * 64 + dim)
+    X = rng.integers(0, 3, (n, dim)).astype(np.float64)
+    X = {"lattice": X, "equal": np.ones((n, dim)), "tiny": X * 1e-161,
+         "huge": 1e153 * (1 + 0.01 * rng.random((n, dim))),
+         "far": 1e6 + rng.random((n, dim))}[kind]
+    nbr = S.knn(torch.from_numpy(X).to(DEV), K).cpu().numpy()
+    if kind == "tiny":  # the rounding of the sums of underflowed squares: order of addition
+        d = np.zeros((n, n))
+        for c in range(dim):
+            t = X[:, c][:, None] - X[:, c][None, :]
+            d = d + t * t
+        got = np.take_along_axis(d, nbr, 1)
+        d[np.arange(n), np.arange(n)] = np.inf
+        ref = np.sort(d, 1)[:, :K]
+        assert np.abs(got - ref).max() <= dim * 2.0 ** -1074
+    else:
+        idx, _ = O.knn(X, K)
+        assert np.array_equal(nbr, idx)
+
+
+def test_knn_graph_long_rows(S):
+    """A star: the hub's row of the union holds every point (the sort of rows past 64)."""
+    n = 700
+    X = np.zeros((n, 64))
+    rng = np.random.default_rng(9)
+    X[1:] = rng.standard_normal((n - 1, X.shape[1]))
+    X[1:] /= np.linalg.norm(X[1:], axis=1)[:, None]   # all closer to 0 than to each other
+    M = S.knn_graph(torch.from_numpy(X).to(DEV), 2, laplacian=False)
+    rowptr, col, _ = (t.cpu().numpy() for t in M.keep)
+    ref = O.similarity(X, 2, 0.0)
+    assert np.array_equal(rowptr, ref.indptr) and np.array_equal(col, ref.indices)
+    assert rowptr[1] - rowptr[0] > 128
+
+
 @pytest.mark.parametrize("prec", ["f64", "f32"])
 @pytest.mark.parametrize("laplacian,sigma", [(True, 0.0), (False, 0.0), (True, 1.5), (False, 2.0)])
 def test_knn_graph_matches_oracle(S, prec, laplacian, sigma):
