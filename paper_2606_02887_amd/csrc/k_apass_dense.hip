@@ -175,17 +175,32 @@ __global__ __launch_bounds__(256) void k_apass_f64(const double* __restrict__ A,
 // Grid: x = blocks of 256 output rows (4 waves x 64), y = K splits of kchunk rows of A.
 // Wave w handles output rows j0..j0+63 (two MFMA N-blocks of 32) and all r <= 64
 // columns (one or two MFMA M-blocks).  Per k-pair a lane loads A[k+h][j0+c] and
-// A[k+h][j0+32+c] (h = lane/32, c = lane%32) and P[k+h][c], P[k+h][32+c].
+// A[k+h][j0+32+c] (h = lane/32, c = lane%32) and P[k+h][c], P[k+h][32+c]: any lda and n.
+// Bound by the latency of its loads (n = 3001: a wave's share is 80 rows), so kDepth
+// batches of kBatch k-pairs are in flight; lanes past n or r read a clamped address (their
+// columns and ranks are never stored), which keeps the loads unconditional.  With rj.G
+// set, row 0 of the grid computes rho = ||G||_2 (rho.hpp) beside the tiles, first in
+// dispatch order because it is as long as they are.  n = 3001, r = 21: 16.8 us, 21.9 with rho;
+// two batches in flight behind predicated loads took 24.3 us, and rho 21.4 in a launch of
+// its own.
 template <int NMB>
 __global__ __launch_bounds__(256) void k_apass_f32(const float* __restrict__ A, int64_t lda,
                                                    const float* __restrict__ P, int64_t n, int r,
                                                    int64_t kchunk, float* __restrict__ Bpart,
-                                                   int64_t pstride, const State* __restrict__ st) {
+                                                   int64_t pstride, const State* __restrict__ st,
+                                                   RhoJob rj) {
   if (st->done) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (rj.G && blockIdx.y == 0) {
+    if (blockIdx.x == 0) rho_body(rj.G, rj.r, rj.st);
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int c = lane & 31, h = lane >> 5;
   const int64_t j0 = ((int64_t)blockIdx.x * 4 + wave) * 64;
-  const int64_t kb = (int64_t)blockIdx.y * kchunk;
+  if (j0 >= n) return;
+  const int64_t part = (int64_t)blockIdx.y - (rj.G ? 1 : 0);
+  const int64_t kb = part * kchunk;
   const int64_t ke = kb + kchunk < n ? kb + kchunk : n;
   f32x16 acc[NMB][2];
 #pragma unroll
@@ -197,46 +212,67 @@ __global__ __launch_bounds__(256) void k_apass_f32(const float* __restrict__ A, 
   const bool jok0 = j0 + c < n, jok1 = j0 + 32 + c < n;
   const bool mok0 = c < r, mok1 = 32 + c < r;
   const float* arow = A + j0 + c;
-  constexpr int U = 8;  // k-pairs per batch of loads
-  float a0[U], a1[U], p0[U], p1[U];
-  float b0[U], b1[U], q0[U], q1[U];
-  auto load = [&](float (&x0)[U], float (&x1)[U], float (&y0)[U], float (&y1)[U], int64_t kk0) {
+  constexpr int kBatch = 8, kDepth = NMB > 1 ? 2 : 4;
+  struct Batch {
+    float a0[kBatch], a1[kBatch], p0[kBatch], p1[kBatch];
+  } q[kDepth];
+  const float* ac0 = A + (jok0 ? j0 + c : n - 1);
+  const float* ac1 = A + (jok1 ? j0 + 32 + c : n - 1);
+  const float* pc0 = P + (mok0 ? c : 0);
+  const float* pc1 = P + (mok1 ? 32 + c : 0);
+  auto load = [&](Batch& x, int64_t k0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t kk = kk0 + 2 * u + h;
-      x0[u] = jok0 ? __builtin_nontemporal_load(arow + kk * lda) : 0.0f;
-      x1[u] = jok1 ? __builtin_nontemporal_load(arow + kk * lda + 32) : 0.0f;
-      y0[u] = mok0 ? P[kk * r + c] : 0.0f;
-      if (NMB > 1) y1[u] = mok1 ? P[kk * r + 32 + c] : 0.0f;
+    for (int u = 0; u < kBatch; ++u) {
+      const int64_t kk = k0 + 2 * u + h;
+      x.a0[u] = __builtin_nontemporal_load(ac0 + kk * lda);
+      x.a1[u] = __builtin_nontemporal_load(ac1 + kk * lda);
+      x.p0[u] = pc0[kk * r];
+      if (NMB > 1) x.p1[u] = pc1[kk * r];
     }
   };
-  auto mma = [&](const float (&x0)[U], const float (&x1)[U], const float (&y0)[U],
-                 const float (&y1)[U]) {
+  auto mma = [&](const Batch& x) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0[u], x0[u], acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0[u], x1[u], acc[0][1], 0, 0, 0);
+    for (int u = 0; u < kBatch; ++u) {
+      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.p0[u], x.a0[u], acc[0][0], 0, 0, 0);
+      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.p0[u], x.a1[u], acc[0][1], 0, 0, 0);
       if (NMB > 1) {
-        acc[NMB - 1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1[u], x0[u], acc[NMB - 1][0], 0, 0, 0);
-        acc[NMB - 1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1[u], x1[u], acc[NMB - 1][1], 0, 0, 0);
+        acc[NMB - 1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.p1[u], x.a0[u], acc[NMB - 1][0], 0, 0, 0);
+        acc[NMB - 1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.p1[u], x.a1[u], acc[NMB - 1][1], 0, 0, 0);
       }
     }
   };
-  int64_t k = kb;
-  // two batches of loads in flight: the next batch is requested before this one's MFMAs
-  if (k + 2 * U <= ke) load(a0, a1, p0, p1, k);
-  while (k + 2 * U <= ke) {
-    if (k + 4 * U <= ke) {
-      load(b0, b1, q0, q1, k + 2 * U);
-      mma(a0, a1, p0, p1);
-      k += 2 * U;
-      if (k + 4 * U <= ke) load(a0, a1, p0, p1, k + 2 * U);
-      mma(b0, b1, q0, q1);
-      k += 2 * U;
-    } else {
-      mma(a0, a1, p0, p1);
-      k += 2 * U;
+  const int64_t nbat = ke > kb ? (ke - kb) / (2 * kBatch) : 0;
+  int64_t k = kb, b = 0;
+  if (nbat >= kDepth) {
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d) load(q[d], k + d * 2 * kBatch);
+    for (; b + 2 * kDepth <= nbat; b += kDepth) {
+#pragma unroll
+      for (int d = 0; d < kDepth; ++d) {
+        mma(q[d]);
+        load(q[d], k + (kDepth + d) * 2 * kBatch);
+      }
+      k += kDepth * 2 * kBatch;
     }
+    // kDepth batches in flight, fewer than kDepth after them
+    const int left = (int)(nbat - b) - kDepth;
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d) {
+      mma(q[d]);
+      if (d < left) load(q[d], k + (kDepth + d) * 2 * kBatch);
+    }
+#pragma unroll
+    for (int d = 0; d < kDepth - 1; ++d)
+      if (d < left) mma(q[d]);
+    k += (kDepth + left) * 2 * kBatch;
+  } else {
+#pragma unroll
+    for (int d = 0; d < kDepth - 1; ++d)
+      if (d < (int)nbat) load(q[d], k + d * 2 * kBatch);
+#pragma unroll
+    for (int d = 0; d < kDepth - 1; ++d)
+      if (d < (int)nbat) mma(q[d]);
+    k += nbat * 2 * kBatch;
   }
   for (; k < ke; k += 2) {
     const int64_t kk = k + h;
@@ -254,7 +290,7 @@ __global__ __launch_bounds__(256) void k_apass_f32(const float* __restrict__ A, 
   }
   // D[m][j] of block (mb, nb): lane holds j = j0 + 32 nb + c and
   // m = 32 mb + 8 (v/4) + 4 h + v%4 in register v.
-  float* out = Bpart + (int64_t)blockIdx.y * pstride;
+  float* out = Bpart + part * pstride;
 #pragma unroll
   for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
@@ -797,13 +833,13 @@ void launch_apass_f32(const float* A, int64_t lda, const float* P, int64_t n, in
                        d.kchunk, d.nband, d.rchunk, d.ksplit, Bpart, pstride, st, rj, rho_wg);
     return;
   }
-  if (rj.G) launch_rho(rj.G, rj.r, rj.st, s);
+  if (rj.G) ++grid.y;
   if (r > 32)
     hipLaunchKernelGGL(k_apass_f32<2>, grid, dim3(256), 0, s, A, lda, P, n, r, d.kchunk, Bpart,
-                       pstride, st);
+                       pstride, st, rj);
   else
     hipLaunchKernelGGL(k_apass_f32<1>, grid, dim3(256), 0, s, A, lda, P, n, r, d.kchunk, Bpart,
-                       pstride, st);
+                       pstride, st, rj);
 }
 
 DenseSplit plan_dense_bf16(int64_t n) {

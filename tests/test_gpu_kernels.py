@@ -200,3 +200,25 @@ def test_dense_apass_f64_edges(S, n, r, pad):
         B = torch.empty_like(Pt)
         pl.apass(Pt, B)
     assert nrel(B.cpu().numpy(), A @ P) <= 1e-12
+
+
+@pytest.mark.parametrize("n,r,pad", [(15, 1, 0), (16, 15, 1), (33, 32, 0), (65, 5, 0), (255, 31, 1),
+                                     (257, 33, 0), (1000, 20, 0), (1001, 35, 2), (3001, 21, 0),
+                                     (5000, 32, 1), (8190, 63, 0)])
+def test_dense_apass_f32_edges(S, n, r, pad):
+    """The general FP32 product (r <= 32, or odd r or n): K ranges of fewer, as many and more
+    batches than are in flight, remainders of single rows, edges of the 32-column blocks;
+    padding columns hold NaN and must not be read into the result.  Sums of n nonnegative
+    terms in FP32: |error| <= n 2^-24 of the entry."""
+    rng = np.random.default_rng(n + r)
+    A = rng.random((n, n), dtype=np.float32)
+    A = np.triu(A) + np.triu(A, 1).T
+    buf = torch.full((n, n + pad), float("nan"), dtype=torch.float32, device=DEV)
+    buf[:, :n] = torch.from_numpy(A).to(DEV)
+    P = rng.random((n, r), dtype=np.float32)
+    Pt = torch.from_numpy(P).to(DEV)
+    with S.Plan(S.dense(buf[:, :n]), r, S.params(prec=S.F32, max_outer=1)) as pl:
+        B = torch.empty_like(Pt)
+        pl.apass(Pt, B)
+    ref = A.astype(np.float64) @ P.astype(np.float64)
+    assert (np.abs(B.cpu().numpy() - ref) <= n * 2.0 ** -24 * ref).all()
