@@ -39,7 +39,7 @@ inline size_t elt_size(int prec) { return prec == SNMF_F64 ? 8 : 4; }
 // fuse_inner is set and a backtracked update is never clipped by the projection
 // (phi beta_shrink <= 1, no projection, or no backtracking), which their BB step after a
 // backtrack relies on.  They beat the two-kernel form at every size measured: where the
-// iteration is latency-bound (fewer kernels) and where it streams the n x r arrays (five
+// iteration is latency-bound (fewer kernels) and where it streams the n x r arrays (four
 // array transfers per inner iteration against six).
 inline bool fused_inner_ok(const snmf_params& p) {
   const bool unclipped = !p.project_update || p.max_ls == 0 || p.phi * p.beta_shrink <= 1.0;

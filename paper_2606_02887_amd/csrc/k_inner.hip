@@ -395,7 +395,7 @@ __device__ __forceinline__ void tile_direction(Smem<T, RP>& sm, const int (&lr)[
                                                const int (&cl)[8], const uint32_t (&bo)[8],
                                                int64_t row0, int64_t n, int r, const T (&x)[8],
                                                const T (&gv)[8], T rinv, T alpha, T lam,
-                                               T step1, int project, T* __restrict__ Dt,
+                                               T step1, int project,
                                                T* __restrict__ Xt, T* __restrict__ gt,
                                                double (&ls)[4], double (&sp)[3],
                                                double (&xp)[6]) {
@@ -419,7 +419,6 @@ __device__ __forceinline__ void tile_direction(Smem<T, RP>& sm, const int (&lr)[
     const T dd = ok ? second_dir(z[p], gz, alpha) : T(0);
     d[p] = dd;
     if (ok) {
-      sto(Dt, bo[p], dd);
       direction_sums(ls, gz, dd, gv[p], dz);
       const double dzd = (double)dz, gd = (double)gv[p];
       xp[0] = fmaT(dzd, dzd, xp[0]);
@@ -468,7 +467,7 @@ __global__ __launch_bounds__(kThreads, (DIR ? fused_occupancy<T, RP>() : inner_o
     int64_t bstride, T* __restrict__ Cout, T* __restrict__ g, const T* __restrict__ LX,
     const T* __restrict__ GT, int64_t n, int r, int is_hstep, KParams kp, State* __restrict__ st,
     double* __restrict__ partsA, BMap bm, T* __restrict__ Zn, T* __restrict__ Dn,
-    T* __restrict__ Dd, double* __restrict__ pout, T* __restrict__ Xs, T* __restrict__ gs) {
+    double* __restrict__ pout, T* __restrict__ Xs, T* __restrict__ gs) {
   const Loc lc = locate(bm, n, st, nullptr, kp.lam);
   st = lc.st;
   if (st->done) return;
@@ -581,8 +580,7 @@ __global__ __launch_bounds__(kThreads, (DIR ? fused_occupancy<T, RP>() : inner_o
     if constexpr (DIR != 0) {
       __syncthreads();  // every wave is done with the product on sm.a
       tile_direction<T, RP>(sm, lr, cl, bo, row0, n, r, x, gq, rinv, rinv, lam, step1,
-                            kp.project, tile_ptr(Dd, tb), tile_ptr(Xs, tb), tile_ptr(gs, tb), ls,
-                            sp, xp);
+                            kp.project, tile_ptr(Xs, tb), tile_ptr(gs, tb), ls, sp, xp);
     }
   }
   if constexpr (DIR != 0) {
@@ -1189,15 +1187,18 @@ __global__ __launch_bounds__(kThreads, (inner_occupancy<T, RP, V>())) void k_ste
 // partsC, as step 2 does).
 // Two buffer pairs (X0, g0) = the half-step's X and g, (X1, g1) scratch, alternate:
 // before kernel i, pair i % 2 holds the iterate X_i and its gradient, pair (i + 1) % 2 the
-// beta = 1 trial of X_{i+1}.  Kernel i leaves X_{i+1} in pair (i + 1) % 2 (the trial when
-// accepted, else overwritten) and the next trial in pair i % 2; the closing kernel copies
-// the final X into X0 when it sits in pair 1.  Partial sums alternate between two arrays
-// (pin of kernel i = pout of kernel i - 1).  A half-step that stops early (S = 0) marks
+// beta = 1 trial of X_{i+1}.  The direction is not stored: an accepted trial never needs it,
+// and a backtracked one forms it again from X_i and g_i (one more tile product); the kernel
+// moves 4 arrays per inner iteration instead of 5 (n = 200000, r = 32: 30 and 34 us in the
+// W- and H-step, 32 and 35.5 with the direction stored).  Kernel i leaves X_{i+1} in pair
+// (i + 1) % 2 (the trial when accepted, else overwritten) and the next trial in pair i % 2;
+// the closing kernel copies the final X into X0 when it sits in pair 1.  Partial sums
+// alternate between two arrays (pin of kernel i = pout of kernel i - 1).  A half-step that stops early (S = 0) marks
 // the remaining iterations stopped; their kernels return at once.
 template <typename T, int RP, int HS>
 __global__ __launch_bounds__(kThreads, (fused_occupancy<T, RP>())) void k_advance(
     T* __restrict__ X0, T* __restrict__ g0, T* __restrict__ X1, T* __restrict__ g1,
-    T* __restrict__ D, const T* __restrict__ C, const T* __restrict__ P,
+    const T* __restrict__ C, const T* __restrict__ P,
     const T* __restrict__ GT, const double* __restrict__ Gcur, const double* __restrict__ Gprev,
     int64_t n, int r, int K, int i, KParams kp, State* __restrict__ st,
     const double* __restrict__ pin, double* __restrict__ pout, const double* __restrict__ partsA,
@@ -1224,7 +1225,7 @@ __global__ __launch_bounds__(kThreads, (fused_occupancy<T, RP>())) void k_advanc
   // (unconditional loads, selected afterwards: a load under "i > 0" became a branch that
   // waited for it before any other load was issued)
   const int done = st->done, stop_i = st->stop[i];
-  const double rho = st->rho, e_raw = st->e[i];
+  const double rho = st->rho, e_raw = st->e[i], alpha_raw = st->alpha[i];
   const int stopped = i > 0 ? stop_i : 0;
   const double e_i = i > 0 ? e_raw : 0.0;
   double pa[kFusedParts];
@@ -1288,10 +1289,11 @@ __global__ __launch_bounds__(kThreads, (fused_occupancy<T, RP>())) void k_advanc
   const T rinv = (T)(1.0 / rho);
   const T lam = (T)kp.lam;
   const T step = (T)(kp.phi * beta), step1 = (T)(kp.phi * 1.0), alpha = (T)alpha_d;
+  const T alpha_i = i > 0 ? (T)alpha_raw : rinv;  // of direction i
   double ls[4] = {0.0, 0.0, 0.0, 0.0}, sp[3] = {0.0, 0.0, 0.0};
   double xp[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, mon[4] = {0.0, 0.0, 0.0, 0.0};
   // X_{i+1} and its gradient of one tile: the trial, or step 2's update formed from X_i,
-  // g_i and D_i (stored over the trial)
+  // g_i and D_i (formed again as tile_direction did; stored over the trial)
   auto next_tile = [&](int64_t row0, T (&xn)[8], T (&gn)[8]) {
     const int64_t tb = row0 * r;
     if (trial) {
@@ -1308,13 +1310,26 @@ __global__ __launch_bounds__(kThreads, (fused_occupancy<T, RP>())) void k_advanc
       const bool ok = row0 + lr[p] < n && cl[p] < r;
       x[p] = ok ? ldo(tile_ptr(Xc, tb), bo[p]) : T(0);
       go[p] = ok ? ldo(tile_ptr(gc, tb), bo[p]) : T(0);
-      const T dd = ok ? ldo(tile_ptr(D, tb), bo[p]) : T(0);
+    }
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      const bool ok = row0 + lr[p] < n && cl[p] < r;
       const T zz = first_proj(x[p], go[p], rinv);
+      sm.a[lr[p] * L::YP + cl[p]] = ok ? zz - x[p] : T(0);
+    }
+    __syncthreads();
+    T sg[8];
+    tile_gemm<T, RP>(sm.a, sm.G, sg);
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      const bool ok = row0 + lr[p] < n && cl[p] < r;
+      const T zz = first_proj(x[p], go[p], rinv);
+      const T gz = grad_at_z(go[p], sg[p], lam, zz - x[p]);
+      const T dd = ok ? second_dir(zz, gz, alpha_i) : T(0);
       xn[p] = ok ? next_point(zz, dd, step, kp.project) : T(0);
       sm.b[lr[p] * L::YP + cl[p]] = ok ? xn[p] - x[p] : T(0);
     }
     __syncthreads();
-    T sg[8];
     tile_gemm<T, RP>(sm.b, sm.G, sg);
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
@@ -1352,8 +1367,7 @@ __global__ __launch_bounds__(kThreads, (fused_occupancy<T, RP>())) void k_advanc
       if (trial && t + nb < ntiles) load_trial(row0 + (int64_t)nb * TM);
       // sm.a was last read before this tile's first barrier
       tile_direction<T, RP>(sm, lr, cl, bo, row0, n, r, xn, gn, rinv, alpha, lam, step1,
-                            kp.project, tile_ptr(D, tb), tile_ptr(Xc, tb), tile_ptr(gc, tb), ls,
-                            sp, xp);
+                            kp.project, tile_ptr(Xc, tb), tile_ptr(gc, tb), ls, sp, xp);
     }
   }
   if (dir) {
@@ -1451,23 +1465,23 @@ template <typename T>
 void launch_init(const T* X, const T* P, const T* Bpart, int ksplit, int64_t bstride, T* C, T* g,
                  const T* LX, const T* GT, int64_t n, int r, int is_hstep, const KParams& kp,
                  State* st, double* partsA, hipStream_t s, const BMap& bm, int grid, T* Zn,
-                 T* Dn, T* Dd, double* pout, T* Xs, T* gs) {
+                 T* Dn, double* pout, T* Xs, T* gs) {
   if (grid <= 0) grid = inner_grid(n, r, (int)sizeof(T));
-  if (Dd) {
+  if (Xs) {
     SNMF_DISPATCH_RP(rank_pad(r),
                      hipLaunchKernelGGL((k_init<T, RP, 1>), dim3(grid), dim3(kThreads), 0, s, X,
                                         P, Bpart, ksplit, bstride, C, g, LX, GT, n, r, is_hstep,
-                                        kp, st, partsA, bm, Zn, Dn, Dd, pout, Xs, gs))
+                                        kp, st, partsA, bm, Zn, Dn, pout, Xs, gs))
   } else {
     SNMF_DISPATCH_RP(rank_pad(r),
                      hipLaunchKernelGGL((k_init<T, RP, 0>), dim3(grid), dim3(kThreads), 0, s, X,
                                         P, Bpart, ksplit, bstride, C, g, LX, GT, n, r, is_hstep,
-                                        kp, st, partsA, bm, Zn, Dn, Dd, pout, Xs, gs))
+                                        kp, st, partsA, bm, Zn, Dn, pout, Xs, gs))
   }
 }
 
 template <typename T>
-void launch_advance(T* X, T* g, T* Xs, T* gs, T* D, const T* C, const T* P, const T* GT,
+void launch_advance(T* X, T* g, T* Xs, T* gs, const T* C, const T* P, const T* GT,
                     const double* Gcur, const double* Gprev, int64_t n, int r, int K, int i,
                     int is_hstep, const KParams& kp, State* st, const double* pin, double* pout,
                     const double* partsA, double* partsC, double* trace, hipStream_t s,
@@ -1476,12 +1490,12 @@ void launch_advance(T* X, T* g, T* Xs, T* gs, T* D, const T* C, const T* P, cons
   if (is_hstep) {
     SNMF_DISPATCH_RP(rank_pad(r),
                      hipLaunchKernelGGL((k_advance<T, RP, 1>), dim3(grid), dim3(kThreads), 0, s,
-                                        X, g, Xs, gs, D, C, P, GT, Gcur, Gprev, n, r, K, i, kp,
+                                        X, g, Xs, gs, C, P, GT, Gcur, Gprev, n, r, K, i, kp,
                                         st, pin, pout, partsA, partsC, trace))
   } else {
     SNMF_DISPATCH_RP(rank_pad(r),
                      hipLaunchKernelGGL((k_advance<T, RP, 0>), dim3(grid), dim3(kThreads), 0, s,
-                                        X, g, Xs, gs, D, C, P, GT, Gcur, Gprev, n, r, K, i, kp,
+                                        X, g, Xs, gs, C, P, GT, Gcur, Gprev, n, r, K, i, kp,
                                         st, pin, pout, partsA, partsC, trace))
   }
 }
@@ -1533,8 +1547,8 @@ void launch_step2(T* X, T* g, T* Z, T* D, const T* LS, const T* C, const T* P, T
 #define SNMF_INST(T)                                                                            \
   template void launch_init<T>(const T*, const T*, const T*, int, int64_t, T*, T*, const T*,   \
                                const T*, int64_t, int, int, const KParams&, State*, double*,   \
-                               hipStream_t, const BMap&, int, T*, T*, T*, double*, T*, T*);     \
-  template void launch_advance<T>(T*, T*, T*, T*, T*, const T*, const T*, const T*,          \
+                               hipStream_t, const BMap&, int, T*, T*, double*, T*, T*);         \
+  template void launch_advance<T>(T*, T*, T*, T*, const T*, const T*, const T*,              \
                                   const double*, const double*, int64_t, int, int, int, int,   \
                                   const KParams&, State*, const double*, double*,              \
                                   const double*, double*, double*, hipStream_t, int);          \

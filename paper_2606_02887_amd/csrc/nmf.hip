@@ -114,12 +114,12 @@ void half_step(NmfPlan& pl, T* X, int64_t nX, const T* P, int64_t nP, int is_hst
   // partial sums alternate between partsB and partsD
   const bool fused = run_inner && fused_inner_ok(pl.p);
   launch_init<T>(X, Pz, B, ksplit, nX * r, (T*)pl.C, g, nullptr, GT, nX, r, is_hstep, pl.kp,
-                 pl.st, pl.partsA, s, BMap{}, grid, nullptr, nullptr, fused ? D : nullptr,
+                 pl.st, pl.partsA, s, BMap{}, grid, nullptr, nullptr,
                  fused ? pl.partsB : nullptr, fused ? Z : nullptr, fused ? (T*)pl.gs : nullptr);
   if (fused) {
     const int K = pl.p.inner_iters;
     for (int i = 0; i < K; ++i)
-      launch_advance<T>(X, g, Z, (T*)pl.gs, D, (const T*)pl.C, Pz, GT, pl.G64[0], pl.G64[1], nX,
+      launch_advance<T>(X, g, Z, (T*)pl.gs, (const T*)pl.C, Pz, GT, pl.G64[0], pl.G64[1], nX,
                         r, K, i,
                         is_hstep, pl.kp, pl.st, (i & 1) ? pl.partsD : pl.partsB,
                         (i & 1) ? pl.partsB : pl.partsD, pl.partsA, pl.partsC, pl.trace, s,

@@ -308,8 +308,7 @@ snmf_status half_start(snmf_plan* pl, T* X, const T* P, int is_hstep, bool with_
   launch_init<T>(X, P, (const T*)pl->Bpart, ksplit_of(pl), n * r, (T*)pl->C, (T*)pl->g,
                  lap ? (const T*)pl->LX : nullptr, (const T*)pl->GT[gi], n, r, is_hstep, pl->kp,
                  pl->st, pl->partsA, s, BMap{}, pl->grid, lap ? (T*)pl->Z : nullptr,
-                 lap ? (T*)pl->D : nullptr, dir ? (T*)pl->D : nullptr,
-                 dir ? pl->partsB : nullptr, dir ? (T*)pl->Z : nullptr,
+                 lap ? (T*)pl->D : nullptr, dir ? pl->partsB : nullptr, dir ? (T*)pl->Z : nullptr,
                  dir ? (T*)pl->gs : nullptr);
   HIP_TRY(hipGetLastError());
   return SNMF_OK;
@@ -375,7 +374,7 @@ snmf_status inner_steps(snmf_plan* pl, T* X, const T* P, int is_hstep, hipStream
   const int K = pl->p.inner_iters;
   if (fused) {
     for (int i = 0; i < K; ++i) {
-      launch_advance<T>(X, (T*)pl->g, (T*)pl->Z, (T*)pl->gs, (T*)pl->D, (const T*)pl->C, P,
+      launch_advance<T>(X, (T*)pl->g, (T*)pl->Z, (T*)pl->gs, (const T*)pl->C, P,
                         (const T*)pl->GT[is_hstep ? 1 : 0], pl->G64[0], pl->G64[1], pl->n, pl->r,
                         K, i, is_hstep, pl->kp, pl->st, (i & 1) ? pl->partsD : pl->partsB,
                         (i & 1) ? pl->partsB : pl->partsD, pl->partsA, pl->partsC, pl->trace, s,

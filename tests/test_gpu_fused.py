@@ -105,6 +105,22 @@ def test_fused_backtracking_matches_oracle(S):
     assert e_two <= 1e-10
 
 
+@pytest.mark.parametrize("n,r", [(40000, 64), (3000, 17), (1500, 3)])
+def test_fused_backtracking_forms_the_direction_again(S, n, r):
+    """After a backtrack a fused kernel forms D again from X_i and g_i, for every row tile of
+    its workgroup (n = 40000, r = 64: 1250 tiles on 1024 workgroups) and in each layout of
+    a tile (ranks below 16 and from 16 on).  FP64: the two paths agree to 1e-10."""
+    a_ = gen.random_symmetric_csr(n, 6.0, 3)
+    rng = np.random.default_rng(r)
+    W0 = gen.start_factor(rng, n, r, gen.mean_of_sparse(a_))
+    a, b = _both(S, S.csr_from_scipy(a_, torch.float64), _t(W0, torch.float64),
+                 lam=0.01 * float(np.sqrt(np.sum(a_.data ** 2))), prec=S.F64, max_outer=3,
+                 theta=0.5, eta=0.0, max_ls=20)
+    assert a[2]["ls_evals"] > a[2]["inner_total"]  # some trials backtracked
+    for u, v in ((a[0], b[0]), (a[1], b[1])):
+        assert np.abs(u - v).max() <= 1e-10 * np.abs(v).max()
+
+
 @pytest.mark.parametrize("inner", [1, 3, 5])
 def test_fused_inner_counts_same_bits(S, inner):
     A, W0, lam = _planted(500, 16, 5 + inner)
