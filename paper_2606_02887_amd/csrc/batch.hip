@@ -73,13 +73,14 @@ snmf_status bcheck_csr(snmf_batch* b, const snmf_matrix* M, const std::string& w
   return SNMF_OK;
 }
 
-// G64 set (dense BF16X3 only): rho of every instance inside the stacked A-pass launches
-// (the product's when its workgroups fit, else the split's), from its Gram in G64
+// G64 set (CSR, dense BF16X3): rho of every instance inside the A-pass launches, from its
+// Gram in G64 (BF16X3: the product's when its workgroups fit, else the split's)
 template <typename T>
 snmf_status bapass(snmf_batch* b, const T* P, T* B, hipStream_t s,
                    const double* G64 = nullptr) {
   if (!b->dense) {
-    launch_bspmm<T>(b->dgraph, b->sblk_tab, b->sblocks, b->states, P, B, s);
+    launch_bspmm<T>(b->dgraph, b->sblk_tab, b->sblocks, b->states, P, B, s, b->dinst,
+                    G64 ? b->ninst : 0, G64);
     HIP_TRY(hipGetLastError());
     return SNMF_OK;
   }
@@ -140,8 +141,7 @@ snmf_status bhalf_start(snmf_batch* b, T* X, const T* P, int is_hstep, bool with
   launch_bgram_reduce<T>(b->dinst, b->ninst, b->max_r, b->states, b->gpart, b->G64[gi],
                          (T*)b->GT[gi], s);
   HIP_TRY(hipGetLastError());
-  // dense BF16X3: rho runs inside the stacked A-pass launches (product or split)
-  const bool rho_in_apass = b->dense && b->prec == SNMF_BF16X3;
+  const bool rho_in_apass = !b->dense || b->prec == SNMF_BF16X3;
   if (with_rho && !rho_in_apass) {
     launch_brho(b->dinst, b->ninst, b->states, b->G64[gi], s);
     HIP_TRY(hipGetLastError());
@@ -297,9 +297,13 @@ snmf_status batch_create(int32_t nprob, const snmf_matrix* A, const int32_t* r, 
   b->gpsum = gpoff;
   b->gblocks = gblk;
   std::vector<int32_t> gtab;
-  // classes: instances grouped by rank, in instance order within a class
+  // classes: ranks up to 32 in one, above in the other; in a class by decreasing rank (the
+  // workgroups with the most work start first), then in instance order
   std::map<int, std::vector<int>> by_r;
-  for (int i = 0; i < b->ninst; ++i) by_r[b->hinst[i].r].push_back(i);
+  for (int i = 0; i < b->ninst; ++i) by_r[b->hinst[i].r <= 32 ? 32 : 64].push_back(i);
+  for (auto& kv : by_r)
+    std::stable_sort(kv.second.begin(), kv.second.end(),
+                     [&](int x, int y) { return b->hinst[x].r > b->hinst[y].r; });
   std::vector<int32_t> btab;
   int part_row = 0;
   // row tiles per inner-kernel workgroup: more than one amortises each workgroup's fixed
@@ -309,8 +313,6 @@ snmf_status batch_create(int32_t nprob, const snmf_matrix* A, const int32_t* r, 
   for (auto& kv : by_r) {
     snmf_batch::Cls c;
     c.r = kv.first;
-    const int rp = rank_pad(c.r);
-    const int tpb = tpb_cls[rp <= 8 ? 0 : rp <= 16 ? 1 : rp <= 32 ? 2 : 3];
     c.tab_off = (int64_t)btab.size();
     c.gtab_off = (int64_t)gtab.size();
     int blk = 0, gb = 0;
@@ -318,10 +320,19 @@ snmf_status batch_create(int32_t nprob, const snmf_matrix* A, const int32_t* r, 
       BInst& d = b->hinst[i];
       d.blk0 = blk;
       {
-        const int tm = 8 * kThreads / rank_pad(d.r);
+        const int rp = rank_pad(d.r), tm = 8 * kThreads / rp;
+        const int tpb = tpb_cls[rp <= 8 ? 0 : rp <= 16 ? 1 : rp <= 32 ? 2 : 3];
         const int64_t nt = std::max<int64_t>(1, (d.n + tm - 1) / tm);
         d.nblk = (int)std::min<int64_t>(kInnerGrid, (nt + tpb - 1) / tpb);
       }
+      if (b->ranks.empty() || b->ranks.back().r != d.r) {
+        snmf_batch::Cls q;
+        q.r = d.r;
+        q.base = blk;
+        q.tab_off = (int64_t)btab.size();
+        b->ranks.push_back(q);
+      }
+      b->ranks.back().blocks += d.nblk;
       d.part0 = part_row;
       for (int j = 0; j < d.nblk; ++j) btab.push_back(i);
       blk += d.nblk;

@@ -33,14 +33,16 @@ struct snmf_batch {
   std::vector<uint16_t*> Ahi, Alo;           // BF16X3: split A of every problem
   uint16_t *Pthi = nullptr, *Ptlo = nullptr; // BF16X3: stacked split P of one problem
   bool rho_in_apass = false;                 // BF16X3: rho in the product (else split) launch
-  struct Cls {
-    int r = 0;
+  struct Cls {             // instances that share a launch: ranks up to 32, ranks above
+    int r = 0;             // 32 or 64
     int blocks = 0;        // inner-kernel workgroups
+    int base = 0;          // the first one's number in its class (ranks below)
     int64_t tab_off = 0;   // their first entry in blk_tab
     int gblocks = 0;       // Gram workgroups
     int64_t gtab_off = 0;  // their first entry in gblk_tab
   };
   std::vector<Cls> cls;
+  std::vector<Cls> ranks;  // the instances of one rank: a contiguous part of their class
   int gblocks = 0, sblocks = 0, max_r = 0, part_rows = 0;
   int64_t total = 0, max_nr = 0, gsum = 0, gpsum = 0;
   int ksplit_max = 1;
@@ -74,6 +76,7 @@ struct snmf_batch {
     m.states = states;
     m.traces = traces;
     m.trace_stride = trace_stride;
+    m.base = c.base;
     return m;
   }
 

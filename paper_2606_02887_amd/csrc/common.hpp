@@ -89,7 +89,7 @@ struct BInst {
   int64_t off;     // element offset of the instance's n x r arrays
   int64_t n;
   int32_t r;
-  int32_t blk0;    // inner kernels: first workgroup of the instance in its class launch
+  int32_t blk0;    // inner kernels: first workgroup of the instance in its class
   int32_t nblk;    //   and its number of workgroups (<= kInnerGrid)
   int32_t part0;   //   first row of its partial sums
   int64_t goff;    // element offset of its r x r Gram (FP64 and iterate-type copies)
@@ -126,6 +126,7 @@ struct BMap {
   State* states;            // one State per instance
   double* traces;           // per-instance traces of trace_stride doubles (nullable)
   int64_t trace_stride;
+  int32_t base;             // first workgroup of the class in this launch (one rank's part)
 };
 
 // Cross-lane data movement with DPP (GFX9 encoding).  Lanes whose source is outside the

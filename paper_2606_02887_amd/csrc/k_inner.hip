@@ -256,13 +256,13 @@ __device__ __forceinline__ void load_cols(const double* __restrict__ part, int n
 // and offsets the batch buffers, Gram copies, partial sums, State and trace by it.
 struct Loc {
   int64_t off, n, goff, poff;
-  int bid, nb;
+  int bid, nb, r;
   State* st;
   double* trace;
   double lam;
 };
-__device__ __forceinline__ Loc locate(const BMap& bm, int64_t n, State* st, double* trace,
-                                      double lam) {
+__device__ __forceinline__ Loc locate(const BMap& bm, int64_t n, int r, State* st,
+                                      double* trace, double lam) {
   Loc l;
   if (bm.blk_inst == nullptr) {
     l.off = 0;
@@ -271,6 +271,7 @@ __device__ __forceinline__ Loc locate(const BMap& bm, int64_t n, State* st, doub
     l.poff = 0;
     l.bid = blockIdx.x;
     l.nb = gridDim.x;
+    l.r = r;
     l.st = st;
     l.trace = trace;
     l.lam = lam;
@@ -283,6 +284,7 @@ __device__ __forceinline__ Loc locate(const BMap& bm, int64_t n, State* st, doub
     l.poff = (int64_t)d->part0 * kNumPart;
     l.bid = (int)blockIdx.x - d->blk0;
     l.nb = d->nblk;
+    l.r = d->r;
     l.st = bm.states + i;
     l.trace = bm.traces ? bm.traces + (size_t)i * bm.trace_stride : nullptr;
     l.lam = d->lam;
@@ -462,16 +464,17 @@ __device__ __forceinline__ void tile_direction(Smem<T, RP>& sm, const int (&lr)[
 // its sums (tile_direction) into pout and its beta = 1 trial update into (Xs, gs); the
 // first fused kernel runs its line search.
 template <typename T, int RP, int DIR>
-__global__ __launch_bounds__(kThreads, (DIR ? fused_occupancy<T, RP>() : inner_occupancy<T, RP>())) void k_init(
-    const T* __restrict__ X, const T* __restrict__ P, const T* __restrict__ Bpart, int ksplit,
+__device__ __forceinline__ void init_body(
+    Smem<T, RP>& sm, const T* __restrict__ X, const T* __restrict__ P, const T* __restrict__ Bpart, int ksplit,
     int64_t bstride, T* __restrict__ Cout, T* __restrict__ g, const T* __restrict__ LX,
     const T* __restrict__ GT, int64_t n, int r, int is_hstep, KParams kp, State* __restrict__ st,
     double* __restrict__ partsA, BMap bm, T* __restrict__ Zn, T* __restrict__ Dn,
     double* __restrict__ pout, T* __restrict__ Xs, T* __restrict__ gs) {
-  const Loc lc = locate(bm, n, st, nullptr, kp.lam);
+  const Loc lc = locate(bm, n, r, st, nullptr, kp.lam);
   st = lc.st;
   if (st->done) return;
   n = lc.n;
+  r = lc.r;
   kp.lam = lc.lam;
   X += lc.off;
   P += lc.off;
@@ -483,7 +486,6 @@ __global__ __launch_bounds__(kThreads, (DIR ? fused_occupancy<T, RP>() : inner_o
   partsA += lc.poff;
   typedef Lay<T, RP> L;
   constexpr int TM = L::TM;
-  __shared__ Smem<T, RP> sm;
   const int tid = threadIdx.x;
   int lr[8], cl[8];
   uint32_t bo[8];
@@ -597,6 +599,49 @@ __global__ __launch_bounds__(kThreads, (DIR ? fused_occupancy<T, RP>() : inner_o
     double* pa = partsA + (size_t)lc.bid * kNumPart;
     block_sum_emit<1>(v, sm.red, [&](int j, double a) { pa[j] = a; });
   }
+}
+
+template <typename T, int RP, int DIR>
+__global__ __launch_bounds__(kThreads, (DIR ? fused_occupancy<T, RP>() : inner_occupancy<T, RP>())) void k_init(
+    const T* __restrict__ X, const T* __restrict__ P, const T* __restrict__ Bpart, int ksplit,
+    int64_t bstride, T* __restrict__ Cout, T* __restrict__ g, const T* __restrict__ LX,
+    const T* __restrict__ GT, int64_t n, int r, int is_hstep, KParams kp, State* __restrict__ st,
+    double* __restrict__ partsA, BMap bm, T* __restrict__ Zn, T* __restrict__ Dn,
+    double* __restrict__ pout, T* __restrict__ Xs, T* __restrict__ gs) {
+  __shared__ Smem<T, RP> sm;
+  init_body<T, RP, DIR>(sm, X, P, Bpart, ksplit, bstride, Cout, g, LX, GT, n, r, is_hstep, kp, st,
+                        partsA, bm, Zn, Dn, pout, Xs, gs);
+}
+
+// ----------------------------------------------------------------------------- ranks up to 32
+// The instances of a batch whose rank is at most 32 share one launch per kernel: the
+// workgroup picks the layout of its instance's rank.  One launch per rank left most of the
+// chip idle at each one's end and start (30 graphs of 500 to 5000 rows, 8 restarts, ranks
+// 8, 16, 32: step 1 29.6, step 2 38.6, the init 51 us per inner iteration or half-step,
+// with one launch per rank 45, 60 and 51).  Ranks above 32 need more registers and LDS and
+// keep a launch of their own.
+template <typename T>
+struct __attribute__((aligned(32))) SmemMax {
+  static constexpr size_t mx(size_t a, size_t b) { return a > b ? a : b; }
+  unsigned char b[mx(mx(sizeof(Smem<T, 4>), sizeof(Smem<T, 8>)),
+                     mx(sizeof(Smem<T, 16>), sizeof(Smem<T, 32>)))];
+};
+#define SNMF_RANK_BODY(...)                                                          \
+  __shared__ SmemMax<T> mem;                                                         \
+  const int rr = bm.inst[bm.blk_inst[blockIdx.x]].r;                                 \
+  if (rr <= 4) { constexpr int RP = 4; Smem<T, RP>& sm = *(Smem<T, RP>*)&mem; __VA_ARGS__; }        \
+  else if (rr <= 8) { constexpr int RP = 8; Smem<T, RP>& sm = *(Smem<T, RP>*)&mem; __VA_ARGS__; }   \
+  else if (rr <= 16) { constexpr int RP = 16; Smem<T, RP>& sm = *(Smem<T, RP>*)&mem; __VA_ARGS__; } \
+  else { constexpr int RP = 32; Smem<T, RP>& sm = *(Smem<T, RP>*)&mem; __VA_ARGS__; }
+
+template <typename T>
+__global__ __launch_bounds__(kThreads, (inner_occupancy<T, 32>())) void k_binit(
+    const T* __restrict__ X, const T* __restrict__ P, const T* __restrict__ Bpart,
+    T* __restrict__ Cout, T* __restrict__ g, const T* __restrict__ GT, int is_hstep, KParams kp,
+    double* __restrict__ partsA, BMap bm) {
+  SNMF_RANK_BODY(init_body<T, RP, 0>(sm, X, P, Bpart, 1, 0, Cout, g, nullptr, GT, 0, 0, is_hstep,
+                                     kp, nullptr, partsA, bm, nullptr, nullptr, nullptr, nullptr,
+                                     nullptr))
 }
 
 // ----------------------------------------------------------------------------- entry
@@ -789,18 +834,19 @@ __device__ int inner_entry(int k, int is_hstep, int r, const KParams& kp, State*
 // V = 0: phase 0 only (a compile-time constant, so the Laplacian operands and their
 // registers drop out); V = 1: any phase.
 template <typename T, int RP, int V>
-__global__ __launch_bounds__(kThreads, (inner_occupancy<T, RP>())) void k_step1(
-    const T* __restrict__ X, const T* __restrict__ g, T* __restrict__ Z, T* __restrict__ D,
+__device__ __forceinline__ void step1_body(
+    Smem<T, RP>& sm, const T* __restrict__ X, const T* __restrict__ g, T* __restrict__ Z, T* __restrict__ D,
     const T* __restrict__ LdZ, const T* __restrict__ GT, const double* __restrict__ Gcur,
     const double* __restrict__ Gprev, int64_t n, int r, int k, int phase, int is_hstep,
     KParams kp, State* __restrict__ st, const double* __restrict__ partsA,
     double* __restrict__ partsB, const double* __restrict__ partsC, double* __restrict__ trace,
     BMap bm, int rd) {
   if constexpr (V == 0) phase = 0;
-  const Loc lc = locate(bm, n, st, trace, kp.lam);
+  const Loc lc = locate(bm, n, r, st, trace, kp.lam);
   st = lc.st;
   trace = lc.trace;
   n = lc.n;
+  r = lc.r;
   kp.lam = lc.lam;
   X += lc.off;
   g += lc.off;
@@ -815,7 +861,6 @@ __global__ __launch_bounds__(kThreads, (inner_occupancy<T, RP>())) void k_step1(
   partsC += lc.poff;
   typedef Lay<T, RP> L;
   constexpr int TM = L::TM;
-  __shared__ Smem<T, RP> sm;
   int lr[8], cl[8];
   uint32_t bo[8];
 #pragma unroll
@@ -915,6 +960,30 @@ __global__ __launch_bounds__(kThreads, (inner_occupancy<T, RP>())) void k_step1(
   block_sum_emit<4>(v, sm.red, [&](int j, double a) { pb[j] = a; });
 }
 
+template <typename T, int RP, int V>
+__global__ __launch_bounds__(kThreads, (inner_occupancy<T, RP>())) void k_step1(
+    const T* __restrict__ X, const T* __restrict__ g, T* __restrict__ Z, T* __restrict__ D,
+    const T* __restrict__ LdZ, const T* __restrict__ GT, const double* __restrict__ Gcur,
+    const double* __restrict__ Gprev, int64_t n, int r, int k, int phase, int is_hstep,
+    KParams kp, State* __restrict__ st, const double* __restrict__ partsA,
+    double* __restrict__ partsB, const double* __restrict__ partsC, double* __restrict__ trace,
+    BMap bm, int rd) {
+  __shared__ Smem<T, RP> sm;
+  step1_body<T, RP, V>(sm, X, g, Z, D, LdZ, GT, Gcur, Gprev, n, r, k, phase, is_hstep, kp, st,
+                       partsA, partsB, partsC, trace, bm, rd);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kThreads, (inner_occupancy<T, 32>())) void k_bstep1(
+    const T* __restrict__ X, const T* __restrict__ g, const T* __restrict__ GT,
+    const double* __restrict__ Gcur, const double* __restrict__ Gprev, int k, int is_hstep,
+    KParams kp, const double* __restrict__ partsA, double* __restrict__ partsB,
+    const double* __restrict__ partsC, BMap bm) {
+  SNMF_RANK_BODY(step1_body<T, RP, 0>(sm, X, g, nullptr, nullptr, nullptr, GT, Gcur, Gprev, 0, 0,
+                                      k, 0, is_hstep, kp, nullptr, partsA, partsB, partsC,
+                                      nullptr, bm, 1))
+}
+
 // ----------------------------------------------------------------------------- line search
 // Backtracking from beta = 1 by beta_shrink, at most max_ls reductions (the last beta is
 // kept when the cap is hit).  Algorithm 1 accepts beta when
@@ -959,8 +1028,8 @@ __device__ __forceinline__ double line_search(double delta, double q, double dZ,
 // rd (phase 0): step 1 stored no D; step 2 forms it again from X, g, G and alpha_k with
 // the same operations in the same order, so it holds the same bits.
 template <typename T, int RP, int V>
-__global__ __launch_bounds__(kThreads, (inner_occupancy<T, RP, V>())) void k_step2(
-    T* __restrict__ X, T* __restrict__ g, T* __restrict__ Z, T* __restrict__ D,
+__device__ __forceinline__ void step2_body(
+    Smem<T, RP>& sm, T* __restrict__ X, T* __restrict__ g, T* __restrict__ Z, T* __restrict__ D,
     const T* __restrict__ LS, const T* __restrict__ C, const T* __restrict__ P,
     T* __restrict__ LXb, const T* __restrict__ GT, int64_t n, int r, int k, int phase,
     int is_hstep, KParams kp, State* __restrict__ st, const double* __restrict__ partsB,
@@ -969,9 +1038,10 @@ __global__ __launch_bounds__(kThreads, (inner_occupancy<T, RP, V>())) void k_ste
     phase = 0;
     is_hstep = V == 0 ? 0 : 1;
   }
-  const Loc lc = locate(bm, n, st, nullptr, kp.lam);
+  const Loc lc = locate(bm, n, r, st, nullptr, kp.lam);
   st = lc.st;
   n = lc.n;
+  r = lc.r;
   kp.lam = lc.lam;
   X += lc.off;
   g += lc.off;
@@ -986,7 +1056,6 @@ __global__ __launch_bounds__(kThreads, (inner_occupancy<T, RP, V>())) void k_ste
   partsC += lc.poff;
   typedef Lay<T, RP> L;
   constexpr int TM = L::TM;
-  __shared__ Smem<T, RP> sm;
   int lr[8], cl[8];
   uint32_t bo[8];
 #pragma unroll
@@ -1170,6 +1239,27 @@ __global__ __launch_bounds__(kThreads, (inner_occupancy<T, RP, V>())) void k_ste
     st->pending = 1;
     st->t_hstep = wall_clock64();
   }
+}
+
+template <typename T, int RP, int V>
+__global__ __launch_bounds__(kThreads, (inner_occupancy<T, RP, V>())) void k_step2(
+    T* __restrict__ X, T* __restrict__ g, T* __restrict__ Z, T* __restrict__ D,
+    const T* __restrict__ LS, const T* __restrict__ C, const T* __restrict__ P,
+    T* __restrict__ LXb, const T* __restrict__ GT, int64_t n, int r, int k, int phase,
+    int is_hstep, KParams kp, State* __restrict__ st, const double* __restrict__ partsB,
+    const double* __restrict__ partsD, int nbD, double* __restrict__ partsC, BMap bm, int rd) {
+  __shared__ Smem<T, RP> sm;
+  step2_body<T, RP, V>(sm, X, g, Z, D, LS, C, P, LXb, GT, n, r, k, phase, is_hstep, kp, st, partsB,
+                       partsD, nbD, partsC, bm, rd);
+}
+
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads, (inner_occupancy<T, 32>())) void k_bstep2(
+    T* __restrict__ X, T* __restrict__ g, const T* __restrict__ C, const T* __restrict__ P,
+    const T* __restrict__ GT, int k, KParams kp, const double* __restrict__ partsB,
+    double* __restrict__ partsC, BMap bm) {
+  SNMF_RANK_BODY(step2_body<T, RP, V>(sm, X, g, nullptr, nullptr, nullptr, C, P, nullptr, GT, 0, 0,
+                                      k, 0, 0, kp, nullptr, partsB, nullptr, 0, partsC, bm, 1))
 }
 
 // ----------------------------------------------------------------------------- fused
@@ -1467,7 +1557,10 @@ void launch_init(const T* X, const T* P, const T* Bpart, int ksplit, int64_t bst
                  State* st, double* partsA, hipStream_t s, const BMap& bm, int grid, T* Zn,
                  T* Dn, double* pout, T* Xs, T* gs) {
   if (grid <= 0) grid = inner_grid(n, r, (int)sizeof(T));
-  if (Xs) {
+  if (bm.blk_inst && r <= 32) {
+    hipLaunchKernelGGL(k_binit<T>, dim3(grid), dim3(kThreads), 0, s, X, P, Bpart, C, g, GT,
+                       is_hstep, kp, partsA, bm);
+  } else if (Xs) {
     SNMF_DISPATCH_RP(rank_pad(r),
                      hipLaunchKernelGGL((k_init<T, RP, 1>), dim3(grid), dim3(kThreads), 0, s, X,
                                         P, Bpart, ksplit, bstride, C, g, LX, GT, n, r, is_hstep,
@@ -1507,7 +1600,10 @@ void launch_step1(const T* X, const T* g, T* Z, T* D, const T* LdZ, const T* GT,
                   double* partsB, const double* partsC, double* trace, hipStream_t s,
                   const BMap& bm, int grid, int rd) {
   if (grid <= 0) grid = inner_grid(n, r, (int)sizeof(T));
-  if (phase == 0) {
+  if (bm.blk_inst && r <= 32) {
+    hipLaunchKernelGGL(k_bstep1<T>, dim3(grid), dim3(kThreads), 0, s, X, g, GT, Gcur, Gprev, k,
+                       is_hstep, kp, partsA, partsB, partsC, bm);
+  } else if (phase == 0) {
     SNMF_DISPATCH_RP(rank_pad(r),
                      hipLaunchKernelGGL((k_step1<T, RP, 0>), dim3(grid), dim3(kThreads), 0, s, X,
                                         g, Z, D, LdZ, GT, Gcur, Gprev, n, r, k, phase, is_hstep,
@@ -1532,7 +1628,14 @@ void launch_step2(T* X, T* g, T* Z, T* D, const T* LS, const T* C, const T* P, T
                    hipLaunchKernelGGL((k_step2<T, RP, V>), dim3(grid), dim3(kThreads), 0, s, X, \
                                       g, Z, D, LS, C, P, LXb, GT, n, r, k, phase, is_hstep, kp, \
                                       st, partsB, partsD, nbD, partsC, bm, rd))
-  if (phase != 0) {
+#define SNMF_BSTEP2(V)                                                                    \
+  hipLaunchKernelGGL((k_bstep2<T, V>), dim3(grid), dim3(kThreads), 0, s, X, g, C, P, GT, k, kp, \
+                     partsB, partsC, bm)
+  if (bm.blk_inst && r <= 32) {
+    if (!is_hstep) SNMF_BSTEP2(0);
+    else if (k >= last_k) SNMF_BSTEP2(1);
+    else SNMF_BSTEP2(3);
+  } else if (phase != 0) {
     SNMF_STEP2(2)
   } else if (is_hstep && k >= last_k) {
     SNMF_STEP2(1)
@@ -1542,6 +1645,7 @@ void launch_step2(T* X, T* g, T* Z, T* D, const T* LS, const T* C, const T* P, T
     SNMF_STEP2(0)
   }
 #undef SNMF_STEP2
+#undef SNMF_BSTEP2
 }
 
 #define SNMF_INST(T)                                                                            \

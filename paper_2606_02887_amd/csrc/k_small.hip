@@ -150,8 +150,9 @@ __global__ __launch_bounds__(kThreads) void k_gram(const T* __restrict__ P, int6
   gram_slab<T, RPG>(P, r, rb, re, part + (size_t)blockIdx.x * r * r);
 }
 
-// Batched: the workgroups of one rank class; workgroup -> (instance, slab) through
-// gblk_inst.  The same slabs as a single solve of that instance, so G is bitwise equal.
+// Batched: the instances of rank up to 32 (RPG = 32) or above it; workgroup -> (instance,
+// slab) through gblk_inst.  The same slabs as a single solve of that instance, so G is
+// bitwise equal.
 template <typename T, int RPG>
 __global__ __launch_bounds__(kThreads) void k_bgram(const T* __restrict__ P,
                                                     const int32_t* __restrict__ gblk_inst,
@@ -164,7 +165,11 @@ __global__ __launch_bounds__(kThreads) void k_bgram(const T* __restrict__ P,
   const int j = (int)blockIdx.x - d->gblk0;
   const int64_t rb = (int64_t)j * d->grpb;
   const int64_t re = rb + d->grpb < d->n ? rb + d->grpb : d->n;
-  gram_slab<T, RPG>(P + d->off, d->r, rb, re, gpart + d->gpoff + (size_t)j * d->r * d->r);
+  double* out = gpart + d->gpoff + (size_t)j * d->r * d->r;
+  if (RPG <= 32 && d->r <= 16)
+    gram_slab<T, 16>(P + d->off, d->r, rb, re, out);
+  else
+    gram_slab<T, RPG>(P + d->off, d->r, rb, re, out);
 }
 
 // Sum over the slabs b = q, q + 4, q + 8, ... (in increasing b) of entry e; the Gram is
@@ -405,9 +410,12 @@ void launch_rho(const double* G, int r, State* st, hipStream_t s) {
 template <typename T>
 void launch_bgram(const T* P, int r, const int32_t* gblk_inst, int gblocks, const BInst* inst,
                   const State* states, double* gpart, hipStream_t s) {
-  SNMF_DISPATCH_RPG(rank_pad(r),
-                    hipLaunchKernelGGL((k_bgram<T, RPG>), dim3(gblocks), dim3(kThreads), 0, s, P,
-                                       gblk_inst, inst, states, gpart))
+  if (r <= 32)
+    hipLaunchKernelGGL((k_bgram<T, 32>), dim3(gblocks), dim3(kThreads), 0, s, P, gblk_inst, inst,
+                       states, gpart);
+  else
+    hipLaunchKernelGGL((k_bgram<T, 64>), dim3(gblocks), dim3(kThreads), 0, s, P, gblk_inst, inst,
+                       states, gpart);
 }
 template <typename T>
 void launch_bgram_reduce(const BInst* inst, int ninst, int max_r, const State* states,

@@ -116,19 +116,90 @@ __global__ __launch_bounds__(256) void k_spmm(const int64_t* __restrict__ rowptr
   if (threadIdx.x == 0) part[(size_t)bid * kNumPart] = v[0];
 }
 
+// Lane k's value, wave-uniform.
+__device__ __forceinline__ float lane_value(float v, int k) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
+}
+__device__ __forceinline__ double lane_value(double v, int k) { return readlane_d(v, k); }
+
 // ----------------------------------------------------------------------------- batched
 // Stacked A-pass of a batched solve: B_s = A P_s for all S restarts of a problem in one
 // sweep over its CSR (the restarts form one n x (S r) operand).  One wavefront per row;
 // lane c of a chunk of cw columns (cw = 64, or the smallest power of two >= S r) serves
 // stacked column c0 + c = s r + j, and the 64 / cw lane groups split the row's nonzeros.
-// The wave loads up to 64 (column, value) pairs of the row at once and broadcasts them
-// with cross-lane shuffles, so the gathers of four nonzeros are in flight together.
+// The wave loads up to 64 (column, value) pairs of the row at once and reads them across
+// lanes.  Bound by the latency of the gathers of P: more than 32 columns (cw = 64) run
+// wide_row, which takes up to four chunks of columns together and keeps 16 gathers in
+// flight, and the next row's pairs and the row pointers after it are loaded ahead (30
+// graphs of 500 to 5000 rows with 35 nonzeros per row, 8 restarts, ranks 8, 16, 32: 107
+// us with rho inside; one chunk at a time with four gathers in flight 184 us).
+// Workgroups 0 .. nrho - 1 compute rho = ||G||_2 of the instances (rho.hpp) beside the rows
+// (29 us in a launch of its own), first in dispatch order because each is one long chain.
+
+// The sums of one row for NC chunks of 64 columns, nonzeros in increasing order, U of them
+// in flight.  pl[q]: this lane's column of chunk q (clamped to a valid one); mc, mv: the
+// first 64 (column, value) pairs; `more` loads the next 64.
+template <typename T, int NC, int U, typename F>
+__device__ __forceinline__ void wide_row(const T* const (&pl)[NC], int r, int64_t cnt, int mc,
+                                         T mv, F&& more, T (&acc)[NC]) {
+#pragma unroll
+  for (int q = 0; q < NC; ++q) acc[q] = T(0);
+  for (int64_t z0 = 0;;) {
+    const int c = cnt - z0 < kWave ? (int)(cnt - z0) : kWave;
+    int k0 = 0;
+    for (; k0 + U <= c; k0 += U) {
+      T pk[U][NC];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t o = (int64_t)__builtin_amdgcn_readlane(mc, k0 + u) * r;
+#pragma unroll
+        for (int q = 0; q < NC; ++q) pk[u][q] = pl[q][o];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const T v = lane_value(mv, k0 + u);
+#pragma unroll
+        for (int q = 0; q < NC; ++q) acc[q] += v * pk[u][q];
+      }
+    }
+    if (k0 < c) {  // the last ones: loads repeat the last nonzero, products past it are dropped
+      T pk[U][NC];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t o = (int64_t)__builtin_amdgcn_readlane(mc, k0 + u < c ? k0 + u : c - 1) * r;
+#pragma unroll
+        for (int q = 0; q < NC; ++q) pk[u][q] = pl[q][o];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const T v = lane_value(mv, k0 + u < c ? k0 + u : c - 1);
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+          const T t = acc[q] + v * pk[u][q];
+          acc[q] = k0 + u < c ? t : acc[q];
+        }
+      }
+    }
+    z0 += kWave;
+    if (z0 >= cnt) break;
+    more(z0, mc, mv);
+  }
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_bspmm(const BGraph* __restrict__ graphs,
                                                const int32_t* __restrict__ sblk_graph,
-                                               const State* __restrict__ states,
-                                               const T* __restrict__ P, T* __restrict__ B) {
-  const BGraph* G = graphs + sblk_graph[blockIdx.x];
+                                               State* __restrict__ states,
+                                               const T* __restrict__ P, T* __restrict__ B,
+                                               const BInst* __restrict__ inst, int nrho,
+                                               const double* __restrict__ G64) {
+  if ((int)blockIdx.x < nrho) {
+    const int i = blockIdx.x;
+    if (!states[i].done) rho_body(G64 + inst[i].goff, inst[i].r, states + i);
+    return;
+  }
+  const int bid = (int)blockIdx.x - nrho;
+  const BGraph* G = graphs + sblk_graph[bid];
   const int r = G->r, S = G->S;
   bool all_done = true;
   for (int s = 0; s < S; ++s) all_done = all_done && states[G->inst0 + s].done;
@@ -140,7 +211,8 @@ __global__ __launch_bounds__(256) void k_bspmm(const BGraph* __restrict__ graphs
   const int ns = kWave / cw;
   const int lane = threadIdx.x & 63;
   const int c = lane % cw, slot = lane / cw;
-  const int64_t wave = ((int64_t)blockIdx.x - G->blk0) * (kThreads / kWave) + threadIdx.x / kWave;
+  const int64_t wave = (int64_t)(bid - G->blk0) * (kThreads / kWave) +
+                       __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
   const int64_t nw = (int64_t)G->nblk * (kThreads / kWave);
   // the CSR arrays come from the graph table, so the compiler cannot see that they are
   // global memory: without the address space it would emit flat loads, which also count
@@ -154,57 +226,113 @@ __global__ __launch_bounds__(256) void k_bspmm(const BGraph* __restrict__ graphs
   const int64_t nr = n * r;
   const T* __restrict__ Pg = P + G->off0;
   T* __restrict__ Bg = B + G->off0;
+  if (cw == kWave) {
+    if (wave >= n) return;
+    // pairs lane, lane + 1, ... of a row from pair z on (clamped into the row; the CSR of
+    // a batch has at least one nonzero, which an empty row reads instead)
+    auto pairs = [&](int64_t b, int64_t cnt, int& mc, T& mv) __attribute__((always_inline)) {
+      const int64_t z = cnt > 0 ? b + (lane < cnt ? lane : cnt - 1) : 0;
+      mc = col[z];
+      mv = val[z];
+    };
+    int64_t b = rowptr[wave], e = rowptr[wave + 1];
+    int64_t row1 = wave + nw < n ? wave + nw : wave;
+    int64_t b1 = rowptr[row1], e1 = rowptr[row1 + 1];
+    int mc;
+    T mv;
+    pairs(b, e - b, mc, mv);
+    for (int64_t row = wave; row < n; row += nw) {
+      const int64_t row2 = row + 2 * nw < n ? row + 2 * nw : row;
+      const int64_t b2 = rowptr[row2], e2 = rowptr[row2 + 1];
+      int mc1;
+      T mv1;
+      pairs(b1, e1 - b1, mc1, mv1);
+      auto more = [&](int64_t z0, int& xc, T& xv) { pairs(b + z0, e - b - z0, xc, xv); };
+      auto chunks = [&](auto nc, auto un, int c0) __attribute__((always_inline)) {
+        constexpr int NC = decltype(nc)::value, U = decltype(un)::value;
+        const T* pl[NC];
+        int64_t out[NC];
+        bool cok[NC];
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+          const int cc = c0 + q * kWave + lane;
+          cok[q] = cc < width;
+          const int s = cok[q] ? cc / r : 0, j = cok[q] ? cc - s * r : 0;
+          out[q] = s * nr + j;
+          pl[q] = Pg + out[q];
+        }
+        T acc[NC];
+        wide_row<T, NC, U>(pl, r, e - b, mc, mv, more, acc);
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+          if (cok[q]) Bg[out[q] + row * r] = acc[q];
+      };
+      int c0 = 0;
+      for (; c0 + 2 * kWave < width; c0 += 4 * kWave)
+        chunks(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{}, c0);
+      if (c0 + kWave < width)
+        chunks(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{}, c0);
+      else if (c0 < width)
+        chunks(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{}, c0);
+      b = b1;
+      e = e1;
+      b1 = b2;
+      e1 = e2;
+      mc = mc1;
+      mv = mv1;
+    }
+    return;
+  }
+  // up to 32 columns: the lane groups take every ns-th nonzero each, four in flight
+  const bool cok = c < width;
+  const int s = cok ? c / r : 0, j = c - s * r;
+  const T* __restrict__ Ps = Pg + s * nr + j;
   for (int64_t row = wave; row < n; row += nw) {
     const int64_t b = rowptr[row], e = rowptr[row + 1];
-    for (int c0 = 0; c0 < width; c0 += cw) {
-      const int cc = c0 + c;
-      const bool cok = cc < width;
-      const int s = cok ? cc / r : 0;
-      const int j = cc - s * r;
-      const T* __restrict__ Ps = Pg + s * nr + j;
-      T acc = T(0);
-      for (int64_t zb = b; zb < e; zb += kWave) {
-        const int cnt = e - zb < kWave ? (int)(e - zb) : kWave;
-        const int mc = lane < cnt ? col[zb + lane] : 0;
-        const T mv = lane < cnt ? val[zb + lane] : T(0);
-        for (int k0 = 0; k0 < cnt; k0 += 4 * ns) {  // uniform trip count: all lanes shuffle
-          int ck[4];
-          T vk[4];
+    T acc = T(0);
+    for (int64_t zb = b; zb < e; zb += kWave) {
+      const int cnt = e - zb < kWave ? (int)(e - zb) : kWave;
+      const int mc = lane < cnt ? col[zb + lane] : 0;
+      const T mv = lane < cnt ? val[zb + lane] : T(0);
+      for (int k0 = 0; k0 < cnt; k0 += 4 * ns) {  // uniform trip count: all lanes shuffle
+        int ck[4];
+        T vk[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int k = k0 + slot + u * ns;
-            const int src = k < kWave ? k : kWave - 1;
-            ck[u] = __shfl(mc, src, kWave);
-            vk[u] = __shfl(mv, src, kWave);
-          }
-          T pk[4];
+        for (int u = 0; u < 4; ++u) {
+          const int k = k0 + slot + u * ns;
+          const int src = k < kWave ? k : kWave - 1;
+          ck[u] = __shfl(mc, src, kWave);
+          vk[u] = __shfl(mv, src, kWave);
+        }
+        T pk[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int k = k0 + slot + u * ns;
-            pk[u] = (cok && k < cnt) ? Ps[(int64_t)ck[u] * r] : T(0);
-          }
+        for (int u = 0; u < 4; ++u) {
+          const int k = k0 + slot + u * ns;
+          pk[u] = (cok && k < cnt) ? Ps[(int64_t)ck[u] * r] : T(0);
+        }
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int k = k0 + slot + u * ns;
-            if (k < cnt) acc += vk[u] * pk[u];
-          }
+        for (int u = 0; u < 4; ++u) {
+          const int k = k0 + slot + u * ns;
+          if (k < cnt) acc += vk[u] * pk[u];
         }
       }
-      for (int o = cw; o < kWave; o <<= 1) acc += __shfl_xor(acc, o, kWave);
-      if (slot == 0 && cok) Bg[s * nr + row * r + j] = acc;
     }
+    for (int o = cw; o < kWave; o <<= 1) acc += __shfl_xor(acc, o, kWave);
+    if (slot == 0 && cok) Bg[s * nr + row * r + j] = acc;
   }
 }
 
 template <typename T>
 void launch_bspmm(const BGraph* graphs, const int32_t* sblk_graph, int sblocks,
-                  const State* states, const T* P, T* B, hipStream_t s) {
-  hipLaunchKernelGGL(k_bspmm<T>, dim3(sblocks), dim3(256), 0, s, graphs, sblk_graph, states, P, B);
+                  State* states, const T* P, T* B, hipStream_t s, const BInst* inst, int nrho,
+                  const double* G64) {
+  hipLaunchKernelGGL(k_bspmm<T>, dim3(nrho + sblocks), dim3(256), 0, s, graphs, sblk_graph, states,
+                     P, B, inst, nrho, G64);
 }
-template void launch_bspmm<float>(const BGraph*, const int32_t*, int, const State*, const float*,
-                                  float*, hipStream_t);
-template void launch_bspmm<double>(const BGraph*, const int32_t*, int, const State*,
-                                   const double*, double*, hipStream_t);
+template void launch_bspmm<float>(const BGraph*, const int32_t*, int, State*, const float*, float*,
+                                  hipStream_t, const BInst*, int, const double*);
+template void launch_bspmm<double>(const BGraph*, const int32_t*, int, State*, const double*,
+                                   double*, hipStream_t, const BInst*, int, const double*);
 
 // ----------------------------------------------------------------------------- LAI
 // Partial T_b = U_b^T P_b over a slab of rows, FP64.  ell <= 128, r <= 64.

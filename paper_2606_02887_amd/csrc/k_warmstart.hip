@@ -473,7 +473,7 @@ __global__ __launch_bounds__(kThreads) void k_mlp_fwd(MlpDev m, int64_t N,
     const BInst* d = bm.inst + i;
     off = d->off;
     rows = d->n;
-    bid = (int64_t)blockIdx.x - d->blk0;
+    bid = (int64_t)blockIdx.x + bm.base - d->blk0;
     nb = d->nblk;
     sc = (float)sqrt(sqrt((double)r) * sqrt(d->normA2) / ((double)d->n * r));
   }

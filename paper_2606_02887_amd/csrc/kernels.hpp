@@ -123,7 +123,9 @@ void launch_spmm(const int64_t* rowptr, const int32_t* col, const T* val, const 
 int spmm_dot_grid(int64_t n);
 template <typename T>
 void launch_bspmm(const BGraph* graphs, const int32_t* sblk_graph, int sblocks,
-                  const State* states, const T* P, T* B, hipStream_t s);
+                  State* states, const T* P, T* B, hipStream_t s,
+                  const BInst* inst = nullptr, int nrho = 0,  // rho of instances 0 .. nrho - 1
+                  const double* G64 = nullptr);               // from their Gram;
 void launch_breset(State* states, const BInst* inst, int ninst, hipStream_t s,
                    unsigned* bad = nullptr);  // bad: also set to kCopyOk
 void launch_bout(const State* states, int ninst, BOut* out, hipStream_t s);

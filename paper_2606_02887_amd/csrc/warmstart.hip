@@ -253,12 +253,12 @@ snmf_status snmf_batch_warmstart(snmf_batch* b, int32_t nmodels, const snmf_mlp*
     SNMF_TRY(check_mlp(&models[q], false));
     pick[models[q].r] = &models[q];
   }
-  for (const auto& c : b->cls)
+  for (const auto& c : b->ranks)
     if (!pick[c.r]) return fail(SNMF_E_ARG, "no network for rank " + std::to_string(c.r));
   SNMF_TRY(begin(b, user));
   // the sketch lands in B, the coordinates in C (solve scratch, free between solves)
   SNMF_TRY(frame_async(b, Omega, b->B, b->C, nullptr));
-  for (const auto& c : b->cls) {
+  for (const auto& c : b->ranks) {
     launch_mlp_forward(dev_of(pick[c.r]), 0, (const float*)b->C, nullptr, (float*)W0, b->bmap(c),
                        c.blocks, b->s);
     HIP_TRY(hipGetLastError());

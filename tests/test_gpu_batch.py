@@ -8,6 +8,7 @@ trajectory.
 """
 import numpy as np
 import pytest
+import scipy.sparse as sp
 
 import oracle as O
 from paper_2606_02887_amd import gen
@@ -134,6 +135,59 @@ def test_batch_stacked_apass(S, prec):
             assert nrel(Bi, a_in[g] @ Pi) <= tol, (g, s)
             off += n * r
     assert off == Pn.size
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("r,restarts", [(1, 1), (8, 4), (11, 3), (32, 2), (13, 5), (64, 2), (43, 3),
+                                        (48, 4), (64, 4), (52, 5), (64, 7)])
+def test_batch_stacked_apass_chunks(S, prec, r, restarts):
+    """The stacked SpMM at the edges of its 64-column chunks (width r S = 1 ... 448), on rows
+    without nonzeros, of one to a few tens, and of more than one load of 64 pairs.  A row
+    of k nonnegative terms: |error| <= (k + 1) ulp of the entry."""
+    dt = DT[prec]
+    n = 200
+    rng = np.random.default_rng(r * 8 + restarts)
+    d = np.zeros((n, n))
+    for i in range(2, n):
+        k = rng.integers(0, 18)
+        d[i, rng.integers(2, n, k)] = rng.random(k)
+    d[5, 6:] = rng.random(n - 6)          # 194 nonzeros: three loads of pairs and a remainder
+    d[9, 12:76] = rng.random(64)
+    d = np.maximum(d, d.T).astype(np.float32).astype(np.float64)
+    A = sp.csr_matrix(d)
+    prm = S.params(prec=S.F64 if prec == "f64" else S.F32, max_outer=1)
+    with S.Batch([S.csr_from_scipy(A, dt)], [r], prm, restarts=restarts) as b:
+        P = torch.from_numpy(rng.random(b.elements)).to(DEV, dt)
+        B = torch.empty_like(P)
+        b.apass(P, B)
+    P, B = P.double().cpu().numpy(), B.double().cpu().numpy()
+    ulp = 2.0 ** (-53 if prec == "f64" else -24)
+    k = (np.diff(A.indptr) + 1)[:, None]
+    for q in range(restarts):
+        ref = A @ P[q * n * r:(q + 1) * n * r].reshape(n, r)
+        got = B[q * n * r:(q + 1) * n * r].reshape(n, r)
+        assert (np.abs(got - ref) <= (k + 1) * ulp * ref).all()
+
+
+def test_batch_ranks_share_launches(S):
+    """Ranks of every tile layout in one batch (up to 32 in one launch, above in another):
+    each instance follows its single two-kernel solve (FP64, 1e-9: the sums are grouped
+    differently where a workgroup owns several tiles)."""
+    ranks, ns = [17, 1, 64, 4, 33, 5, 8, 32, 9, 16], [300, 40, 200, 700, 90, 1300, 256, 129, 600, 257]
+    probs = [gen.planted_dense(n, max(r, 2), 50 + n) for n, r in zip(ns, ranks)]
+    As = [S.dense(torch.from_numpy(q["A"]).to(DEV)) for q in probs]
+    rng = np.random.default_rng(4)
+    W0s = [torch.from_numpy(rng.random((2, n, r)) * np.sqrt(q["A"].mean() / r)).to(DEV)
+           for q, n, r in zip(probs, ns, ranks)]
+    prm = dict(lam=0.5, prec=S.F64, max_outer=5)
+    with S.Batch(As, ranks, S.params(**prm), restarts=2) as b:
+        Ws, Hs, infos, _ = b.solve(W0s)
+    for g in range(len(ranks)):
+        for q in range(2):
+            W, Ht, info = S.solve(As[g], W0s[g][q].contiguous(), S.params(fuse_inner=0, **prm))
+            for u, v in ((Ws[g][q], W), (Hs[g][q], Ht)):
+                assert (u - v).abs().max() <= 1e-9 * v.abs().max(), (g, q)
+            assert infos[2 * g + q]["inner_total"] == info["inner_total"], (g, q)
 
 
 def test_batch_per_instance_target_stop(S):
