@@ -9,8 +9,21 @@
 //    wave sums, and the normalisation uses b^(-1) = (b^2)^(-1/2) from the hardware
 //    estimate plus two Newton steps, so a step has no division and no square root.
 //    T = tridiag(b, a, b) has the spectrum of G on the Krylov space; the process stops
-//    early when that space is invariant (b^2 <= (1e-15 ||G||_F)^2).  The bounds
-//    lo = max a_k <= lambda_max(T) (interlacing) and hi (Gershgorin) are kept on the way.
+//    early when that space is invariant (b^2 <= (1e-15 ||G||_F)^2), or when the steps left
+//    cannot move the top eigenvalue any more (below).  The bounds lo = max a_k <=
+//    lambda_max(T) (interlacing) and hi (Gershgorin) are kept on the way.
+//    Stop by dominance: let F = ||G||_F, theta_2 = lambda_max(T_2) <= lambda_1 and
+//    mu = (F^2 - theta_2^2)^(1/2): every other eigenvalue of G is at most mu in magnitude.  The
+//    norm of T without its first row and column is at most nu = (F^2 - a_1^2 - 2 b_1^2)^(1/2)
+//    (||T||_F <= F).  With d = theta_2 - max(mu, nu) > 0 and theta = lambda_max(T_k) >= theta_2,
+//    the last component of theta's unit eigenvector is at most prod_{j<k} b_j / d (each pivot
+//    of theta I - T_{j..k}, j >= 2, is at least d), the residual of the Ritz pair is b_k times
+//    that, and lambda_1 - theta <= residual^2 / d.  The process ends when
+//    prod_{j<=k} (b_j / d)^2 <= 2^-60, an error below 2^-60 lambda_1; used for
+//    d >= theta_2 / 16, far above the rounding of F^2 - theta_2^2.  The Gram of a factor whose
+//    columns all correlate stops after 4 to 10 steps (r = 64: 8.7, r = 21: 7.3 us), that
+//    of a near-indicator factor, with many large eigenvalues, runs all r steps (r = 64: 56,
+//    r = 21: 21 us).
 // 2. Multisection on T: each round places 256 shifts x evenly in [lo, hi], one per
 //    thread, and keeps the subinterval where x I - T turns positive definite.  The test
 //    runs the leading principal minors s_k = det(x I - T_k),
@@ -76,7 +89,8 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
     sz[0][i][wv] = gn2;
     __syncthreads();
     const double4 g4 = *(const double4*)&sz[0][i][0];
-    const double tol2 = 1e-30 * wave_sum((g4.x + g4.y) + (g4.z + g4.w));
+    const double fro2 = wave_sum((g4.x + g4.y) + (g4.z + g4.w));
+    const double tol2 = 1e-30 * fro2;
     __syncthreads();
     // G v is formed on the unnormalised vector v and scaled by 1/||v|| afterwards, so the
     // reciprocal square root of a step overlaps the broadcast and product of the next.
@@ -87,6 +101,7 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
     double q = v * rb, qprev = 0.0, bprev = 0.0;
     double lo = -1e300, hi = -1e300;  // max a_k and the Gershgorin bound, uniform
     double myA = 0.0, myB2 = 0.0;     // lane j keeps a_j and b_j^2
+    double a1 = 0.0, invd2 = 0.0, prod = 1.0;  // 1 / d^2 (0: no dominance), prod (b_j / d)^2
     int m = 0;
     sv[wv][i] = v;
     __builtin_amdgcn_wave_barrier();
@@ -112,7 +127,19 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
       const double ww = wave_sum(w * w);
       m = j + 1;
       // b_j couples rows j and j + 1 of T; it is 0 when the process stops here
-      const bool more = ww > tol2 && j + 1 < r;  // false for NaN as well
+      prod *= ww;
+      if (j == 0) a1 = a;
+      if (j == 1) {  // bprev = b_1
+        const double hd = 0.5 * (a1 - a);
+        const double th = 0.5 * (a1 + a) + sqrt(__builtin_fma(hd, hd, bprev * bprev));
+        const double mu2 = fro2 - th * th, nu2 = fro2 - a1 * a1 - 2.0 * bprev * bprev;
+        const double d = th - sqrt(fmax(fmax(mu2, nu2), 0.0));
+        invd2 = d > 0.0 && d >= 0.0625 * th ? 1.0 / (d * d) : 0.0;
+        prod *= invd2;  // of b_1
+      }
+      prod = j > 0 ? prod * invd2 : prod;
+      const bool more = ww > tol2 && j + 1 < r &&
+                        !(invd2 > 0.0 && prod <= 0x1p-60);  // false for NaN as well
       if (more) {
         __builtin_amdgcn_wave_barrier();  // this wave has read the old vector
         sv[wv][i] = w;

@@ -56,6 +56,25 @@ def test_rho_near_degenerate_spectrum(S):
     assert abs(got - ref) <= 1e-13 * ref
 
 
+@pytest.mark.parametrize("r", [2, 3, 21, 64])
+@pytest.mark.parametrize("ratio", [0.0, 1e-8, 0.03, 0.5, 0.9, 0.999])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_rho_one_dominant_eigenvalue(S, r, ratio, mixed):
+    """The stop of the Lanczos process by dominance: lambda_1 = 1 (a positive eigenvector away
+    from the all-ones start), one further eigenvalue `ratio`, the others ratio / 100 (mixed:
+    spread between 0 and ratio), over and below where the stop is used."""
+    rng = np.random.default_rng(r)
+    v = 0.2 + rng.random(r)
+    q, _ = np.linalg.qr(np.column_stack([v, rng.standard_normal((r, r - 1))]))
+    lam = np.concatenate([[1.0, ratio], rng.random(r - 2) * ratio if mixed
+                          else np.full(r - 2, ratio / 100)])
+    G = 7.3e4 * (q * lam) @ q.T
+    G = 0.5 * (G + G.T)
+    got = S.rho(_t(G, torch.float64))
+    ref = np.linalg.eigvalsh(G)[-1]
+    assert abs(got - ref) <= 1e-13 * ref
+
+
 # ------------------------------------------------------------------ Gram and A-pass
 # (132, 34) and (260, 64): FP32 workgroup chunks longer than a tile's K (one workgroup
 # spans several tiles); (2048, 64), (4100, 34), (4608, 64): chunks that end inside tiles
