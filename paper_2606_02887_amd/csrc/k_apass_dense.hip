@@ -172,12 +172,13 @@ __global__ __launch_bounds__(256) void k_apass_f64(const double* __restrict__ A,
 }
 
 // ----------------------------------------------------------------------------- FP32 MFMA
+// Panels of B = A^T P, A K x N row-major, P K x r (a symmetric A: K = N = n).
 // Grid: x = blocks of 256 output rows (4 waves x 64), y = K splits of kchunk rows of A.
 // Wave w handles output rows j0..j0+63 (two MFMA N-blocks of 32) and all r <= 64
 // columns (one or two MFMA M-blocks).  Per k-pair a lane loads A[k+h][j0+c] and
 // A[k+h][j0+32+c] (h = lane/32, c = lane%32) and P[k+h][c], P[k+h][32+c]: any lda and n.
 // Bound by the latency of its loads (n = 3001: a wave's share is 80 rows), so kDepth
-// batches of kBatch k-pairs are in flight; lanes past n or r read a clamped address (their
+// batches of kBatch k-pairs are in flight; lanes past N or r read a clamped address (their
 // columns and ranks are never stored), which keeps the loads unconditional.  With rj.G
 // set, row 0 of the grid computes rho = ||G||_2 (rho.hpp) beside the tiles, first in
 // dispatch order because it is as long as they are.  n = 3001, r = 21: 16.8 us, 21.9 with rho;
@@ -185,7 +186,8 @@ __global__ __launch_bounds__(256) void k_apass_f64(const double* __restrict__ A,
 // its own.
 template <int NMB>
 __global__ __launch_bounds__(256) void k_apass_f32(const float* __restrict__ A, int64_t lda,
-                                                   const float* __restrict__ P, int64_t n, int r,
+                                                   const float* __restrict__ P, int64_t K, int64_t N,
+                                                   int r,
                                                    int64_t kchunk, float* __restrict__ Bpart,
                                                    int64_t pstride, const State* __restrict__ st,
                                                    RhoJob rj) {
@@ -198,10 +200,10 @@ __global__ __launch_bounds__(256) void k_apass_f32(const float* __restrict__ A, 
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int c = lane & 31, h = lane >> 5;
   const int64_t j0 = ((int64_t)blockIdx.x * 4 + wave) * 64;
-  if (j0 >= n) return;
+  if (j0 >= N) return;
   const int64_t part = (int64_t)blockIdx.y - (rj.G ? 1 : 0);
   const int64_t kb = part * kchunk;
-  const int64_t ke = kb + kchunk < n ? kb + kchunk : n;
+  const int64_t ke = kb + kchunk < K ? kb + kchunk : K;
   f32x16 acc[NMB][2];
 #pragma unroll
   for (int mb = 0; mb < NMB; ++mb)
@@ -209,15 +211,15 @@ __global__ __launch_bounds__(256) void k_apass_f32(const float* __restrict__ A, 
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.0f;
-  const bool jok0 = j0 + c < n, jok1 = j0 + 32 + c < n;
+  const bool jok0 = j0 + c < N, jok1 = j0 + 32 + c < N;
   const bool mok0 = c < r, mok1 = 32 + c < r;
   const float* arow = A + j0 + c;
   constexpr int kBatch = 8, kDepth = NMB > 1 ? 2 : 4;
   struct Batch {
     float a0[kBatch], a1[kBatch], p0[kBatch], p1[kBatch];
   } q[kDepth];
-  const float* ac0 = A + (jok0 ? j0 + c : n - 1);
-  const float* ac1 = A + (jok1 ? j0 + 32 + c : n - 1);
+  const float* ac0 = A + (jok0 ? j0 + c : N - 1);
+  const float* ac1 = A + (jok1 ? j0 + 32 + c : N - 1);
   const float* pc0 = P + (mok0 ? c : 0);
   const float* pc1 = P + (mok1 ? 32 + c : 0);
   auto load = [&](Batch& x, int64_t k0) __attribute__((always_inline)) {
@@ -296,7 +298,7 @@ __global__ __launch_bounds__(256) void k_apass_f32(const float* __restrict__ A, 
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
       const int64_t j = j0 + 32 * nb + c;
-      if (j < n) {
+      if (j < N) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int m = 32 * mb + 8 * (v >> 2) + 4 * h + (v & 3);
@@ -815,6 +817,18 @@ DenseSplit plan_dense_f32(int64_t n, int64_t lda, int r, const void* A) {
   return d;
 }
 
+void launch_apass_f32_panels(const float* A, int64_t lda, const float* P, int64_t K, int64_t N,
+                             int r, int64_t kchunk, dim3 grid, float* Bpart, int64_t pstride,
+                             const State* st, hipStream_t s, const RhoJob& rj) {
+  if (rj.G) ++grid.y;
+  if (r > 32)
+    hipLaunchKernelGGL(k_apass_f32<2>, grid, dim3(256), 0, s, A, lda, P, K, N, r, kchunk, Bpart,
+                       pstride, st, rj);
+  else
+    hipLaunchKernelGGL(k_apass_f32<1>, grid, dim3(256), 0, s, A, lda, P, K, N, r, kchunk, Bpart,
+                       pstride, st, rj);
+}
+
 void launch_apass_f32(const float* A, int64_t lda, const float* P, int64_t n, int r,
                       const DenseSplit& d, float* Bpart, int64_t pstride, const State* st,
                       hipStream_t s, const RhoJob& rj) {
@@ -833,13 +847,7 @@ void launch_apass_f32(const float* A, int64_t lda, const float* P, int64_t n, in
                        d.kchunk, d.nband, d.rchunk, d.ksplit, Bpart, pstride, st, rj, rho_wg);
     return;
   }
-  if (rj.G) ++grid.y;
-  if (r > 32)
-    hipLaunchKernelGGL(k_apass_f32<2>, grid, dim3(256), 0, s, A, lda, P, n, r, d.kchunk, Bpart,
-                       pstride, st, rj);
-  else
-    hipLaunchKernelGGL(k_apass_f32<1>, grid, dim3(256), 0, s, A, lda, P, n, r, d.kchunk, Bpart,
-                       pstride, st, rj);
+  launch_apass_f32_panels(A, lda, P, n, n, r, d.kchunk, grid, Bpart, pstride, st, s, rj);
 }
 
 DenseSplit plan_dense_bf16(int64_t n) {

@@ -178,117 +178,173 @@ __global__ __launch_bounds__(kThreads) void k_csr_sort_pairs(const int64_t* __re
 // ----------------------------------------------------------------------------- FP32 MFMA
 typedef float f32x16n __attribute__((ext_vector_type(16)));
 
-// Split-K product panel y of B = A^T P: Bpart[y][j][m] = sum over k in chunk y of
-// A[k][j] P[k][m], A K x N row-major (leading dimension lda), P K x r, on
-// v_mfma_f32_32x32x2f32.  Grid x: blocks of 256 output rows (4 waves x 64), y: K chunks of
-// kchunk rows (kchunk even).  Wave w takes output rows j0 .. j0 + 63 (two MFMA N-blocks)
-// and all r <= 64 columns (NMB M-blocks of 32); per k-pair lane (c, h) = (lane % 32,
-// lane / 32) loads A[k + h][j0 + c], A[k + h][j0 + 32 + c] and P[k + h][c], P[k + h][32 + c],
-// eight k-pairs per batch with the next batch in flight during this one's MFMAs.  With
-// A = V (m x n) the panel sums give V^T P (the H-step), with A = V^T (an n x m transposed
-// copy) V P (the W-step).  With rj.G set the grid has one more row of workgroups, the
-// first (dispatched before the panels, so that it runs beside them from the start), whose
-// first workgroup computes rho = ||G||_2 (rho.hpp).  Skipped when the solve is done.
-template <int NMB>
-__global__ __launch_bounds__(256) void k_rect_f32(const float* __restrict__ A, int64_t lda,
-                                                  const float* __restrict__ P, int64_t K,
-                                                  int64_t N, int r, int64_t kchunk,
-                                                  float* __restrict__ Bpart, int64_t pstride,
-                                                  const State* __restrict__ st, RhoJob rj) {
+// Split-K panels of V^T P (the H-step) and V P (the W-step): panel y of the N x r product
+// holds the sums over k in chunk y (kchunk rows of P, a multiple of 16), every sum in
+// increasing k on v_mfma_f32_32x32x2f32.  The general path is that of the symmetric A-pass
+// (k_apass_dense.hip), with a transposed copy of V for the W-step; for r in (32, 64] and
+// aligned V these wide kernels serve both from V itself.  A wave computes 128 output rows and
+// all ranks (rank m = 2 c + b in M-block b: P is loaded two ranks at a time), so a k-pair
+// feeds 8 MFMAs from one 16-byte load of V (the general kernel: 4 from two 4-byte loads);
+// 16 k (ROWS: 8) per batch, the next batch in flight during this one's 64 (32) MFMAs, one
+// load among every few MFMAs.  Two wavefronts' registers fit a SIMD, so that the workgroup of rho finds a place
+// beside a tile workgroup (with 288 registers the last tile waited for it: 106 us).
+// ROWS = false (V^T P): lane (c, h) = (lane % 32, lane / 32) loads V[k + h][j0 + 4c .. +3],
+// column block q = rows j0 + 4c + q of the product.
+// ROWS = true (V P): lane c reads 8 consecutive k of row j0 + 32 q + c of V, both halves of
+// the wave the same 32 bytes; half h takes the k of its parity.
+// With rj.G set the grid has one more row of workgroups, the first, whose first workgroup
+// computes rho = ||G||_2 (rho.hpp).  Skipped when the solve is done.
+// V 8192 x 4096, r = 64: V^T P 47, V P 59 us (FP32 matrix rate 28, V from memory 27, the
+// panels' stores 7 and more), up to 88 beside a rho of all r steps (56 alone); the general
+// kernel took 74 and 97 us, the transposed copy 58 us and 134 MB per call.
+typedef float f32x4n __attribute__((ext_vector_type(4)));
+
+template <bool ROWS>
+__global__ __launch_bounds__(256, 2) void k_rect_f32w(const float* __restrict__ V, int64_t ld,
+                                                      const float* __restrict__ P, int64_t K,
+                                                      int64_t N, int r, int64_t kchunk,
+                                                      float* __restrict__ Bpart, int64_t pstride,
+                                                      const State* __restrict__ st, RhoJob rj) {
   if (st->done) return;
   int64_t y = blockIdx.y;
   if (rj.G) {
     if (y == 0) {
-      if (blockIdx.x == 0) rho_body(rj.G, rj.r, rj.st);  // (issue priority: no gain measured)
+      if (blockIdx.x == 0) rho_body(rj.G, rj.r, rj.st);
       return;
     }
     --y;
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 31, h = lane >> 5;
-  const int64_t j0 = ((int64_t)blockIdx.x * 4 + wave) * 64;
+  const int64_t j0 = ((int64_t)blockIdx.x * 4 + wave) * 128;
+  if (j0 >= N) return;
   const int64_t kb = y * kchunk;
   const int64_t ke = kb + kchunk < K ? kb + kchunk : K;
-  f32x16n acc[NMB][2];
+  f32x16n acc[2][4];
 #pragma unroll
-  for (int mb = 0; mb < NMB; ++mb)
+  for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
+    for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.0f;
-  const bool jok0 = j0 + c < N, jok1 = j0 + 32 + c < N;
-  const bool mok0 = c < r, mok1 = 32 + c < r;
-  const float* arow = A + j0 + c;
-  constexpr int U = 8;
-  float a0[U], a1[U], p0[U], p1[U];
-  float b0[U], b1[U], q0[U], q1[U];
-  auto load = [&](float (&x0)[U], float (&x1)[U], float (&y0)[U], float (&y1)[U], int64_t kk0) {
+  // rows and ranks out of range read a clamped, valid address; they are never stored
+  const float* prow = P + (2 * c + 1 < r ? 2 * c : 0);
+  const float* vrow[ROWS ? 4 : 1];
+  if constexpr (ROWS) {
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+      const int64_t j = j0 + 32 * nb + c;
+      vrow[nb] = V + (j < N ? j : N - 1) * ld;
+    }
+  } else {
+    vrow[0] = V + (j0 + 4 * c + 3 < N ? j0 + 4 * c : N - 4);  // N % 4 == 0 here
+  }
+  constexpr int U = ROWS ? 4 : 8;  // k-pairs per batch
+  struct Batch {
+    f32x4n x[ROWS ? 2 * U : U];
+    float2 p[U];
+  } qa, qb;
+  auto load = [&](Batch& q, int64_t k0) __attribute__((always_inline)) {
+    if constexpr (ROWS) {
+#pragma unroll
+      for (int t = 0; t < U / 2; ++t)
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) q.x[4 * t + nb] = *(const f32x4n*)(vrow[nb] + k0 + 4 * t);
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t kk = kk0 + 2 * u + h;
-      x0[u] = jok0 ? __builtin_nontemporal_load(arow + kk * lda) : 0.0f;
-      x1[u] = jok1 ? __builtin_nontemporal_load(arow + kk * lda + 32) : 0.0f;
-      y0[u] = mok0 ? P[kk * r + c] : 0.0f;
-      if (NMB > 1) y1[u] = mok1 ? P[kk * r + 32 + c] : 0.0f;
+      const int64_t kk = k0 + 2 * u + h;
+      if constexpr (!ROWS) q.x[u] = __builtin_nontemporal_load((const f32x4n*)(vrow[0] + kk * ld));
+      q.p[u] = *(const float2*)(prow + kk * r);
     }
   };
-  auto mma = [&](const float (&x0)[U], const float (&x1)[U], const float (&y0)[U],
-                 const float (&y1)[U]) {
+  auto mma = [&](const Batch& q) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0[u], x0[u], acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0[u], x1[u], acc[0][1], 0, 0, 0);
-      if (NMB > 1) {
-        acc[NMB - 1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1[u], x0[u], acc[NMB - 1][0], 0, 0, 0);
-        acc[NMB - 1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1[u], x1[u], acc[NMB - 1][1], 0, 0, 0);
+      const float pv[2] = {q.p[u].x, q.p[u].y};
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb) {
+        float a;
+        if constexpr (ROWS) {
+          const f32x4n x = q.x[4 * (u >> 1) + nb];
+          a = h ? x[2 * (u & 1) + 1] : x[2 * (u & 1)];
+        } else {
+          a = q.x[u][nb];
+        }
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+          acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(pv[mb], a, acc[mb][nb], 0, 0, 0);
       }
     }
   };
-  int64_t k = kb;
-  if (k + 2 * U <= ke) load(a0, a1, p0, p1, k);
-  while (k + 2 * U <= ke) {
-    if (k + 4 * U <= ke) {
-      load(b0, b1, q0, q1, k + 2 * U);
-      mma(a0, a1, p0, p1);
-      k += 2 * U;
-      if (k + 4 * U <= ke) load(a0, a1, p0, p1, k + 2 * U);
-      mma(b0, b1, q0, q1);
-      k += 2 * U;
-    } else {
-      mma(a0, a1, p0, p1);
-      k += 2 * U;
+  const int64_t nbat = ke > kb ? (ke - kb) / (2 * U) : 0;
+  const int64_t klast = kb + (nbat > 0 ? nbat - 1 : 0) * 2 * U;
+  int64_t k = kb, b = 0;
+  if (nbat > 0) load(qa, k);
+  for (; b + 2 <= nbat; b += 2) {
+    // a prefetch past the last batch reads the last one again: no load is conditional
+    load(qb, k + 2 * U);
+    mma(qa);
+    load(qa, k + 4 * U < klast ? k + 4 * U : klast);
+    mma(qb);
+    k += 4 * U;
+#pragma unroll
+    for (int i = 0; i < 2 * U; ++i) {
+      if constexpr (ROWS) {
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // a load, MFMAs
+        __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+      } else {
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+      }
     }
   }
-  for (; k < ke; k += 2) {
+  if (b < nbat) {
+    mma(qa);
+    k += 2 * U;
+  }
+  for (; k < ke; k += 2) {  // the end of K
     const int64_t kk = k + h;
     const bool kin = kk < ke;
-    const float x0 = (kin && jok0) ? arow[kk * lda] : 0.0f;
-    const float x1 = (kin && jok1) ? arow[kk * lda + 32] : 0.0f;
-    const float y0 = (kin && mok0) ? P[kk * r + c] : 0.0f;
-    const float y1 = (NMB > 1 && kin && mok1) ? P[kk * r + 32 + c] : 0.0f;
-    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0, x0, acc[0][0], 0, 0, 0);
-    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0, x1, acc[0][1], 0, 0, 0);
-    if (NMB > 1) {
-      acc[NMB - 1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1, x0, acc[NMB - 1][0], 0, 0, 0);
-      acc[NMB - 1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1, x1, acc[NMB - 1][1], 0, 0, 0);
+    const int64_t kc = kin ? kk : ke - 1;
+    float2 p = *(const float2*)(prow + kc * r);
+    f32x4n x;
+    if constexpr (ROWS) {
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb) x[nb] = vrow[nb][kc];
+    } else {
+      x = *(const f32x4n*)(vrow[0] + kc * ld);
+    }
+    const float pv[2] = {kin ? p.x : 0.0f, kin ? p.y : 0.0f};
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+      const float a = kin ? x[nb] : 0.0f;
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb)
+        acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(pv[mb], a, acc[mb][nb], 0, 0, 0);
     }
   }
-  // D[m][j] of block (mb, nb): lane (c, h) holds j = j0 + 32 nb + c and
-  // m = 32 mb + 8 (v / 4) + 4 h + v % 4 in register v
+  // D[row][column]: lane (c, h) holds column c and row 8 (v / 4) + 4 h + v % 4 of a block in
+  // register v; rows v, v + 1 of both M-blocks are four consecutive ranks
   float* out = Bpart + y * pstride;
 #pragma unroll
-  for (int mb = 0; mb < NMB; ++mb)
+  for (int nb = 0; nb < 4; ++nb) {
+    const int64_t j = ROWS ? j0 + 32 * nb + c : j0 + 4 * c + nb;
+    if (j >= N) continue;
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      const int64_t j = j0 + 32 * nb + c;
-      if (j < N) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int m = 32 * mb + 8 * (v >> 2) + 4 * h + (v & 3);
-          if (m < r) out[j * r + m] = acc[mb][nb][v];
-        }
-      }
+    for (int v = 0; v < 16; v += 2) {
+      const int m = 2 * (8 * (v >> 2) + 4 * h + (v & 3));
+      const float o[4] = {acc[0][nb][v], acc[1][nb][v], acc[0][nb][v + 1], acc[1][nb][v + 1]};
+      if (m + 3 < r) __builtin_memcpy(out + j * r + m, o, 16);
+      else if (m + 1 < r) __builtin_memcpy(out + j * r + m, o, 8);
     }
+  }
 }
 
 // AT (cols x rows) = A^T for A rows x cols (leading dimension lda): 64 x 64 tiles through
@@ -357,16 +413,25 @@ RectSplit rect_split(int64_t K, int64_t N) {
   return sp;
 }
 
-void launch_rect_f32(const float* A, int64_t lda, const float* P, int64_t K, int64_t N, int r,
-                     const RectSplit& sp, float* Bpart, const State* st, hipStream_t s,
-                     const RhoJob& rj) {
-  const dim3 grid((unsigned)sp.gx, (unsigned)(sp.ksplit + (rj.G ? 1 : 0)));
-  if (r > 32)
-    hipLaunchKernelGGL(k_rect_f32<2>, grid, dim3(256), 0, s, A, lda, P, K, N, r, sp.kchunk,
-                       Bpart, N * r, st, rj);
-  else
-    hipLaunchKernelGGL(k_rect_f32<1>, grid, dim3(256), 0, s, A, lda, P, K, N, r, sp.kchunk,
-                       Bpart, N * r, st, rj);
+bool rect_f32_wide(const void* V, int64_t ld, int64_t rows, int64_t cols, int r) {
+  return r > 32 && r % 2 == 0 && cols % 4 == 0 && ld % 4 == 0 && ((uintptr_t)V & 15) == 0;
+}
+
+void launch_rect_f32(const float* V, int64_t ld, const float* VT, int trans, const float* P,
+                     int64_t K, int64_t N, int r, const RectSplit& sp, float* Bpart,
+                     const State* st, hipStream_t s, const RhoJob& rj) {
+  if (rect_f32_wide(V, ld, trans ? K : N, trans ? N : K, r)) {
+    const dim3 grid((unsigned)((N + 511) / 512), (unsigned)(sp.ksplit + (rj.G ? 1 : 0)));
+    if (trans)
+      hipLaunchKernelGGL(k_rect_f32w<false>, grid, dim3(256), 0, s, V, ld, P, K, N, r, sp.kchunk,
+                         Bpart, N * r, st, rj);
+    else
+      hipLaunchKernelGGL(k_rect_f32w<true>, grid, dim3(256), 0, s, V, ld, P, K, N, r, sp.kchunk,
+                         Bpart, N * r, st, rj);
+    return;
+  }
+  launch_apass_f32_panels(trans ? V : VT, trans ? ld : N, P, K, N, r, sp.kchunk,
+                          dim3((unsigned)sp.gx, (unsigned)sp.ksplit), Bpart, N * r, st, s, rj);
 }
 
 template <typename T>

@@ -241,9 +241,17 @@ struct RectSplit {
   int64_t kchunk = 0;
 };
 RectSplit rect_split(int64_t K, int64_t N);
-void launch_rect_f32(const float* A, int64_t lda, const float* P, int64_t K, int64_t N, int r,
-                     const RectSplit& sp, float* Bpart, const State* st, hipStream_t s,
-                     const RhoJob& rj = RhoJob{});
+// V (rows x cols, row-major): trans: V^T P from V itself; else V P, from V itself (rows) or
+// from its transposed copy VT (VT != nullptr).
+void launch_rect_f32(const float* V, int64_t ld, const float* VT, int trans, const float* P,
+                     int64_t K, int64_t N, int r, const RectSplit& sp, float* Bpart,
+                     const State* st, hipStream_t s, const RhoJob& rj);
+// True when V P and V^T P both run the wide kernels (no transposed copy).
+bool rect_f32_wide(const void* V, int64_t ld, int64_t rows, int64_t cols, int r);
+// The general FP32 panels of A^T P (k_apass_dense.hip), grid = (blocks of 256 columns, panels).
+void launch_apass_f32_panels(const float* A, int64_t lda, const float* P, int64_t K, int64_t N,
+                             int r, int64_t kchunk, dim3 grid, float* Bpart, int64_t pstride,
+                             const State* st, hipStream_t s, const RhoJob& rj);
 template <typename T>
 void launch_transpose(const T* A, int64_t rows, int64_t cols, int64_t lda, T* AT, hipStream_t s);
 void launch_csr_check_rect(const int64_t* rowptr, const int32_t* col, int64_t m, int64_t ncols,

@@ -85,11 +85,11 @@ void half_step(NmfPlan& pl, T* X, int64_t nX, const T* P, int64_t nP, int is_hst
   T* B = (T*)pl.B;
   int ksplit = 1;
   if (pl.V.fmt == SNMF_DENSE && sizeof(T) == 4) {
-    // FP32 MFMA: the H-step's V^T W reads V, the W-step's V Ht its transposed copy
+    // FP32 MFMA: both products read V where the wide kernels take it, else the W-step its
+    // transposed copy
     const RectSplit& sp = is_hstep ? pl.spH : pl.spW;
-    const float* A = is_hstep ? (const float*)pl.V.dense : (const float*)pl.VT;
-    const int64_t lda = is_hstep ? pl.V.ld : pl.m;
-    launch_rect_f32(A, lda, (const float*)P, nP, nX, r, sp, (float*)pl.Bpart, pl.st, s, rj);
+    launch_rect_f32((const float*)pl.V.dense, pl.V.ld, (const float*)pl.VT, is_hstep,
+                    (const float*)P, nP, nX, r, sp, (float*)pl.Bpart, pl.st, s, rj);
     B = (T*)pl.Bpart;
     ksplit = sp.ksplit;
   } else if (pl.V.fmt == SNMF_DENSE) {
@@ -279,7 +279,7 @@ snmf_status nmf_solve(const snmf_matrix* V, int64_t ncols, int32_t r, const void
       return fail(SNMF_E_SHAPE, "V: FP32 dense NMF takes m, n_cols <= 4194240");
     pl.spW = rect_split(ncols, m);  // W-step: K = n_cols, output rows m
     pl.spH = rect_split(m, ncols);  // H-step: K = m, output rows n_cols
-    add(&pl.VT, (size_t)m * ncols * 4);
+    if (!rect_f32_wide(V->dense, V->ld, m, ncols, r)) add(&pl.VT, (size_t)m * ncols * 4);
     add(&pl.Bpart, (size_t)std::max<int64_t>(pl.spW.ksplit * m, pl.spH.ksplit * ncols) * r * 4);
   }
   if (V->fmt == SNMF_CSR) {

@@ -126,3 +126,27 @@ def test_nmf_error_codes(S):
     assert code(M, 20, W0, H0[:20].contiguous(), lam=0.0) == "E_SHAPE"   # columns >= n_cols
     lr = S.lowrank(W0, torch.ones(4, dtype=torch.float64, device=DEV))
     assert code(lr, 30, W0, H0, lam=0.0) == "E_UNSUPPORTED"
+
+
+@pytest.mark.parametrize("m,n,r", [(64, 64, 64), (100, 516, 34), (129, 260, 36), (513, 132, 62),
+                                   (700, 1028, 64), (1300, 508, 48), (2048, 2052, 34),
+                                   (515, 640, 40), (4099, 1600, 64)])
+@pytest.mark.parametrize("pad", [0, 8])
+def test_nmf_wide_products_same_bits(S, m, n, r, pad):
+    """r in (32, 64], even, on aligned V: both products read V through the wide kernels, each
+    sum over the same panels in the same order as the general path, which a leading
+    dimension not divisible by 4 selects: the factors are bitwise equal.  Edges: rows not
+    divisible by the 128 of a wavefront, last panels of fewer than 16 k, pitched V (its
+    padding NaN)."""
+    prob = gen.planted_rect(m, n, r, 3 * m + n)
+    out = []
+    for ld in (n + pad, n + pad + 1):
+        buf = torch.full((m, ld), float("nan"), dtype=torch.float32, device=DEV)
+        buf[:, :n] = torch.from_numpy(prob["V"]).to(DEV)
+        W, Ht, info = S.nmf_solve(S.dense(buf[:, :n]), n,
+                                  torch.from_numpy(prob["W0"]).to(DEV, torch.float32),
+                                  torch.from_numpy(prob["Ht0"]).to(DEV, torch.float32),
+                                  S.params(prec=S.F32, lam=0.0, max_outer=2))
+        assert info["status"] == 0
+        out.append((W, Ht))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
