@@ -348,7 +348,7 @@ __global__ __launch_bounds__(256, 2) void k_apass_f32w(const float* __restrict__
     rho_body(rj.G, rj.r, rj.st);
     return;
   }
-  __shared__ float sacc[2 * 8 * 16 * 64];  // [slot][block(mb,nb)][v][lane], 64 KB
+  __shared__ float sacc[4 * 4 * 16 * 64];  // [wave][nb][v][lane], 64 KB
   // the wave index is uniform: K ranges, batch counts and loop control stay scalar
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 31, h = lane >> 5;
@@ -406,7 +406,7 @@ __global__ __launch_bounds__(256, 2) void k_apass_f32w(const float* __restrict__
     // column or rank that is never stored.
     const float* arow = A + (jok ? jc : n - 4);
     const float* prow = P + (mok ? 2 * c : 0);
-    constexpr int U = 6;  // k-pairs per batch of loads (2: 91.3 us, 4: 90.7, 6: 89.0; 8 spills)
+    constexpr int U = 6;  // k-pairs per batch of loads (2: 2.3, 4: 1.7 us slower; 8 spills)
     f32x4v xa[U], xb[U];
     float2 ya[U], yb[U];
     const f32x4v z4 = {0.f, 0.f, 0.f, 0.f};
@@ -481,50 +481,49 @@ __global__ __launch_bounds__(256, 2) void k_apass_f32w(const float* __restrict__
         }
       }
     }
-    // the four K-quarter tiles, added pairwise in a fixed order in 64 KB of LDS:
-    // (w0 + w1) + (w2 + w3), the total in slot 0
-    auto put = [&](int sl) {
+    // the four K-quarter tiles, added pairwise in a fixed order, (w0 + w1) + (w2 + w3): for
+    // each M-block every wave parks its four column blocks in LDS (64 KB) and adds up one,
+    // so that it ends with both M-blocks of the rows j0 + 4c + wave and stores them from
+    // registers (n = 8192, r = 64: 80 us; 91 with wave 0 adding up and the total read back
+    // from LDS row by row, 32 lanes to a bank, twice in the chunks that span two tiles).
+    f32x16 tot[2];
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+    for (int mb = 0; mb < 2; ++mb) {
+      __syncthreads();  // the LDS of the block (or range) before is read
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
+      for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) sacc[((sl * 8 + mb * 4 + nb) * 16 + v) * 64 + lane] = acc[mb][nb][v];
-    };
-    auto add = [&](int sl) {
+        for (int v = 0; v < 16; ++v)
+          sacc[((wave * 4 + nb) * 16 + v) * 64 + lane] = acc[mb][nb][v];
+      __syncthreads();
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) acc[mb][nb][v] += sacc[((sl * 8 + mb * 4 + nb) * 16 + v) * 64 + lane];
-    };
-    if (wave & 1) put(wave >> 1);
-    __syncthreads();
-    if (!(wave & 1)) add(wave >> 1);
-    __syncthreads();
-    if (wave == 2) put(0);
-    __syncthreads();
-    if (wave == 0) {
-      add(0);
-      put(0);
-    }
-    __syncthreads();
-    // element (jl, m) of the 128 x r tile: jl = 4c + nb, m = 2 mrow + mb with
-    // mrow = 8 (v/4) + 4 h + v%4
-    float* out = Bpart + (int64_t)slot * pstride;
-    for (int e = threadIdx.x; e < 128 * 64; e += 256) {
-      const int jl = e >> 6, m = e & 63;
-      const int64_t jj = j0 + jl;
-      if (m < r && jj < n) {
-        const int cc = jl >> 2, nb = jl & 3, mb = m & 1, mrow = m >> 1;
-        const int hh = (mrow >> 2) & 1, v = 4 * (mrow >> 3) + (mrow & 3);
-        const int idx = ((mb * 4 + nb) * 16 + v) * 64 + 32 * hh + cc;
-        out[jj * r + m] = sacc[idx];
-        for (int z = slot + 1; z < zend; ++z) Bpart[(int64_t)z * pstride + jj * r + m] = 0.0f;
+      for (int v = 0; v < 16; ++v) {
+        const float* p = sacc + (wave * 16 + v) * 64 + lane;
+        tot[mb][v] = (p[0] + p[4 * 16 * 64]) + (p[2 * 4 * 16 * 64] + p[3 * 4 * 16 * 64]);
       }
     }
-    __syncthreads();  // sacc is reused by the next range
+    // rank m = 2 mrow + mb, mrow = 8 (v/4) + 4 h + v%4: registers v, v + 1 of both M-blocks
+    // are four consecutive ranks
+    const int64_t jj = j0 + 4 * c + wave;
+    if (jj < n) {
+      float* out = Bpart + (int64_t)slot * pstride + jj * r;
+#pragma unroll
+      for (int v = 0; v < 16; v += 2) {
+        const int m = 2 * (8 * (v >> 2) + 4 * h + (v & 3));
+        const float o[4] = {tot[0][v], tot[1][v], tot[0][v + 1], tot[1][v + 1]};
+        if (m + 3 < r) __builtin_memcpy(out + m, o, 16);
+        else if (m + 1 < r) __builtin_memcpy(out + m, o, 8);
+      }
+      for (int z = slot + 1; z < zend; ++z)
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) {
+          const int m = 2 * (8 * (v >> 2) + 4 * h + (v & 3));
+          const float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+          float* oz = Bpart + (int64_t)z * pstride + jj * r;
+          if (m + 3 < r) __builtin_memcpy(oz + m, o, 16);
+          else if (m + 1 < r) __builtin_memcpy(oz + m, o, 8);
+        }
+    }
   }
 }
 
