@@ -100,7 +100,9 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
     double rb = 1.0 / sqrt((double)r);
     double q = v * rb, qprev = 0.0, bprev = 0.0;
     double lo = -1e300, hi = -1e300;  // max a_k and the Gershgorin bound, uniform
-    double myA = 0.0, myB2 = 0.0;     // lane j keeps a_j and b_j^2
+    // (scalars of all lanes: held in scalar registers, the vector registers of this body set
+    // how many wavefronts of the kernels around it are resident)
+    auto uniform = [](double x) { return readlane_d(x, 0); };
     double a1 = 0.0, invd2 = 0.0, prod = 1.0;  // 1 / d^2 (0: no dominance), prod (b_j / d)^2
     int m = 0;
     sv[wv][i] = v;
@@ -128,16 +130,18 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
       m = j + 1;
       // b_j couples rows j and j + 1 of T; it is 0 when the process stops here
       prod *= ww;
-      if (j == 0) a1 = a;
+      if (j == 0) a1 = uniform(a);
       if (j == 1) {  // bprev = b_1
         const double hd = 0.5 * (a1 - a);
-        const double th = 0.5 * (a1 + a) + sqrt(__builtin_fma(hd, hd, bprev * bprev));
+        const double h2 = __builtin_fma(hd, hd, bprev * bprev);  // > 0: b_1 > 0 here
+        const double th = 0.5 * (a1 + a) + h2 * rsqrt_nr(h2);
         const double mu2 = fro2 - th * th, nu2 = fro2 - a1 * a1 - 2.0 * bprev * bprev;
-        const double d = th - sqrt(fmax(fmax(mu2, nu2), 0.0));
-        invd2 = d > 0.0 && d >= 0.0625 * th ? 1.0 / (d * d) : 0.0;
+        const double m2 = fmax(mu2, nu2), d = m2 > 0.0 ? th - m2 * rsqrt_nr(m2) : th;
+        const double di = rsqrt_nr(d * d);
+        invd2 = uniform(d > 0.0 && d >= 0.0625 * th ? di * di : 0.0);
         prod *= invd2;  // of b_1
       }
-      prod = j > 0 ? prod * invd2 : prod;
+      prod = uniform(j > 0 ? prod * invd2 : prod);
       const bool more = ww > tol2 && j + 1 < r &&
                         !(invd2 > 0.0 && prod <= 0x1p-60);  // false for NaN as well
       if (more) {
@@ -147,17 +151,17 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
       }
       const double rbn = more ? rsqrt_nr(ww) : 0.0;
       const double b = ww * rbn;
-      lo = fmax(lo, a);
-      hi = fmax(hi, a + bprev + b);
-      if (i == j) {
-        myA = a;
-        myB2 = more ? ww : 0.0;
+      lo = uniform(fmax(lo, a));
+      hi = uniform(fmax(hi, a + bprev + b));
+      if (t == 0) {  // unscaled: a_j, b_j^2 (not read where the process stops)
+        sA[j] = a;
+        sB[j] = ww;
       }
       if (!more) break;
       qprev = q;
       q = w * rbn;
-      bprev = b;
-      rb = rbn;
+      bprev = uniform(b);
+      rb = uniform(rbn);
     }
     if (wv == 0) {
       // scale T by 2^-ex (exact) so that hi lies in [1/2, 1)
@@ -165,6 +169,11 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
       int ex = 0;
       if (okb) frexp(hi, &ex);
       const int mpad = (m + 3) & ~3;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const double myA = sA[i], myB2 = sB[i];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
       if (i < mpad) {
         // padding rows sit two units below lo, so they never bound a shift from above
         sA[i] = i < m ? ldexp(myA, -ex) : ldexp(lo, -ex) - 2.0;
