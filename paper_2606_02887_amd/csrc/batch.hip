@@ -309,7 +309,7 @@ snmf_status batch_create(int32_t nprob, const snmf_matrix* A, const int32_t* r, 
   // row tiles per inner-kernel workgroup: more than one amortises each workgroup's fixed
   // cost (instance lookup, partial-sum reduction, line search, G staging).  The default 4
   // measured best on 256 graphs x 8 restarts (1: 114k, 2: 132k, 4: 138k, 8: 136k instance
-  // outer iterations/s); a tuning picks it per rank class.
+  // outer iterations/s, with one launch per rank); a tuning picks it per rank class.
   for (auto& kv : by_r) {
     snmf_batch::Cls c;
     c.r = kv.first;

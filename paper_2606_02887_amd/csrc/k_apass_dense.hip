@@ -435,9 +435,9 @@ __global__ __launch_bounds__(256, 2) void k_apass_f32w(const float* __restrict__
     // next two batches among the MFMAs of the current two, one load per four MFMAs (the
     // scheduling-group barriers below fix that order).  A wave issues in order and
     // stalls on a load the memory pipeline cannot take yet, so loads issued in bursts
-    // held back MFMAs that were ready (at n = 8192: 106.5 us in bursts, 88-91 us
-    // interleaved, TCP stalled on pending data 65% of the cycles with MFMA 49% busy
-    // before).  The prefetch of a batch beyond the last one re-reads the last batch (a
+    // held back MFMAs that were ready (at n = 8192, with an earlier epilogue: 106.5 us in
+    // bursts, 88-91 us interleaved, TCP stalled on pending data 65% of the cycles with
+    // MFMA 49% busy before).  The prefetch of a batch beyond the last one re-reads the last batch (a
     // valid address) and is never used, which keeps every load unconditional.
     const int64_t nbat = (we - wb) / (2 * U);
     const int64_t klast = wb + (nbat > 0 ? nbat - 1 : 0) * 2 * U;
