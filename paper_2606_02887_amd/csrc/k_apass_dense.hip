@@ -183,7 +183,8 @@ __global__ __launch_bounds__(256) void k_apass_f64(const double* __restrict__ A,
 // set, row 0 of the grid computes rho = ||G||_2 (rho.hpp) beside the tiles, first in
 // dispatch order because it is as long as they are.  n = 3001, r = 21: 16.8 us, 21.9 with rho;
 // two batches in flight behind predicated loads took 24.3 us, and rho 21.4 in a launch of
-// its own.
+// its own.  Whole calls at n = 16384: r = 21 190 us, r = 33 319 (200 and 454 with the loads of
+// a batch in one burst; 272 and 441 in the predicated form).
 template <int NMB>
 __global__ __launch_bounds__(256) void k_apass_f32(const float* __restrict__ A, int64_t lda,
                                                    const float* __restrict__ P, int64_t K, int64_t N,
@@ -253,6 +254,13 @@ __global__ __launch_bounds__(256) void k_apass_f32(const float* __restrict__ A, 
       for (int d = 0; d < kDepth; ++d) {
         mma(q[d]);
         load(q[d], k + (kDepth + d) * 2 * kBatch);
+      }
+      // a k-pair's MFMAs, then the loads that take its registers: a burst of loads that the
+      // memory pipeline cannot take yet would hold back MFMAs that are ready
+#pragma unroll
+      for (int i = 0; i < kDepth * kBatch; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 2 * NMB, 0);
+        __builtin_amdgcn_sched_group_barrier(0x020, 2 + NMB, 0);
       }
       k += kDepth * 2 * kBatch;
     }
