@@ -93,7 +93,7 @@ __global__ __launch_bounds__(256) void k_apass_f64(const double* __restrict__ A,
 #pragma unroll
           for (int q = 0; q < NB; ++q) x.p[u][s][q] = P[(k + s) * r + pc[q]];
       }
-    } else {  // the range's end: columns past it are zeros of A against a valid row of P
+    } else {  // the range's end: columns past it are zeros of A, and of P after `trim`
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -110,6 +110,18 @@ __global__ __launch_bounds__(256) void k_apass_f64(const double* __restrict__ A,
         }
     }
   };
+  // zeros for the rows of P past the range's end, once they are loaded: an infinite or NaN entry
+  // of P meets no column but its own (zeroed in `load`, the values are held twice: 200 to 256
+  // registers for 136 to 192)
+  auto trim = [&](Batch& x, int64_t k0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+          x.p[u][s][q] = k0 + 16 * u + 4 * g + s < ke ? x.p[u][s][q] : 0.0;
+  };
   auto mma = [&](const Batch& x) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -123,11 +135,15 @@ __global__ __launch_bounds__(256) void k_apass_f64(const double* __restrict__ A,
                                                               acc[mt][q], 0, 0, 0);
   };
   if (kb < ke) {
-    Batch x, y;
+    Batch x, y = {};
     load(x, kb);
     for (int64_t k0 = kb; k0 < ke; k0 += 32 * U) {
       const bool two = k0 + 16 * U < ke;
       if (two) load(y, k0 + 16 * U);
+      if (k0 + 32 * U > ke) {  // the last two batches
+        trim(x, k0);
+        trim(y, k0 + 16 * U);
+      }
       mma(x);
       if (!two) break;
       if (k0 + 32 * U < ke) load(x, k0 + 32 * U);

@@ -241,3 +241,22 @@ def test_dense_apass_f32_edges(S, n, r, pad):
         pl.apass(Pt, B)
     ref = A.astype(np.float64) @ P.astype(np.float64)
     assert (np.abs(B.cpu().numpy() - ref) <= n * 2.0 ** -24 * ref).all()
+
+
+@pytest.mark.parametrize("n,r", [(33, 16), (200, 16), (1000, 40), (4100, 17)])
+def test_dense_apass_f64_infinite_partner(S, n, r):
+    """An infinite entry of P makes its column of A P infinite (A > 0), never NaN, wherever it
+    lies in the K ranges: the zeros that fill a range's end meet zeros, not a row of P."""
+    rng = np.random.default_rng(n)
+    A = rng.random((n, n)) + 0.1
+    A = 0.5 * (A + A.T)
+    P = rng.random((n, r))
+    rows = np.unique(np.linspace(0, n - 1, r - 1).astype(int))
+    P[rows, np.arange(len(rows))] = np.inf     # the last row among them
+    Pt = _t(P, torch.float64)
+    with S.Plan(S.dense(_t(A, torch.float64)), r, S.params(prec=S.F64, max_outer=1)) as pl:
+        B = torch.empty_like(Pt)
+        pl.apass(Pt, B)
+    B = B.cpu().numpy()
+    assert (B[:, : len(rows)] == np.inf).all()
+    assert nrel(B[:, len(rows):], A @ P[:, len(rows):]) <= 1e-12
