@@ -129,7 +129,6 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
       const double ww = wave_sum(w * w);
       m = j + 1;
       // b_j couples rows j and j + 1 of T; it is 0 when the process stops here
-      prod *= ww;
       if (j == 0) a1 = uniform(a);
       if (j == 1) {  // bprev = b_1
         const double hd = 0.5 * (a1 - a);
@@ -141,7 +140,8 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
         invd2 = uniform(d > 0.0 && d >= 0.0625 * th ? di * di : 0.0);
         prod *= invd2;  // of b_1
       }
-      prod = uniform(j > 0 ? prod * invd2 : prod);
+      // every factor is formed relative to d: a bare b_1^2 b_2^2 underflows for a G of 1e-84
+      prod = uniform(j > 0 ? prod * (ww * invd2) : ww);
       const bool more = ww > tol2 && j + 1 < r &&
                         !(invd2 > 0.0 && prod <= 0x1p-60);  // false for NaN as well
       if (more) {

@@ -74,6 +74,17 @@ def test_rho_one_dominant_eigenvalue(S, r, ratio, mixed):
     ref = np.linalg.eigvalsh(G)[-1]
     assert abs(got - ref) <= 1e-13 * ref
 
+@pytest.mark.parametrize("scale", [1e-140, 1e-100, 1e-84, 1e-60, 1e60, 1e100, 1e140])
+def test_rho_dominance_at_any_scale(S, scale):
+    """The stop by dominance does not depend on the scale of G: the products of squared
+    off-diagonals it tests are formed relative to the gap."""
+    rng = np.random.default_rng(20)
+    P = rng.random((57, 20))
+    G = P.T @ P
+    got = S.rho(_t(G * scale, torch.float64)) / scale
+    ref = np.linalg.eigvalsh(G)[-1]
+    assert abs(got - ref) <= 1e-13 * ref
+
 
 # ------------------------------------------------------------------ Gram and A-pass
 # (132, 34) and (260, 64): FP32 workgroup chunks longer than a tile's K (one workgroup
