@@ -318,7 +318,7 @@ __global__ __launch_bounds__(kThreads) void k_split_pt_stack(const float* __rest
   if ((int64_t)blockIdx.x >= ntile) {
     const int s = (int)((int64_t)blockIdx.x - ntile);
     __builtin_amdgcn_s_setprio(3);  // rho sets this launch's length: issue priority
-    if (!st[s].done) rho_body(Grho + (int64_t)s * r * r, r, st + s);
+    if (!st[s].done) rho_body<true>(Grho + (int64_t)s * r * r, r, st + s);
     return;
   }
   bool all = true;

@@ -22,8 +22,8 @@ namespace snmf {
 // under a null test waited for its pointer argument and its flag in turn).
 __device__ int32_t g_no_gate = 0;
 
-template <typename T, int RP, bool RHO>
-__global__ __launch_bounds__(256, 8) void k_spmm(const int64_t* __restrict__ rowptr,
+template <typename T, int RP, int RHO>
+__global__ __launch_bounds__(256, RHO == 1 ? 7 : 8) void k_spmm(const int64_t* __restrict__ rowptr,
                                               const int32_t* __restrict__ col,
                                               const T* __restrict__ val, const T* __restrict__ X,
                                               int64_t n, int r, T* __restrict__ Y,
@@ -35,13 +35,15 @@ __global__ __launch_bounds__(256, 8) void k_spmm(const int64_t* __restrict__ row
   const int32_t* __restrict__ g2 = gate2 ? gate2 : g1;
   // RHO: workgroup 0 computes rho = ||G||_2 (dispatched first, so it runs beside the
   // product) and the product uses the workgroups after it.  A template flag, so the plain
-  // product keeps its lower register count; both are held to 64 registers (eight wavefronts
-  // per SIMD; rho alone takes 74, and at 84 the product lost 20% at n = 100000, r = 32).
+  // product keeps its lower register count.  RHO = 2 is held to 64 registers (eight wavefronts
+  // per SIMD), which the product needs where it sets the launch's length (at 84 registers it
+  // lost 20% at n = 100000, r = 32) and which lengthens rho's steps; RHO = 1 to 72, for the
+  // launches that rho sets the length of (rho_sets_length).
   constexpr int64_t b0 = RHO ? 1 : 0;
   if constexpr (RHO) {
     if (blockIdx.x == 0) {
       if (g1[0] | g2[0]) return;
-      rho_body(rj.G, rj.r, rj.st);
+      rho_body<true>(rj.G, rj.r, rj.st);
       return;
     }
   }
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(256) void k_bspmm(const BGraph* __restrict__ graphs
                                                const double* __restrict__ G64) {
   if ((int)blockIdx.x < nrho) {
     const int i = blockIdx.x;
-    if (!states[i].done) rho_body(G64 + inst[i].goff, inst[i].r, states + i);
+    if (!states[i].done) rho_body<true>(G64 + inst[i].goff, inst[i].r, states + i);
     return;
   }
   const int bid = (int)blockIdx.x - nrho;
@@ -684,22 +686,36 @@ __global__ __launch_bounds__(256) void k_lai_ut32(const float* __restrict__ U, i
     default: { constexpr int RP = 64; __VA_ARGS__; } break;         \
   }
 
+// True where rho (up to 0.85 us per rank, all r steps) is the longer part of a sparse product's
+// launch.  An outer iteration in FP32 with rho held to 72 / to 64 registers: 30 nonzeros per
+// row, r = 8 at n = 20000 129.5 / 131.1 us, at 30000 141.3 / 139.7; r = 32 at n = 2000 165 / 170,
+// at 40000 243 / 251, at 60000 284 / 281; r = 64 at n = 40000 532 / 547, at 100000 906 / 888; at
+// n = 20000, r = 32 with 100 nonzeros per row 205 / 212, with 500 357 / 347.
+static bool rho_sets_length(int64_t n, int64_t nnz, int r) {
+  return n < 15000 + 1200 * r && nnz < 4000000;
+}
+
 template <typename T>
 void launch_spmm(const int64_t* rowptr, const int32_t* col, const T* val, const T* X, int64_t n,
                  int r, T* Y, const T* X2, double* part, const int32_t* gate,
-                 const int32_t* gate2, hipStream_t s, const RhoJob& rj) {
+                 const int32_t* gate2, hipStream_t s, const RhoJob& rj, int64_t nnz) {
   int64_t nb = (n + 3) / 4;
   if (X2) nb = spmm_dot_grid(n);
   if (nb > 65535 * 4) nb = 65535 * 4;
   if (nb < 1) nb = 1;
-  if (rj.G) {
+  if (rj.G && rho_sets_length(n, nnz, r)) {
     SNMF_DISPATCH_RP2(rank_pad(r),
-                      hipLaunchKernelGGL((k_spmm<T, RP, true>), dim3((unsigned)(nb + 1)), dim3(256),
+                      hipLaunchKernelGGL((k_spmm<T, RP, 1>), dim3((unsigned)(nb + 1)), dim3(256),
+                                         0, s, rowptr, col, val, X, n, r, Y, X2, part, gate, gate2,
+                                         rj))
+  } else if (rj.G) {
+    SNMF_DISPATCH_RP2(rank_pad(r),
+                      hipLaunchKernelGGL((k_spmm<T, RP, 2>), dim3((unsigned)(nb + 1)), dim3(256),
                                          0, s, rowptr, col, val, X, n, r, Y, X2, part, gate, gate2,
                                          rj))
   } else {
     SNMF_DISPATCH_RP2(rank_pad(r),
-                      hipLaunchKernelGGL((k_spmm<T, RP, false>), dim3((unsigned)nb), dim3(256), 0,
+                      hipLaunchKernelGGL((k_spmm<T, RP, 0>), dim3((unsigned)nb), dim3(256), 0,
                                          s, rowptr, col, val, X, n, r, Y, X2, part, gate, gate2,
                                          rj))
   }
@@ -764,7 +780,7 @@ void launch_lai(const T* U, int ell, const double* lam, const T* P, int64_t n, i
 #define SNMF_INST_SP(T)                                                                      \
   template void launch_spmm<T>(const int64_t*, const int32_t*, const T*, const T*, int64_t,  \
                                int, T*, const T*, double*, const int32_t*, const int32_t*,   \
-                               hipStream_t, const RhoJob&);                                  \
+                               hipStream_t, const RhoJob&, int64_t);                         \
   template void launch_lai<T>(const T*, int, const double*, const T*, int64_t, int, double*, \
                               T*, T*, const int32_t*, hipStream_t, const RhoJob&);
 SNMF_INST_SP(float)

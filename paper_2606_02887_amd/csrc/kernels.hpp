@@ -119,7 +119,8 @@ void launch_apass_bf16x3_stack(const uint16_t* Ahi, const uint16_t* Alo, int64_t
 template <typename T>
 void launch_spmm(const int64_t* rowptr, const int32_t* col, const T* val, const T* X, int64_t n,
                  int r, T* Y, const T* X2, double* part, const int32_t* gate,
-                 const int32_t* gate2, hipStream_t s, const RhoJob& rj = RhoJob{});
+                 const int32_t* gate2, hipStream_t s, const RhoJob& rj = RhoJob{},
+                 int64_t nnz = 0);  // with rj.G: the matrix's nonzeros
 int spmm_dot_grid(int64_t n);
 template <typename T>
 void launch_bspmm(const BGraph* graphs, const int32_t* sblk_graph, int sblocks,

@@ -97,10 +97,10 @@ void half_step(NmfPlan& pl, T* X, int64_t nX, const T* P, int64_t nP, int is_hst
     launch_rect_apass<T>((const T*)pl.V.dense, pl.V.ld, nX, nP, is_hstep, P, r, B, pl.st, s);
   } else if (!is_hstep) {
     launch_spmm<T>(pl.V.rowptr, pl.V.col, (const T*)pl.V.val, P, nX, r, B, nullptr, nullptr,
-                   &pl.st->done, nullptr, s, rj);
+                   &pl.st->done, nullptr, s, rj, pl.V.nnz);
   } else {
     launch_spmm<T>(pl.rowptrT, pl.colT, (const T*)pl.valT, P, nX, r, B, nullptr, nullptr,
-                   &pl.st->done, nullptr, s, rj);
+                   &pl.st->done, nullptr, s, rj, pl.V.nnz);
   }
   const T* Pz = (const T*)pl.Pz;
   const T* GT = (const T*)pl.GT[gi];

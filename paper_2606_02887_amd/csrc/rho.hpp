@@ -20,10 +20,12 @@
 //    of theta I - T_{j..k}, j >= 2, is at least d), the residual of the Ritz pair is b_k times
 //    that, and lambda_1 - theta <= residual^2 / d.  The process ends when
 //    prod_{j<=k} (b_j / d)^2 <= 2^-60, an error below 2^-60 lambda_1; used for
-//    d >= theta_2 / 16, far above the rounding of F^2 - theta_2^2.  The Gram of a factor whose
-//    columns all correlate stops after 4 to 10 steps (r = 64: 8.7, r = 21: 7.3 us), that
-//    of a near-indicator factor, with many large eigenvalues, runs all r steps (r = 64: 56,
-//    r = 21: 21 us).
+//    d >= theta_2 / 16, far above the rounding of F^2 - theta_2^2.  Where step 2 finds no
+//    dominance the steps after it leave the test out (with it a step waits for one more chain
+//    of products and a lane read).  The Gram of a factor whose columns all correlate stops
+//    after 4 to 10 steps (r = 64: 8.3, r = 20: 8.5 us), that of a near-indicator factor, with
+//    many large eigenvalues, runs all r steps (r = 64: 52.2 us, r = 20: 19.6; 54.6 and 20.3
+//    with the test in every step; 53.1 and 19.9 before there was one).
 // 2. Multisection on T: each round places 256 shifts x evenly in [lo, hi], one per
 //    thread, and keeps the subinterval where x I - T turns positive definite.  The test
 //    runs the leading principal minors s_k = det(x I - T_k),
@@ -59,7 +61,10 @@ __device__ __forceinline__ double rsqrt_nr(double x) {
 }
 
 // Whole workgroup (kThreads threads) must call; writes st->rho, or flags a breakdown when
-// the result is not a positive finite number.
+// the result is not a positive finite number.  LEAN: the scalars that all lanes share are kept
+// in scalar registers by lane reads (74 vector registers for 82, a full run 1.5 us longer at
+// r = 64), for kernels whose product loses resident wavefronts to this body's registers.
+template <bool LEAN = false>
 __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
                                          State* __restrict__ st) {
   constexpr int kW = kThreads / kWave;   // 4 wavefronts
@@ -100,14 +105,15 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
     double rb = 1.0 / sqrt((double)r);
     double q = v * rb, qprev = 0.0, bprev = 0.0;
     double lo = -1e300, hi = -1e300;  // max a_k and the Gershgorin bound, uniform
-    // (scalars of all lanes: held in scalar registers, the vector registers of this body set
-    // how many wavefronts of the kernels around it are resident)
     auto uniform = [](double x) { return readlane_d(x, 0); };
-    double a1 = 0.0, invd2 = 0.0, prod = 1.0;  // 1 / d^2 (0: no dominance), prod (b_j / d)^2
+    auto keep = [](double x) { return LEAN ? readlane_d(x, 0) : x; };
+    double myA = 0.0, myB2 = 0.0;     // lane j keeps a_j and b_j^2
     int m = 0;
     sv[wv][i] = v;
     __builtin_amdgcn_wave_barrier();
-    for (int j = 0; j < r; ++j) {
+    // Step j: a_j and ww = b_j^2, and the vector of step j + 1 in sv and q unless the process
+    // stops here (`end` may stop it too); false: it stopped.
+    auto step = [&](int j, double& a, double& ww, auto&& end) __attribute__((always_inline)) {
       double w0 = 0.0, w1 = 0.0, w2 = 0.0, w3 = 0.0;
 #pragma unroll
       for (int c = 0; c < kC; c += 4) {
@@ -123,27 +129,13 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
       __syncthreads();
       const double4 z4 = *(const double4*)&sz[par][i][0];
       double w = ((z4.x + z4.y) + (z4.z + z4.w)) * rb;  // (G q_j)_i
-      const double a = wave_sum(q * w);
+      a = wave_sum(q * w);
       w = __builtin_fma(-a, q, w);
       w = __builtin_fma(-bprev, qprev, w);
-      const double ww = wave_sum(w * w);
+      ww = wave_sum(w * w);
       m = j + 1;
       // b_j couples rows j and j + 1 of T; it is 0 when the process stops here
-      if (j == 0) a1 = uniform(a);
-      if (j == 1) {  // bprev = b_1
-        const double hd = 0.5 * (a1 - a);
-        const double h2 = __builtin_fma(hd, hd, bprev * bprev);  // > 0: b_1 > 0 here
-        const double th = 0.5 * (a1 + a) + h2 * rsqrt_nr(h2);
-        const double mu2 = fro2 - th * th, nu2 = fro2 - a1 * a1 - 2.0 * bprev * bprev;
-        const double m2 = fmax(mu2, nu2), d = m2 > 0.0 ? th - m2 * rsqrt_nr(m2) : th;
-        const double di = rsqrt_nr(d * d);
-        invd2 = uniform(d > 0.0 && d >= 0.0625 * th ? di * di : 0.0);
-        prod *= invd2;  // of b_1
-      }
-      // every factor is formed relative to d: a bare b_1^2 b_2^2 underflows for a G of 1e-84
-      prod = uniform(j > 0 ? prod * (ww * invd2) : ww);
-      const bool more = ww > tol2 && j + 1 < r &&
-                        !(invd2 > 0.0 && prod <= 0x1p-60);  // false for NaN as well
+      const bool more = ww > tol2 && j + 1 < r && !end();  // false for NaN as well
       if (more) {
         __builtin_amdgcn_wave_barrier();  // this wave has read the old vector
         sv[wv][i] = w;
@@ -151,17 +143,46 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
       }
       const double rbn = more ? rsqrt_nr(ww) : 0.0;
       const double b = ww * rbn;
-      lo = uniform(fmax(lo, a));
-      hi = uniform(fmax(hi, a + bprev + b));
-      if (t == 0) {  // unscaled: a_j, b_j^2 (not read where the process stops)
-        sA[j] = a;
-        sB[j] = ww;
+      lo = keep(fmax(lo, a));
+      hi = keep(fmax(hi, a + bprev + b));
+      if (i == j) {  // (b_j^2 is not read where the process stops)
+        myA = a;
+        myB2 = ww;
       }
-      if (!more) break;
+      if (!more) return false;
       qprev = q;
       q = w * rbn;
-      bprev = uniform(b);
-      rb = uniform(rbn);
+      bprev = keep(b);
+      rb = keep(rbn);
+      return true;
+    };
+    // The first two steps, and the others where an eigenvalue dominates; else the plain steps
+    // (a test that cannot hold would lengthen each of r steps).
+    {
+      double a, ww, invd2 = 0.0, prod = 0.0;  // 1 / d^2 (0: no dominance), prod (b_j / d)^2
+      bool run = step(0, a, ww, [] { return false; });
+      if (run) {
+        const double a1 = uniform(a), b1 = uniform(ww);
+        run = step(1, a, ww, [&]() __attribute__((always_inline)) {
+          const double hd = 0.5 * (a1 - a);
+          const double h2 = __builtin_fma(hd, hd, b1);  // > 0: b_1 > 0 here
+          const double th = 0.5 * (a1 + a) + h2 * rsqrt_nr(h2);
+          const double mu2 = fro2 - th * th, nu2 = fro2 - a1 * a1 - 2.0 * b1;
+          const double m2 = fmax(mu2, nu2), d = m2 > 0.0 ? th - m2 * rsqrt_nr(m2) : th;
+          const double di = rsqrt_nr(d * d);
+          invd2 = uniform(d > 0.0 && d >= 0.0625 * th ? di * di : 0.0);
+          prod = uniform((b1 * invd2) * (ww * invd2));  // each factor free of the scale of G
+          return invd2 > 0.0 && prod <= 0x1p-60;
+        });
+      }
+      int j = 2;
+      if (invd2 > 0.0)
+        for (; run; ++j)
+          run = step(j, a, ww, [&]() __attribute__((always_inline)) {
+            prod = uniform(prod * (ww * invd2));
+            return prod <= 0x1p-60;
+          });
+      for (; run; ++j) run = step(j, a, ww, [] { return false; });
     }
     if (wv == 0) {
       // scale T by 2^-ex (exact) so that hi lies in [1/2, 1)
@@ -169,11 +190,6 @@ __device__ __forceinline__ void rho_body(const double* __restrict__ G, int r,
       int ex = 0;
       if (okb) frexp(hi, &ex);
       const int mpad = (m + 3) & ~3;
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      const double myA = sA[i], myB2 = sB[i];
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
       if (i < mpad) {
         // padding rows sit two units below lo, so they never bound a shift from above
         sA[i] = i < m ? ldexp(myA, -ex) : ldexp(lo, -ex) - 2.0;

@@ -259,7 +259,7 @@ snmf_status apass(snmf_plan* pl, const T* P, hipStream_t s, const RhoJob& rj = R
       break;
     case SNMF_CSR:
       launch_spmm<T>(pl->A.rowptr, pl->A.col, (const T*)pl->A.val, P, n, r, (T*)pl->Bpart, nullptr,
-                     nullptr, gate, nullptr, s, rj);
+                     nullptr, gate, nullptr, s, rj, pl->A.nnz);
       break;
     default:
       launch_lai<T>((const T*)pl->A.U, (int)pl->A.ell, pl->A.lam, P, n, r, pl->lai_part,

@@ -86,6 +86,31 @@ def test_rho_dominance_at_any_scale(S, scale):
     assert abs(got - ref) <= 1e-13 * ref
 
 
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("n,r,row", [(20999, 5, 3), (21000, 5, 3), (62999, 40, 3), (63000, 40, 3),
+                                     (2100, 33, 4199)])
+def test_rho_in_the_sparse_product(S, prec, n, r, row):
+    """rho beside the sparse product, on both sides of the choice between the two forms of the
+    launch (n < 15000 + 1200 r, fewer than 4e6 nonzeros), with no dominant eigenvalue (the
+    partner's columns are nearly disjoint) and with one: FP64 1e-13; FP32 rounds P alone, the
+    Gram of the rounded P is taken as the reference."""
+    dt = torch.float64 if prec == "f64" else torch.float32
+    rng = np.random.default_rng(n + r)
+    k = (row - 1) // 2
+    A = sp.diags([np.ones(n - d) for d in range(k + 1)], range(k + 1))
+    A = (A + sp.triu(A, 1).T).tocsr()
+    assert (A.nnz >= 4_000_000) == (row == 4199)
+    for P in (rng.random((n, r)), 0.01 * rng.random((n, r))):
+        if P.max() < 0.1:
+            P[np.arange(n), np.arange(n) % r] += 1.0 + 0.1 * (np.arange(n) % r)
+        Pt = _t(P, dt)
+        with S.Plan(S.csr_from_scipy(A, dt), r, S.params(prec=S.prec_of(dt), max_outer=1)) as pl:
+            got = pl.half_step(Pt.clone(), Pt, False)["rho"]
+        Pd = Pt.double().cpu().numpy()
+        ref = np.linalg.eigvalsh(Pd.T @ Pd)[-1]
+        assert abs(got - ref) <= 1e-13 * ref
+
+
 # ------------------------------------------------------------------ Gram and A-pass
 # (132, 34) and (260, 64): FP32 workgroup chunks longer than a tile's K (one workgroup
 # spans several tiles); (2048, 64), (4100, 34), (4608, 64): chunks that end inside tiles
