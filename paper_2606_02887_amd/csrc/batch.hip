@@ -442,6 +442,7 @@ snmf_status batch_create(int32_t nprob, const snmf_matrix* A, const int32_t* r, 
   add((void**)&b->part, (size_t)2 * kMaxGrid * kNumPart * 8);
   add((void**)&b->dots, 64 * 8);
   add((void**)&b->flags, 4 * sizeof(unsigned));
+  add((void**)&b->bad, sizeof(uint64_t));
   add((void**)&b->dinst, (size_t)b->ninst * sizeof(BInst));
   add((void**)&b->blk_tab, btab.size() * 4);
   add((void**)&b->gblk_tab, gtab.size() * 4);
@@ -458,6 +459,7 @@ snmf_status batch_create(int32_t nprob, const snmf_matrix* A, const int32_t* r, 
     o += q.second;
   }
   HIP_TRY(hipMemsetAsync(b->states, 0, (size_t)b->ninst * sizeof(State), b->s));
+  HIP_TRY(hipMemsetAsync(b->bad, 0, sizeof(uint64_t), b->s));
 
   // ---- input checks and ||A_g||^2
   b->normA2.resize(nprob);
@@ -529,27 +531,30 @@ snmf_status batch_solve(snmf_batch* b, const void* const* W0, void* const* W_out
         t.s[t.n++] = {H, Ht_out[g], nullptr, cnt};
       }
       if (t.n < kCopySegs && g + 1 < b->nprob) continue;
-      unsigned* const bad = b->p.validate ? b->flags : nullptr;
-      if (b->prec == SNMF_F64) launch_copy<double>(t, in, bad, b->s);
-      else launch_copy<float>(t, in, bad, b->s);
+      uint64_t* const bad = in && b->p.validate ? b->bad : nullptr;
+      if (b->prec == SNMF_F64) launch_copy<double>(t, in, bad, b->seq, b->s);
+      else launch_copy<float>(t, in, bad, b->seq, b->s);
       t.n = 0;
       t.base = g + 1;
     }
   };
-  auto check = [&](unsigned bad) -> snmf_status {
-    if (bad == kCopyOk) return SNMF_OK;
-    if ((bad & 1u) == 0) return fail(SNMF_E_NONFINITE, "W0 has NaN/Inf entries");
-    return fail(SNMF_E_NEGATIVE, "W0 has negative entries");
-  };
-  launch_breset(b->states, b->dinst, b->ninst, b->s, b->flags);
+  if (++b->seq == 0) {
+    HIP_TRY(hipMemsetAsync(b->bad, 0, sizeof(uint64_t), b->s));
+    b->seq = 1;
+  }
   copy(true);
   HIP_TRY(hipGetLastError());
-  unsigned bad = kCopyOk;
   if (b->p.validate) {  // one host wait for all starts
-    HIP_TRY(hipMemcpyAsync(&bad, b->flags, sizeof(bad), hipMemcpyDeviceToHost, b->s));
+    uint64_t bad = 0;
+    HIP_TRY(hipMemcpyAsync(&bad, b->bad, sizeof(bad), hipMemcpyDeviceToHost, b->s));
     HIP_TRY(hipStreamSynchronize(b->s));
-    SNMF_TRY(check(bad));
+    if (copy_bad(bad, b->seq)) {
+      if ((copy_code(bad) & 1u) == 0) return fail(SNMF_E_NONFINITE, "W0 has NaN/Inf entries");
+      return fail(SNMF_E_NEGATIVE, "W0 has negative entries");
+    }
   }
+  launch_breset(b->states, b->dinst, b->ninst, b->s);  // the solve's clock starts here
+  HIP_TRY(hipGetLastError());
   const int every = std::max(1, b->p.check_every);
   if (b->p.use_graph && !b->gexec) {
     HIP_TRY(hipStreamBeginCapture(b->s, hipStreamCaptureModeThreadLocal));

@@ -59,6 +59,8 @@ struct snmf_batch {
   snmf::BOut* bout = nullptr;        // every instance's results, for the read back
   int32_t* flag = nullptr;
   unsigned* flags = nullptr;
+  uint64_t* bad = nullptr;           // what the checks of the starts found, and the last one's
+  uint32_t seq = 0;                  //   number (common.hpp)
   BInst* dinst = nullptr;
   int32_t *blk_tab = nullptr, *gblk_tab = nullptr, *sblk_tab = nullptr;
   BGraph* dgraph = nullptr;

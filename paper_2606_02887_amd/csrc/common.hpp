@@ -65,9 +65,13 @@ struct CopyTab {
   int32_t n;       // segments
   int32_t base;    // number of the first one over all launches
 };
-// What a check of copied values found: kCopyOk, or 2 q + (0: non-finite, 1: negative) for the
-// first segment q with such a value.
-constexpr unsigned kCopyOk = ~0u;
+// What the checks of copied values found, in a word that starts at 0 and is never cleared:
+// check number seq (from 1) raises it to seq 2^32 + ~code, code = 2 q + (0: non-finite, 1:
+// negative) for the first segment q with such a value.
+__host__ __device__ inline bool copy_bad(uint64_t word, uint32_t seq) {
+  return (uint32_t)(word >> 32) == seq;
+}
+inline uint32_t copy_code(uint64_t word) { return ~(uint32_t)word; }
 
 // Results of one instance of a batched solve, gathered for one small read back.
 struct BOut {

@@ -207,8 +207,8 @@ template void launch_csr_symmetry<float>(const int64_t*, const int32_t*, const f
 template void launch_csr_symmetry<double>(const int64_t*, const int32_t*, const double*, int64_t,
                                           int64_t, unsigned*, hipStream_t);
 
-// Solve start: clear the device state, store ||A||^2 and the start time; one wavefront (one
-// thread storing the whole struct took 41 us).
+// Solve start, after the copy and check of the start: clear the device state, store ||A||^2
+// and the start time; one wavefront (one thread storing the whole struct took 41 us).
 static_assert(sizeof(State) % 8 == 0, "State is cleared in 8-byte words");
 __device__ __forceinline__ void reset_state(State* st, double normA2) {
   uint64_t* const w = (uint64_t*)st;
@@ -219,22 +219,23 @@ __device__ __forceinline__ void reset_state(State* st, double normA2) {
     st->t0 = wall_clock64();
   }
 }
-__global__ __launch_bounds__(kWave) void k_reset_state(State* st, double normA2, unsigned* bad) {
+__global__ __launch_bounds__(kWave) void k_reset_state(State* st, double normA2,
+                                                       const uint64_t* bad, uint32_t seq) {
+  const int done = bad && copy_bad(*bad, seq);
   reset_state(st, normA2);
-  if (bad && threadIdx.x == 0) *bad = kCopyOk;
+  if (threadIdx.x == 0) st->done = done;
 }
-void launch_reset_state(State* st, double normA2, hipStream_t s, unsigned* bad) {
-  hipLaunchKernelGGL(k_reset_state, dim3(1), dim3(kWave), 0, s, st, normA2, bad);
+void launch_reset_state(State* st, double normA2, hipStream_t s, const uint64_t* bad,
+                        uint32_t seq) {
+  hipLaunchKernelGGL(k_reset_state, dim3(1), dim3(kWave), 0, s, st, normA2, bad, seq);
 }
 
 // Batched solve start: one State per instance.
-__global__ __launch_bounds__(kWave) void k_breset(State* states, const BInst* inst,
-                                                  unsigned* bad) {
+__global__ __launch_bounds__(kWave) void k_breset(State* states, const BInst* inst) {
   reset_state(states + blockIdx.x, inst[blockIdx.x].normA2);
-  if (bad && blockIdx.x == 0 && threadIdx.x == 0) *bad = kCopyOk;
 }
-void launch_breset(State* states, const BInst* inst, int ninst, hipStream_t s, unsigned* bad) {
-  hipLaunchKernelGGL(k_breset, dim3(ninst), dim3(kWave), 0, s, states, inst, bad);
+void launch_breset(State* states, const BInst* inst, int ninst, hipStream_t s) {
+  hipLaunchKernelGGL(k_breset, dim3(ninst), dim3(kWave), 0, s, states, inst);
 }
 
 // Batched solve end: every instance's results in one compact array.
@@ -271,8 +272,9 @@ void launch_bout(const State* states, int ninst, BOut* out, hipStream_t s) {
 // checks and copies they replace were a launch each, and a host wait per array.
 constexpr int kCopyPer = 16;
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_copy(CopyTab t, int check, unsigned* bad) {
-  if (bad && !check && *bad != kCopyOk) return;
+__global__ __launch_bounds__(kThreads) void k_copy(CopyTab t, int check, uint64_t* bad,
+                                                  uint32_t seq) {
+  if (bad && !check && copy_bad(*bad, seq)) return;
   int q = 0;
   while (q + 1 < t.n && (int)blockIdx.x >= t.blk0[q + 1]) ++q;
   const CopySeg& g = t.s[q];
@@ -304,10 +306,11 @@ __global__ __launch_bounds__(kThreads) void k_copy(CopyTab t, int check, unsigne
     }
   }
   if (bad && check && (neg || nonfin))
-    atomicMin(bad, 2u * (unsigned)(t.base + q) + (nonfin ? 0u : 1u));
+    atomicMax((unsigned long long*)bad,
+              (unsigned long long)seq << 32 | (uint32_t)~(2u * (uint32_t)(t.base + q) + (nonfin ? 0u : 1u)));
 }
 template <typename T>
-void launch_copy(CopyTab& t, bool check, unsigned* bad, hipStream_t s) {
+void launch_copy(CopyTab& t, bool check, uint64_t* bad, uint32_t seq, hipStream_t s) {
   int64_t nb = 0;
   for (int q = 0; q < t.n; ++q) {
     t.blk0[q] = (int32_t)nb;
@@ -315,10 +318,11 @@ void launch_copy(CopyTab& t, bool check, unsigned* bad, hipStream_t s) {
   }
   t.blk0[t.n] = (int32_t)nb;
   if (nb < 1) return;
-  hipLaunchKernelGGL(k_copy<T>, dim3((unsigned)nb), dim3(kThreads), 0, s, t, check ? 1 : 0, bad);
+  hipLaunchKernelGGL(k_copy<T>, dim3((unsigned)nb), dim3(kThreads), 0, s, t, check ? 1 : 0, bad,
+                     seq);
 }
-template void launch_copy<float>(CopyTab&, bool, unsigned*, hipStream_t);
-template void launch_copy<double>(CopyTab&, bool, unsigned*, hipStream_t);
+template void launch_copy<float>(CopyTab&, bool, uint64_t*, uint32_t, hipStream_t);
+template void launch_copy<double>(CopyTab&, bool, uint64_t*, uint32_t, hipStream_t);
 
 // flag = 1 when every instance of a batched solve is done.
 __global__ __launch_bounds__(256) void k_all_done(const State* states, int ninst, int32_t* flag) {

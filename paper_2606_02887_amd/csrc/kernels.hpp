@@ -127,8 +127,7 @@ void launch_bspmm(const BGraph* graphs, const int32_t* sblk_graph, int sblocks,
                   State* states, const T* P, T* B, hipStream_t s,
                   const BInst* inst = nullptr, int nrho = 0,  // rho of instances 0 .. nrho - 1
                   const double* G64 = nullptr);               // from their Gram;
-void launch_breset(State* states, const BInst* inst, int ninst, hipStream_t s,
-                   unsigned* bad = nullptr);  // bad: also set to kCopyOk
+void launch_breset(State* states, const BInst* inst, int ninst, hipStream_t s);
 void launch_bout(const State* states, int ninst, BOut* out, hipStream_t s);
 void launch_all_done(const State* states, int ninst, int32_t* flag, hipStream_t s);
 template <typename T>
@@ -182,12 +181,14 @@ void launch_csr_structure(const int64_t* rowptr, const int32_t* col, int64_t n, 
 template <typename T>
 void launch_csr_symmetry(const int64_t* rowptr, const int32_t* col, const T* val, int64_t n,
                          int64_t nnz, unsigned* flags, hipStream_t s);
-void launch_reset_state(State* st, double normA2, hipStream_t s, unsigned* bad = nullptr);
+// bad set: the solve is done from the start when check seq has found a bad value.
+void launch_reset_state(State* st, double normA2, hipStream_t s, const uint64_t* bad = nullptr,
+                        uint32_t seq = 0);
 // Copies the segments of t; with bad set, check: true looks for negative and non-finite
-// values (atomicMin of the code above into bad), false leaves everything alone unless *bad is
-// kCopyOk.
+// values as check number seq (common.hpp), false leaves everything alone when that check
+// has found one.
 template <typename T>
-void launch_copy(CopyTab& t, bool check, unsigned* bad, hipStream_t s);
+void launch_copy(CopyTab& t, bool check, uint64_t* bad, uint32_t seq, hipStream_t s);
 void launch_split_flat(const float* x, int64_t count, uint16_t* hi, uint16_t* lo, hipStream_t s);
 
 

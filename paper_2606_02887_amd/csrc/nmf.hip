@@ -41,6 +41,7 @@ struct NmfPlan {
   double* trace = nullptr;
   State* st = nullptr;
   unsigned *flags = nullptr, *cnt = nullptr;
+  uint64_t* bad = nullptr;  // what the check of the starts found (common.hpp)
   unsigned long long* cursor = nullptr;
   int64_t* rowptrT = nullptr;
   int32_t* colT = nullptr;
@@ -168,7 +169,7 @@ snmf_status run(NmfPlan& pl, void* W_out, void* Ht_out, snmf_info* info, double*
   out.n = 2;
   out.s[0] = {pl.Wb, W_out, nullptr, m * r};
   out.s[1] = {pl.Hb, Ht_out, nullptr, n * r};
-  launch_copy<T>(out, false, nullptr, s);
+  launch_copy<T>(out, false, nullptr, 0, s);
   HIP_TRY(hipGetLastError());
   State hs;
   HIP_TRY(hipMemcpyAsync(&hs, pl.st, sizeof(State), hipMemcpyDeviceToHost, s));
@@ -274,6 +275,7 @@ snmf_status nmf_solve(const snmf_matrix* V, int64_t ncols, int32_t r, const void
   add((void**)&pl.trace, (size_t)p->max_outer * kTraceFields * 8);
   add((void**)&pl.st, sizeof(State));
   add((void**)&pl.flags, 4 * sizeof(unsigned));
+  add((void**)&pl.bad, sizeof(uint64_t));
   if (V->fmt == SNMF_DENSE && p->prec == SNMF_F32) {
     if ((m + 63) / 64 > 65535 || (ncols + 63) / 64 > 65535)
       return fail(SNMF_E_SHAPE, "V: FP32 dense NMF takes m, n_cols <= 4194240");
@@ -335,27 +337,27 @@ snmf_status nmf_solve(const snmf_matrix* V, int64_t ncols, int32_t r, const void
     launch_transpose<float>((const float*)V->dense, m, ncols, V->ld, (float*)pl.VT, s);
     HIP_TRY(hipGetLastError());
   }
-  HIP_TRY(hipMemsetAsync(pl.flags, 0xff, sizeof(unsigned), s));  // kCopyOk
+  HIP_TRY(hipMemsetAsync(pl.bad, 0, sizeof(uint64_t), s));
   CopyTab in{};
   in.n = 2;
   in.s[0] = {W0, pl.Wb, nullptr, m * r};
   in.s[1] = {Ht0, pl.Hb, nullptr, ncols * r};
   if (pl.prec == SNMF_F64)
-    launch_copy<double>(in, true, p->validate ? pl.flags : nullptr, s);
+    launch_copy<double>(in, true, p->validate ? pl.bad : nullptr, 1, s);
   else
-    launch_copy<float>(in, true, p->validate ? pl.flags : nullptr, s);
+    launch_copy<float>(in, true, p->validate ? pl.bad : nullptr, 1, s);
   HIP_TRY(hipGetLastError());
-  unsigned bad = kCopyOk;
+  uint64_t bad = 0;
   if (V->fmt == SNMF_DENSE)
     HIP_TRY(hipMemcpyAsync(st3, pl.dots, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(&bad, pl.flags, sizeof(bad), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(&bad, pl.bad, sizeof(bad), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   if (V->fmt == SNMF_DENSE && p->validate) SNMF_TRY(check_vals(st3, "V"));
   pl.normV2 = st3[0];
   if (!(pl.normV2 > 0.0)) return fail(SNMF_E_ARG, "V is zero");
-  if (bad != kCopyOk) {
-    const std::string what = bad < 2 ? "W0" : "Ht0";
-    if ((bad & 1u) == 0) return fail(SNMF_E_NONFINITE, what + " has NaN/Inf entries");
+  if (copy_bad(bad, 1)) {
+    const std::string what = copy_code(bad) < 2 ? "W0" : "Ht0";
+    if ((copy_code(bad) & 1u) == 0) return fail(SNMF_E_NONFINITE, what + " has NaN/Inf entries");
     return fail(SNMF_E_NEGATIVE, what + " has negative entries");
   }
   if (pl.prec == SNMF_F64) return run<double>(pl, W_out, Ht_out, info, trace);

@@ -57,7 +57,8 @@ struct snmf_plan {
   int64_t ldb = 0;
   State* st = nullptr;
   unsigned* flags = nullptr;
-  unsigned* bad() { return (unsigned*)(st + 1); }  // what the check of W0 found
+  uint64_t* bad() { return (uint64_t*)(st + 1); }  // what the checks of W0 found, and the
+  uint32_t seq = 0;                                //   last one's number (common.hpp)
   DenseSplit ds{};
   int gram_blocks = 1;
   int grid = 1;  // workgroups of every row-tile kernel of the plan (one partial-sum layout)
@@ -551,7 +552,7 @@ snmf_status plan_init(snmf_plan* pl, const snmf_matrix* A, int32_t r, const snmf
     *req[q].first = (char*)pl->pool + off;
     off += req[q].second;
   }
-  HIP_TRY(hipMemsetAsync(pl->st, 0, sizeof(State), pl->s));
+  HIP_TRY(hipMemsetAsync(pl->st, 0, sizeof(State) + 8, pl->s));
   // input checks and ||A||^2
   double st3[3] = {0, 0, 0};
   if (A->fmt == SNMF_DENSE) {
@@ -600,27 +601,28 @@ snmf_status plan_create(const snmf_matrix* A, int32_t r, const snmf_params* p, h
   return SNMF_OK;
 }
 
-snmf_status start_check(unsigned bad, const char* what) {
-  if (bad == kCopyOk) return SNMF_OK;
-  if ((bad & 1u) == 0) return fail(SNMF_E_NONFINITE, std::string(what) + " has NaN/Inf entries");
-  return fail(SNMF_E_NEGATIVE, std::string(what) + " has negative entries");
+snmf_status start_check(const snmf_plan* pl, uint64_t bad) {
+  if (!copy_bad(bad, pl->seq)) return SNMF_OK;
+  if ((copy_code(bad) & 1u) == 0) return fail(SNMF_E_NONFINITE, "W0 has NaN/Inf entries");
+  return fail(SNMF_E_NEGATIVE, "W0 has negative entries");
 }
 
 // Solves of at most this many outer iterations are not held up for the check of W0: its
-// result comes back with theirs, and a bad start leaves every output untouched.  Longer ones
-// wait for it first (a host wait, about 20 us of at least 64 iterations).
+// result comes back with theirs, and a bad start ends the solve on the device (every launch
+// returns at once) and leaves every output untouched.  Longer ones wait for it first (a host
+// wait, about 20 us of at least 64 iterations).
 constexpr int kDeferOuter = 64;
 constexpr int kDirectOuter = 64;  // snmf_solve: direct launches up to here
 
 snmf_status read_info(snmf_plan* pl, snmf_info* info, double* trace) {
   struct {
     State hs;
-    unsigned bad, pad;
+    uint64_t bad;
   } back;
   HIP_TRY(hipMemcpyAsync(&back, pl->st, sizeof(State) + 8, hipMemcpyDeviceToHost, pl->s));
   HIP_TRY(hipStreamSynchronize(pl->s));
   const State& hs = back.hs;
-  SNMF_TRY(start_check(back.bad, "W0"));
+  SNMF_TRY(start_check(pl, back.bad));
   const double hz = snmf_clock_rate_hz();
   if (hs.trace_len > 0 && trace) {
     HIP_TRY(hipMemcpyAsync(trace, pl->trace, (size_t)hs.trace_len * kTraceFields * 8,
@@ -662,22 +664,28 @@ snmf_status plan_solve(snmf_plan* pl, const void* W0, void* W_out, void* Ht_out,
     HIP_TRY(hipEventRecord(pl->ev_in, user));
     HIP_TRY(hipStreamWaitEvent(pl->s, pl->ev_in, 0));
   }
-  auto copy = [&](CopyTab& t, bool check, unsigned* bad) {
-    if (pl->prec == SNMF_F64) launch_copy<double>(t, check, bad, pl->s);
-    else launch_copy<float>(t, check, bad, pl->s);
+  if (++pl->seq == 0) {
+    HIP_TRY(hipMemsetAsync(pl->bad(), 0, sizeof(uint64_t), pl->s));
+    pl->seq = 1;
+  }
+  uint64_t* const bad = pl->p.validate ? pl->bad() : nullptr;
+  auto copy = [&](CopyTab& t, bool check) {
+    if (pl->prec == SNMF_F64) launch_copy<double>(t, check, bad, pl->seq, pl->s);
+    else launch_copy<float>(t, check, bad, pl->seq, pl->s);
   };
-  launch_reset_state(pl->st, pl->normA2, pl->s, pl->bad());
   CopyTab in{};
   in.n = 1;
   in.s[0] = {W0, pl->Wb, pl->Hb, n * r};
-  copy(in, true, pl->p.validate ? pl->bad() : nullptr);
+  copy(in, true);
   HIP_TRY(hipGetLastError());
   if (pl->p.validate && pl->p.max_outer > kDeferOuter) {
-    unsigned bad = kCopyOk;
-    HIP_TRY(hipMemcpyAsync(&bad, pl->bad(), sizeof(bad), hipMemcpyDeviceToHost, pl->s));
+    uint64_t word = 0;
+    HIP_TRY(hipMemcpyAsync(&word, bad, sizeof(word), hipMemcpyDeviceToHost, pl->s));
     HIP_TRY(hipStreamSynchronize(pl->s));
-    SNMF_TRY(start_check(bad, "W0"));
+    SNMF_TRY(start_check(pl, word));
   }
+  launch_reset_state(pl->st, pl->normA2, pl->s, bad, pl->seq);  // the solve's clock starts here
+  HIP_TRY(hipGetLastError());
   const int every = std::max(1, pl->p.check_every);
   auto capture = [&](int iters, hipGraph_t* g, hipGraphExec_t* ge) -> snmf_status {
     HIP_TRY(hipStreamBeginCapture(pl->s, hipStreamCaptureModeThreadLocal));
@@ -725,7 +733,7 @@ snmf_status plan_solve(snmf_plan* pl, const void* W0, void* W_out, void* Ht_out,
   out.n = 2;
   out.s[0] = {pl->Wb, W_out, nullptr, n * r};
   out.s[1] = {pl->Hb, Ht_out, nullptr, n * r};
-  copy(out, false, pl->bad());
+  copy(out, false);
   HIP_TRY(hipGetLastError());
   snmf_status rs = read_info(pl, info, trace);
   if (user) {

@@ -10,6 +10,7 @@ point must lie inside the envelope of oracle runs from rounding-level perturbed 
 """
 import json
 import os
+import time
 
 import numpy as np
 import pytest
@@ -498,3 +499,91 @@ def test_batch_start_check_many_problems(S):
             with pytest.raises(S.SnmfError) as e:
                 b.solve(bad)
             assert e.value.name == name
+
+
+def _plan_of_format(S, fmt, max_outer, **kw):
+    n, r = 1500, 7
+    g = torch.Generator(device="cpu").manual_seed(9)
+    W0 = torch.rand((n, r), generator=g).to(DEV)
+    prm = S.params(lam=1.0, max_outer=max_outer, check_every=1 << 30,
+                   gamma=0.2 if fmt == "laplacian" else 0.0, **kw)
+    if fmt == "lowrank":
+        U = torch.linalg.qr(torch.rand((n, 12), generator=g))[0].contiguous().to(DEV)
+        return S.Plan(S.lowrank(U, torch.linspace(9.0, 1.0, 12, dtype=torch.float64).to(DEV)), r,
+                      prm), W0
+    a = gen.random_symmetric_csr(n, 8.0, 5)
+    L = None
+    if fmt == "laplacian":
+        L = S.csr_from_scipy(sp.csr_matrix(sp.eye(n) + sp.csr_matrix(a > 0) * -0.01), torch.float32)
+    return S.Plan(S.csr_from_scipy(a, torch.float32), r, prm, L), W0
+
+
+@pytest.mark.parametrize("fmt", ["csr", "laplacian", "lowrank"])
+@pytest.mark.parametrize("max_outer", [3, 100])
+def test_start_check_of_every_format(S, fmt, max_outer):
+    """As above for the other formats of A and with the Laplacian term."""
+    pl, W0 = _plan_of_format(S, fmt, max_outer)
+    with pl:
+        for bad, name in ((float("inf"), "E_NONFINITE"), (-1.0, "E_NEGATIVE")):
+            Wb = W0.clone()
+            Wb[700, 3] = bad
+            out = [torch.full_like(W0, 7.0) for _ in range(2)]
+            with pytest.raises(S.SnmfError) as e:
+                pl.solve(Wb, *out)
+            assert e.value.name == name
+            assert all(bool((o == 7.0).all()) for o in out)
+        got = pl.solve(W0)
+    ref, _ = _plan_of_format(S, fmt, max_outer)
+    with ref:
+        ref = ref.solve(W0)
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+
+
+def test_bad_start_ends_the_solve(S):
+    """A start found bad by the check of a short solve ends it: its launches return at once
+    (a negative entry alone would let the iteration run; both runs are the best of 8)."""
+    n, r = 6000, 32
+    g = torch.Generator(device="cpu").manual_seed(3)
+    W = torch.rand((n, r), generator=g).to(DEV)
+    A = W @ W.T
+    W0 = torch.rand((n, r), generator=g).to(DEV)
+    Wb = W0.clone()
+    Wb[0, 0] = -1e-3
+
+    def best(pl, w):
+        t = []
+        for _ in range(8):
+            torch.cuda.synchronize()
+            a = time.perf_counter()
+            try:
+                pl.solve(w, trace=False)
+            except S.SnmfError as e:
+                assert e.name == "E_NEGATIVE"
+            t.append(time.perf_counter() - a)
+        return min(t)
+
+    with S.Plan(S.dense(0.5 * (A + A.T)), r, S.params(lam=1.0, max_outer=64)) as pl:
+        good, bad = best(pl, W0), best(pl, Wb)
+    assert bad <= 0.5 * good, (bad, good)
+
+
+@pytest.mark.parametrize("kind", ["plan", "batch"])
+def test_seconds_do_not_count_the_start_check(S, kind):
+    """info.seconds and the trace's ticks start after the start is copied and checked: with and
+    without the check (whose host wait takes some 20 us) the shortest of 40 tiny solves agree
+    to 15%."""
+    g = torch.Generator(device="cpu").manual_seed(1)
+    W = torch.rand((40, 3), generator=g).to(DEV)
+    A, W0 = S.dense(0.5 * (W @ W.T + (W @ W.T).T)), torch.rand((40, 3), generator=g).to(DEV)
+    best = []
+    for validate in (0, 1):
+        prm = S.params(lam=1.0, max_outer=1 if kind == "batch" else 100, inner_iters=1,
+                       validate=validate)
+        if kind == "batch":
+            with S.Batch([A], [3], prm, 1) as b:
+                best.append(min(b.solve([W0[None].contiguous()])[2][0]["seconds"]
+                                for _ in range(40)))
+        else:
+            with S.Plan(A, 3, prm) as pl:
+                best.append(min(pl.solve(W0)[2]["trace"][0][5] for _ in range(40)))
+    assert best[1] <= 1.15 * best[0], best
