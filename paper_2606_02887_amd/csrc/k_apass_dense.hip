@@ -720,13 +720,13 @@ template void launch_sum_parts<double>(const double*, int, int64_t, double*, int
 // Tiles of 16 rows (32 from n = 4096: half the reads of P, 256 tiles still fill the chip) and
 // K splits up to two workgroups per CU, of at least 128 columns (two 16-column blocks per
 // wavefront: a shorter one is all pipeline start) and at most 8 (their panels are read back).
-DenseSplit plan_dense_f64(int64_t n) {
+DenseSplit plan_dense_f64(int64_t n, int max_split) {
   DenseSplit d;
   d.wide = n >= 4096;
   d.gx = d.wide ? (n + 31) / 32 : (n + 15) / 16;
   int64_t ks = 512 / d.gx;
   if (ks > n / 128) ks = n / 128;
-  if (ks > 8) ks = 8;
+  if (ks > max_split) ks = max_split;
   if (ks < 1) ks = 1;
   d.kchunk = ((n + ks - 1) / ks + 63) / 64 * 64;
   d.ksplit = (int)((n + d.kchunk - 1) / d.kchunk);

@@ -90,7 +90,7 @@ void launch_split_pt_stack(const float* P, int64_t n, int r, int S, int64_t ldp,
 
 template <typename T>
 void launch_sum_parts(const T* part, int ks, int64_t stride, T* out, int64_t N, hipStream_t s);
-DenseSplit plan_dense_f64(int64_t n);  // wide: tiles of 32 rows instead of 16
+DenseSplit plan_dense_f64(int64_t n, int max_split = 8);  // wide: tiles of 32 rows, not 16
 // With rj.G set, rho is computed in the same launch.
 void launch_apass_f64(const double* A, int64_t lda, const double* P, int64_t n, int r,
                       const DenseSplit& d, double* Bpart, int64_t pstride, const State* st,

@@ -507,6 +507,7 @@ snmf_status plan_init(snmf_plan* pl, const snmf_matrix* A, int32_t r, const snmf
   if (fused) add(&pl->gs, nr);
   pl->grid = inner_grid(n, r, (int)pl->esz, fused);
   add(&pl->D, nr);
+  const int bpart = nreq;
   add(&pl->Bpart, nr * ksplit);
   if (lap) {
     add(&pl->LT, nr);
@@ -538,6 +539,14 @@ snmf_status plan_init(snmf_plan* pl, const snmf_matrix* A, int32_t r, const snmf
   }
   size_t total = 0;
   for (int q = 0; q < nreq; ++q) total += req[q].second;
+  // the FP64 product's K splits are a matter of speed: no solve is refused for their panels
+  while (fixed_pool && total > fixed_bytes && A->fmt == SNMF_DENSE && pl->prec == SNMF_F64 &&
+         pl->ds.ksplit > 1) {
+    pl->ds = plan_dense_f64(n, pl->ds.ksplit - 1);
+    total -= req[bpart].second;
+    req[bpart].second = (nr * pl->ds.ksplit + 255) / 256 * 256;
+    total += req[bpart].second;
+  }
   if (fixed_pool) {
     if (total > fixed_bytes)
       return fail(SNMF_E_SHAPE, "the solve needs " + std::to_string(total) +

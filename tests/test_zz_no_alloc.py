@@ -68,3 +68,20 @@ def test_noalloc_refuses_what_does_not_fit(S):
     with pytest.raises(S.SnmfError) as e:
         S.solve_noalloc(S.dense(A), W0, S.params(prec=S.BF16X3, max_outer=1))
     assert e.value.name == "E_UNSUPPORTED"
+
+
+def test_noalloc_keeps_its_limit_in_f64(S):
+    """The split-K panels of the dense FP64 product are a matter of speed: a solve that fits the
+    array without them (here it is the trace of max_outer records that fills it) runs."""
+    n, r = 1000, 64
+    g = torch.Generator(device="cpu").manual_seed(2)
+    W = torch.rand((n, r), generator=g, dtype=torch.float64).to(DEV)
+    W0 = torch.rand((n, r), generator=g, dtype=torch.float64).to(DEV)
+    A = S.dense((0.5 * (W @ W.T + (W @ W.T).T)).contiguous())
+    room = (64 << 20) - 8 * n * r * 8 - (2 << 20)     # 2 MiB for what does not grow with n
+    prm = dict(lam=1.0, prec=S.F64, max_outer=room // 80, target_res=10.0, check_every=1)
+    W1, H1, i1 = S.solve_noalloc(A, W0, S.params(**prm), trace=False)
+    assert i1["status"] == 0 and i1["outer"] == i1["converged_at"] == 1
+    W2, H2, i2 = S.solve(A, W0, S.params(**{**prm, "max_outer": 8}), trace=False)
+    assert (W1 - W2).abs().max() <= 1e-10 * W2.abs().max()
+    assert (H1 - H2).abs().max() <= 1e-10 * H2.abs().max()
