@@ -44,10 +44,12 @@ __host__ __device__ constexpr int inner_occupancy() {
 
 // The fused kernels (k_init with the direction, k_advance) hold more values per thread:
 // bounded to 168 registers they spill at RP <= 32, so they are built for two workgroups
-// per CU, and a plan that uses them caps its grid there (inner_grid).
+// per CU, and a plan that uses them caps its grid there (inner_grid).  FP64 at RP = 8 needs
+// the bound too: unbounded it takes one or three registers too many for two workgroups per CU
+// (n = 200000, r = 8: an outer iteration with a low-rank A 1115 us, 1018 so, CSR 545 and 445).
 template <typename T, int RP>
 __host__ __device__ constexpr int fused_occupancy() {
-  return (sizeof(T) == 4 && RP <= 32) ? 2 : 1;
+  return (sizeof(T) == 4 && RP <= 32) || (sizeof(T) == 8 && RP == 8) ? 2 : 1;
 }
 
 template <int RP>
