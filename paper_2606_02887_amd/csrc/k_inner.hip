@@ -513,6 +513,7 @@ __device__ __forceinline__ void init_body(
   bool first = true;
   for (int64_t t = lc.bid; t < ntiles; t += lc.nb) {
     const int64_t row0 = t * TM, tb = row0 * r;
+    const int left = (int)(n - row0 < TM ? n - row0 : TM);
     const T* __restrict__ Bt = tile_ptr(Bpart, tb);
     T x[8], cv[8], pv[8], lx[8];
     bool ok[8];
@@ -521,7 +522,7 @@ __device__ __forceinline__ void init_body(
     // its partials in panel order
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
-      ok[p] = row0 + lr[p] < n && cl[p] < r;
+      ok[p] = lr[p] < left && cl[p] < r;
       x[p] = ok[p] ? ldo(tile_ptr(X, tb), bo[p]) : T(0);
       pv[p] = ok[p] ? ldo(tile_ptr(P, tb), bo[p]) : T(0);
       lx[p] = (ok[p] && LX) ? ldo(tile_ptr(LX, tb), bo[p]) : T(0);
@@ -550,7 +551,10 @@ __device__ __forceinline__ void init_body(
       for (int p = 0; p < 8; ++p) b[p] += bs[p];
     }
 #pragma unroll
-    for (int p = 0; p < 8; ++p) cv[p] = b[p] + lam * pv[p];
+    for (int p = 0; p < 8; ++p) {
+      cv[p] = b[p] + lam * pv[p];
+      asm volatile("" : "+v"(cv[p]));  // formed here: left to each element's use below, its wait
+    }                                  // for pv would wait for the stores before it as well
     if (first) store_G<T, RP>(sm.G, gv);
     first = false;
     __syncthreads();
@@ -1090,10 +1094,11 @@ __device__ __forceinline__ void step2_body(
   const T alpha_r = (T)st->alpha[k];
   T x[8], zz[8], dd[8], go[8], cv[8], pv[8], ls[8], lx[8];
   auto load_tile = [&](int64_t row0) {
+    const int left = (int)(n - row0 < TM ? n - row0 : TM);
     const int64_t tb = row0 * r;
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
-      const bool ok = row0 + lr[p] < n && cl[p] < r;
+      const bool ok = lr[p] < left && cl[p] < r;
       x[p] = ok ? ldo(tile_ptr(X, tb), bo[p]) : T(0);
       if constexpr (V == 2) zz[p] = ok ? ldo(tile_ptr(Z, tb), bo[p]) : T(0);
       if (V == 2 || !rd) dd[p] = (ok && phase != 2) ? ldo(tile_ptr(D, tb), bo[p]) : T(0);
@@ -1170,6 +1175,7 @@ __device__ __forceinline__ void step2_body(
   double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
   for (int64_t t = lc.bid; t < ntiles; t += lc.nb) {
     const int64_t row0 = t * TM;
+    const int left = (int)(n - row0 < TM ? n - row0 : TM);
     if (t != lc.bid) load_tile(row0);
     T xn[8];
     __syncthreads();
@@ -1177,7 +1183,7 @@ __device__ __forceinline__ void step2_body(
       // D as step 1 formed it: grad f(Z) = g + (Z - X)(G + lam I), then the projection
 #pragma unroll
       for (int p = 0; p < 8; ++p) {
-        const bool ok = row0 + lr[p] < n && cl[p] < r;
+        const bool ok = lr[p] < left && cl[p] < r;
         sm.a[lr[p] * L::YP + cl[p]] = ok ? zz[p] - x[p] : T(0);
       }
       __syncthreads();
@@ -1185,14 +1191,14 @@ __device__ __forceinline__ void step2_body(
       tile_gemm<T, RP>(sm.a, sm.G, dzg);
 #pragma unroll
       for (int p = 0; p < 8; ++p) {
-        const bool ok = row0 + lr[p] < n && cl[p] < r;
+        const bool ok = lr[p] < left && cl[p] < r;
         const T gz = grad_at_z(go[p], dzg[p], lam, zz[p] - x[p]);
         dd[p] = ok ? second_dir(zz[p], gz, alpha_r) : T(0);
       }
     }
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
-      const bool ok = row0 + lr[p] < n && cl[p] < r;
+      const bool ok = lr[p] < left && cl[p] < r;
       if (phase == 2) {
         xn[p] = zz[p];
       } else {
@@ -1206,7 +1212,7 @@ __device__ __forceinline__ void step2_body(
     const int64_t tb = row0 * r;
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
-      if (row0 + lr[p] < n && cl[p] < r) {
+      if (lr[p] < left && cl[p] < r) {
         const T s = xn[p] - x[p];
         T gn = next_grad(go[p], sg[p], lam, s);
         if (lap) gn += gam * ls[p];
