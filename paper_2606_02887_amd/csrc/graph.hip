@@ -24,27 +24,40 @@ snmf_status check_points(const void* X, int64_t n, int dim, int K, int prec) {
   return SNMF_OK;
 }
 
-// E_NONFINITE unless every coordinate is finite (flag: one device unsigned of scratch).
-snmf_status check_finite(const void* X, int64_t count, int prec, unsigned* flag, hipStream_t s) {
-  HIP_TRY(hipMemsetAsync(flag, 0, sizeof(unsigned), s));
-  if (prec == SNMF_F64)
-    launch_count_nonfinite<double>((const double*)X, count, flag, s);
-  else
-    launch_count_nonfinite<float>((const float*)X, count, flag, s);
+// E_NONFINITE unless every coordinate is finite, then the neighbours.  nrm: n doubles, flag:
+// kFlagWords device words of scratch.  The norms that the screened search needs are formed
+// before the host wait of the check, which brings their near counts along.
+constexpr int kFlagWords = 8, kNearWord = 4;
+template <typename T>
+snmf_status check_points_finite(const T* X, int64_t n, int dim, unsigned* flag, double* nrm,
+                                bool* inseparable, hipStream_t s) {
+  const size_t bytes = (nrm ? kFlagWords : 1) * sizeof(unsigned);
+  HIP_TRY(hipMemsetAsync(flag, 0, bytes, s));
+  launch_count_nonfinite<T>(X, n * dim, flag, s);
+  if (nrm) launch_knn_norms<T>(X, n, dim, nrm, flag + kNearWord, s);
   HIP_TRY(hipGetLastError());
-  unsigned bad = 0;
-  HIP_TRY(hipMemcpyAsync(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost, s));
+  unsigned f[kFlagWords] = {};
+  HIP_TRY(hipMemcpyAsync(f, flag, bytes, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  if (bad) return fail(SNMF_E_NONFINITE, "X has NaN/Inf entries");
+  if (f[0]) return fail(SNMF_E_NONFINITE, "X has NaN/Inf entries");
+  *inseparable = knn_inseparable(f + kNearWord, n);
   return SNMF_OK;
 }
 
-void knn_any(const void* X, int64_t n, int dim, int K, int prec, double* nrm, int32_t* nbr,
-             hipStream_t s) {
+snmf_status knn_any(const void* X, int64_t n, int dim, int K, int prec, double* nrm,
+                    unsigned* flag, int32_t* nbr, hipStream_t s) {
+  if (!knn_screened(n, dim, K, elt_size(prec))) nrm = nullptr;
+  bool inseparable = false;
+  SNMF_TRY(prec == SNMF_F64
+               ? check_points_finite<double>((const double*)X, n, dim, flag, nrm, &inseparable, s)
+               : check_points_finite<float>((const float*)X, n, dim, flag, nrm, &inseparable, s));
+  if (inseparable) nrm = nullptr;
   if (prec == SNMF_F64)
     launch_knn<double>((const double*)X, n, dim, K, nrm, nbr, s);
   else
     launch_knn<float>((const float*)X, n, dim, K, nrm, nbr, s);
+  HIP_TRY(hipGetLastError());
+  return SNMF_OK;
 }
 
 }  // namespace
@@ -56,11 +69,10 @@ snmf_status snmf_knn(const void* X, int64_t n, int32_t dim, int32_t K, int32_t p
   SNMF_TRY(check_points(X, n, dim, K, prec));
   if (!nbr_out) return fail(SNMF_E_ARG, "nbr_out is required");
   hipStream_t s = (hipStream_t)stream;
-  DevBuf pool;  // the flag of the check, the squared norms
+  DevBuf pool;  // the flags of the check, the squared norms
   HIP_TRY(hipMalloc(&pool.p, 256 + (size_t)n * 8));
-  SNMF_TRY(check_finite(X, n * dim, prec, (unsigned*)pool.p, s));
-  knn_any(X, n, dim, K, prec, (double*)((char*)pool.p + 256), nbr_out, s);
-  HIP_TRY(hipGetLastError());
+  SNMF_TRY(knn_any(X, n, dim, K, prec, (double*)((char*)pool.p + 256), (unsigned*)pool.p, nbr_out,
+                   s));
   HIP_TRY(hipStreamSynchronize(s));
   return SNMF_OK;
 }
@@ -88,14 +100,13 @@ snmf_status snmf_knn_graph(const void* X, int64_t n, int32_t dim, int32_t K, dou
   DevBuf pool;
   HIP_TRY(hipMalloc(&pool.p, b_nbr + b_cnt + b_cur + b_deg + b_v + 256));
   char* base = (char*)pool.p;
-  SNMF_TRY(check_finite(X, n * dim, prec, (unsigned*)(base + b_nbr + b_cnt + b_cur + b_deg + b_v),
-                        s));
   int32_t* nbr = (int32_t*)base;
   unsigned* cnt = (unsigned*)(base + b_nbr);
   unsigned long long* cursor = (unsigned long long*)(base + b_nbr + b_cnt);
   double* deg = (double*)(base + b_nbr + b_cnt + b_cur);
   double* v = (double*)(base + b_nbr + b_cnt + b_cur + b_deg);
-  knn_any(X, n, dim, K, prec, deg, nbr, s);  // deg is free until the values
+  SNMF_TRY(knn_any(X, n, dim, K, prec, deg,  // deg is free until the values
+                   (unsigned*)(base + b_nbr + b_cnt + b_cur + b_deg + b_v), nbr, s));
   HIP_TRY(hipMemsetAsync(cnt, 0, (size_t)n * 4, s));
   launch_knn_pattern_count(nbr, n, K, diag, cnt, rowptr_out, s);
   launch_knn_pattern_fill(nbr, n, K, diag, rowptr_out, col_out, cursor, (int32_t*)v, s);

@@ -417,11 +417,8 @@ __global__ __launch_bounds__(kThreads, KS <= 4 ? 5 : 1) void k_knn(const T* __re
 // pairs in a sorted register list (a candidate that ties with a kept one goes after it,
 // so within a lane ties keep the lower index).  The wave then takes the K smallest over
 // all lanes by K rounds of a (distance, index) minimum across lanes, the winning lane
-// dropping its head.  The point itself is skipped.  Up to kKnnWaveMax points: the whole chip
-// works on a search of some 20 us where k_knn has too few workgroups (per call, dim = 16,
-// K = 10: n = 1000 75 against 89 us, 2000 102 and 102, 3000 138 against 112; dim = 30,
-// K = 20, n = 1500: 123 against 144).
-constexpr int64_t kKnnWaveMax = 2000;
+// dropping its head.  The point itself is skipped.  Serves few points (knn_wave_max) and
+// points that the screen of k_knn cannot separate (knn_inseparable).
 template <typename T, int KB>
 __global__ __launch_bounds__(kThreads) void k_knn_wave(const T* __restrict__ X, int64_t n, int dim,
                                                        int K, int32_t* __restrict__ nbr) {
@@ -489,18 +486,36 @@ __global__ __launch_bounds__(kThreads) void k_knn_wave(const T* __restrict__ X, 
   }
 }
 
-// |x_i|^2 in FP64; -inf where a product could overflow.
+// |x_i|^2 in FP64; -inf where a product could overflow.  near[q] += points within 1.25 err of
+// probe q, kKnnProbes points spread over the array: where that is most of them the screen
+// separates nothing (knn_inseparable).
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_knn_norms(const T* __restrict__ X, int64_t n,
-                                                        int dim, double* __restrict__ nrm) {
+                                                        int dim, double* __restrict__ nrm,
+                                                        unsigned* __restrict__ near) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= n) return;
-  double d = 0.0;
+  const bool in = i < n;
+  const T* __restrict__ xi = X + (in ? i : n - 1) * dim;
+  double d = 0.0, pn[kKnnProbes], pd[kKnnProbes];
+#pragma unroll
+  for (int q = 0; q < kKnnProbes; ++q) pn[q] = pd[q] = 0.0;
   for (int c = 0; c < dim; ++c) {
-    const double t = (double)X[i * dim + c];
+    const double t = (double)xi[c];
     d = __builtin_fma(t, t, d);
+#pragma unroll
+    for (int q = 0; q < kKnnProbes; ++q) {
+      const double p = (double)X[n / kKnnProbes * q * dim + c];
+      pn[q] = __builtin_fma(p, p, pn[q]);
+      pd[q] = __builtin_fma(t - p, t - p, pd[q]);
+    }
   }
-  nrm[i] = d < 1e290 ? d : -__builtin_inf();
+  if (in) nrm[i] = d < 1e290 ? d : -__builtin_inf();
+  const double c1 = 1.25 * 4.0 * (dim + 4) * 0x1p-53;
+#pragma unroll
+  for (int q = 0; q < kKnnProbes; ++q) {
+    const unsigned long long b = __ballot(in && (d >= 1e290 || pd[q] <= c1 * (d + pn[q])));
+    if (b && (threadIdx.x & 63) == 0) atomicAdd(&near[q], (unsigned)__popcll(b));
+  }
 }
 
 // ----------------------------------------------------------------------------- pattern
@@ -736,9 +751,40 @@ static void knn_go(const T* X, int64_t n, int dim, int K, const double* nrm, int
   hipLaunchKernelGGL((k_knn<T, KS, FULL>), dim3((unsigned)((n + 15) / 16)), dim3(kThreads), lds, s,
                      X, n, dim, K, kb, nrm, nbr);
 }
+// Points up to which one wavefront per query is the faster search: the whole chip works on
+// some 20 us where k_knn has too few workgroups (a call screened / with a wavefront per query,
+// n = 1000, 2100, 2500, 3000, 4000: FP32 dim = 10, K = 10 1.31 1.00 0.93 0.91 0.73, K = 16 1.48
+// 1.16 1.08 1.05 0.85, K = 20 1.56 1.08 1.04 0.99 0.76).  Lists of more than 32 cost the wavefront
+// most of its registers (K = 40: 1.20 0.59 0.60 0.58 0.43), long rows its uncoalesced loads,
+// where the screen loads whole blocks of 16 coordinates (FP64, dim = 32, K = 16: 1.33 0.59 0.53
+// 0.48 0.32; FP64, dim = 24, K = 20: 1.61 1.09 1.02 0.96 0.68).
+static int64_t knn_wave_max(int dim, int K, size_t esz) {
+  if (K > 32 || dim > 24 || (dim == 16 && esz == 8)) return 2000;
+  return K <= 10 ? 2400 : K <= 16 ? 3000 : 2600;
+}
+
+bool knn_screened(int64_t n, int dim, int K, size_t esz) { return n > knn_wave_max(dim, K, esz); }
+
+// More than half of the points lie within the rounding of the screen of one of the probes:
+// nearly every pair would pass it and be formed twice (n = 20000, dim = 16, K = 10, all points
+// equal: 2166 us screened, 1432 with a wavefront per query; FP32 points of unit spread around
+// 1e7: 3211 and 2462).
+bool knn_inseparable(const unsigned* near, int64_t n) {
+  unsigned most = 0;
+  for (int q = 0; q < kKnnProbes; ++q) most = near[q] > most ? near[q] : most;
+  return 2 * (int64_t)most > n;
+}
+
 template <typename T>
-void launch_knn(const T* X, int64_t n, int dim, int K, double* nrm, int32_t* nbr, hipStream_t s) {
-  if (n <= kKnnWaveMax) {
+void launch_knn_norms(const T* X, int64_t n, int dim, double* nrm, unsigned* near, hipStream_t s) {
+  hipLaunchKernelGGL(k_knn_norms<T>, dim3((unsigned)((n + kThreads - 1) / kThreads)),
+                     dim3(kThreads), 0, s, X, n, dim, nrm, near);
+}
+
+template <typename T>
+void launch_knn(const T* X, int64_t n, int dim, int K, const double* nrm, int32_t* nbr,
+                hipStream_t s) {
+  if (!nrm) {
     const dim3 grid((unsigned)((n + kThreads / kWave - 1) / (kThreads / kWave))), block(kThreads);
     if (K <= 16)
       hipLaunchKernelGGL((k_knn_wave<T, 16>), grid, block, 0, s, X, n, dim, K, nbr);
@@ -748,8 +794,6 @@ void launch_knn(const T* X, int64_t n, int dim, int K, double* nrm, int32_t* nbr
       hipLaunchKernelGGL((k_knn_wave<T, 64>), grid, block, 0, s, X, n, dim, K, nbr);
     return;
   }
-  hipLaunchKernelGGL(k_knn_norms<T>, dim3((unsigned)((n + kThreads - 1) / kThreads)),
-                     dim3(kThreads), 0, s, X, n, dim, nrm);
   if (dim == 16) knn_go<T, 4, true>(X, n, dim, K, nrm, nbr, s);
   else if (dim == 32) knn_go<T, 8, true>(X, n, dim, K, nrm, nbr, s);
   else if (dim == 48) knn_go<T, 12, true>(X, n, dim, K, nrm, nbr, s);
@@ -791,8 +835,12 @@ void launch_knn_values(const T* X, int64_t n, int dim, double sigma, int laplaci
                      col, (const double*)v, (const double*)deg, val);
 }
 
-template void launch_knn<float>(const float*, int64_t, int, int, double*, int32_t*, hipStream_t);
-template void launch_knn<double>(const double*, int64_t, int, int, double*, int32_t*, hipStream_t);
+template void launch_knn_norms<float>(const float*, int64_t, int, double*, unsigned*, hipStream_t);
+template void launch_knn_norms<double>(const double*, int64_t, int, double*, unsigned*, hipStream_t);
+template void launch_knn<float>(const float*, int64_t, int, int, const double*, int32_t*,
+                                hipStream_t);
+template void launch_knn<double>(const double*, int64_t, int, int, const double*, int32_t*,
+                                 hipStream_t);
 template void launch_knn_values<float>(const float*, int64_t, int, double, int, const int64_t*,
                                        const int32_t*, double*, double*, float*, hipStream_t);
 template void launch_knn_values<double>(const double*, int64_t, int, double, int, const int64_t*,

@@ -219,8 +219,13 @@ void launch_sketch_select(const double* ev, const double* V, int w, int k, int s
 template <typename T>
 void launch_count_nonfinite(const T* X, int64_t count, unsigned* flag, hipStream_t s);
 template <typename T>
-void launch_knn(const T* X, int64_t n, int dim, int K, double* nrm,  // nrm: n doubles of scratch
-                int32_t* nbr, hipStream_t s);
+void launch_knn_norms(const T* X, int64_t n, int dim, double* nrm, unsigned* near, hipStream_t s);
+template <typename T>  // nrm: of launch_knn_norms, or nullptr for the search without a screen
+void launch_knn(const T* X, int64_t n, int dim, int K, const double* nrm, int32_t* nbr,
+                hipStream_t s);
+constexpr int kKnnProbes = 4;  // near counts of launch_knn_norms (zero before it)
+bool knn_screened(int64_t n, int dim, int K, size_t esz);  // by size: the screened search
+bool knn_inseparable(const unsigned* near, int64_t n);     // by data: not the screened one
 void launch_knn_pattern_count(const int32_t* nbr, int64_t n, int K, int diag, unsigned* cnt,
                               int64_t* rowptr, hipStream_t s);
 void launch_knn_pattern_fill(const int32_t* nbr, int64_t n, int K, int diag,

@@ -80,6 +80,25 @@ def test_knn_edges(S, n, dim, K, kind):
         assert np.array_equal(nbr, idx)
 
 
+@pytest.mark.parametrize("n,dim,K", [(2001, 32, 17), (2401, 3, 3), (2402, 5, 10), (2601, 9, 20),
+                                     (2617, 17, 17), (3001, 16, 16), (2003, 33, 11), (2049, 4, 64),
+                                     (2003, 33, 33), (2100, 64, 40), (2064, 48, 5)])
+@pytest.mark.parametrize("kind", ["lattice", "thirds", "equal", "far", "spread"])
+def test_knn_edges_fp32(S, n, dim, K, kind):
+    """As above in FP32, just past the sizes from which the search is screened: every width of
+    the coordinates' blocks, both forms of their loads, one and two sets of first limits;
+    data that the screen separates (spread), that pass it in part (lattice, thirds: three
+    points many times over) and that it hands to the search without a screen."""
+    rng = np.random.default_rng(n * 64 + dim)
+    X = {"lattice": rng.integers(0, 3, (n, dim)).astype(np.float64),
+         "thirds": rng.standard_normal((3, dim))[np.arange(n) % 3],
+         "equal": np.full((n, dim), 0.3), "far": 1e6 + rng.random((n, dim)),
+         "spread": rng.standard_normal((n, dim))}[kind]
+    X = torch.from_numpy(X).to(DEV, torch.float32)
+    idx, _ = O.knn(X.double().cpu().numpy(), K)
+    assert np.array_equal(S.knn(X, K).cpu().numpy(), idx)
+
+
 def test_knn_graph_long_rows(S):
     """A star: the hub's row of the union holds every point (the sort of rows past 64)."""
     n = 700
