@@ -108,7 +108,7 @@ __device__ __forceinline__ constexpr int knn_coord(int step, int g) {
 }
 
 template <typename T, int KS, bool FULL>
-__global__ __launch_bounds__(kThreads, KS <= 4 ? 5 : 1) void k_knn(const T* __restrict__ X, int64_t n, int dim,
+__global__ __launch_bounds__(kThreads, KS <= 4 ? 5 : KS == 8 && !FULL ? 4 : 1) void k_knn(const T* __restrict__ X, int64_t n, int dim,
                                                   int K, int kb, const double* __restrict__ nrm,
                                                   int32_t* __restrict__ nbr) {
   extern __shared__ __attribute__((aligned(16))) unsigned char knn_lds[];
@@ -178,12 +178,12 @@ __global__ __launch_bounds__(kThreads, KS <= 4 ? 5 : 1) void k_knn(const T* __re
     if (lane < c) {
       j = qu[m * kKnnQueue + lane];
       d = distance(i, j);
-      if (!(d < inf) || !knn_less(d, j, kd, ki)) {
+      if (!knn_less(d, j, kd, ki)) {  // (an infinite distance comes before an empty place)
         d = inf;
         j = 0x7fffffff;
       }
     }
-    if (!__any(d < inf)) return;
+    if (!__any(j != 0x7fffffff)) return;
     if (c <= 16)
       knn_sort<16>(d, j);
     else
@@ -371,10 +371,6 @@ __global__ __launch_bounds__(kThreads, KS <= 4 ? 5 : 1) void k_knn(const T* __re
       j = ((const int32_t*)(knn_lds + (size_t)w * knn_lds_wave(kb) + (size_t)16 * kb *
                             12))[m * kKnnQueue + at];
       d = distance(q0 + m, j);
-      if (!(d < inf)) {
-        d = inf;
-        j = 0x7fffffff;
-      }
     }
     knn_sort<64>(d, j);
     if (lane < K) nbr[(q0 + m) * K + lane] = j;
@@ -445,6 +441,9 @@ __global__ __launch_bounds__(kThreads) void k_knn_wave(const T* __restrict__ X, 
       const double t = sq[wv][c] - (double)xj[c];
       d = __builtin_fma(t, t, d);
     }
+    // a distance beyond the largest double counts as that: an infinite one would not come
+    // before an empty place
+    d = __builtin_fmin(d, 1.7976931348623157e308);
     if (d < dist[KB - 1]) {
 #pragma unroll
       for (int q = KB - 1; q > 0; --q) {

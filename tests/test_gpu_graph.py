@@ -99,6 +99,29 @@ def test_knn_edges_fp32(S, n, dim, K, kind):
     assert np.array_equal(S.knn(X, K).cpu().numpy(), idx)
 
 
+@pytest.mark.parametrize("n,dim,K", [(300, 3, 7), (2500, 16, 10), (2500, 9, 5), (2100, 32, 40)])
+@pytest.mark.parametrize("part", [1, 3])
+def test_knn_distances_beyond_the_largest_double(S, n, dim, K, part):
+    """Finite FP64 points whose squared distances overflow (all of them, or a third): the lists
+    still hold K other points, those at overflowing distances by index, and the graph is
+    that of the lists."""
+    rng = np.random.default_rng(n + dim)
+    X = rng.standard_normal((n, dim))
+    X[::part] *= 1e200
+    X[5] = X[8]                           # a distance of zero among them
+    Xt = torch.from_numpy(X).to(DEV)
+    nbr = S.knn(Xt, K).cpu().numpy()
+    for i in np.unique(np.r_[0:20, rng.integers(0, n, 40), n - 1]):
+        with np.errstate(over="ignore"):
+            d = np.sum((X - X[i]) ** 2, axis=1)
+        order = np.lexsort((np.arange(n), d))
+        assert np.array_equal(nbr[i], order[order != i][:K]), i
+    rowptr, col, _ = (t.cpu().numpy() for t in S.knn_graph(Xt, K, laplacian=False).keep)
+    pairs = np.repeat(np.arange(n), K) * n + nbr.reshape(-1)
+    both = np.unique(np.r_[pairs, pairs % n * n + pairs // n])
+    assert np.array_equal(np.repeat(np.arange(n), np.diff(rowptr)) * n + col, both)
+
+
 def test_knn_graph_long_rows(S):
     """A star: the hub's row of the union holds every point (the sort of rows past 64)."""
     n = 700
