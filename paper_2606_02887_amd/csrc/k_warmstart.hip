@@ -447,11 +447,14 @@ template void launch_ws_spa_only<double>(const BInst*, int, const double*, doubl
 // and M2 read four hidden units at a time.  What bounds it is latency: one thread per row
 // and all of its 2 H r FMAs gave a minibatch of 4096 rows 16 workgroups, 42.8 us at r = 16;
 // 32-row tiles give it 128, 13.7 us with the loss sums of a former kernel of its own.
+// OCC: workgroups per CU it is built for.  At RP = 64 two of them cost 168 bytes of scratch,
+// which pays from more than one tile per CU on (mlp_fwd_go): r = 64, 4096 rows 29.0 us (32.8
+// with two), 32768 rows 112 (87), 1e6 rows 2247 (1431; one thread per row: 1966).
 constexpr int kMlpRows = 32;           // rows of a tile
 constexpr int kMlpPitch = kMlpHidden + 4;
 
-template <int RP>
-__global__ __launch_bounds__(kThreads) void k_mlp_fwd(MlpDev m, int64_t N,
+template <int RP, int OCC>
+__global__ __launch_bounds__(kThreads, OCC) void k_mlp_fwd(MlpDev m, int64_t N,
                                                       const float* __restrict__ C,
                                                       const float* __restrict__ row_scale,
                                                       float* __restrict__ Y, BMap bm,
@@ -775,13 +778,25 @@ static int mlp_fwd_grid(int64_t N) {
   return (int)(g < 1 ? 1 : (g > kMaxGrid ? kMaxGrid : g));
 }
 
+template <int RP>
+static void mlp_fwd_go(int grid, hipStream_t s, const MlpDev& m, int64_t N, const float* C,
+                       const float* row_scale, float* Y, const BMap& bm, const int32_t* idx,
+                       int64_t pool, const float* T, float* cache_a, float* cache_o,
+                       double* part) {
+  if (RP == 64 && grid > 256)
+    hipLaunchKernelGGL((k_mlp_fwd<RP, RP == 64 ? 2 : 1>), dim3(grid), dim3(kThreads), 0, s, m, N, C,
+                       row_scale, Y, bm, idx, pool, T, cache_a, cache_o, part);
+  else
+    hipLaunchKernelGGL((k_mlp_fwd<RP, 1>), dim3(grid), dim3(kThreads), 0, s, m, N, C, row_scale, Y,
+                       bm, idx, pool, T, cache_a, cache_o, part);
+}
+
 void launch_mlp_forward(const MlpDev& m, int64_t N, const float* C, const float* row_scale,
                         float* Y, const BMap& bm, int grid, hipStream_t s) {
   if (!bm.blk_inst) grid = mlp_fwd_grid(N);
   SNMF_DISPATCH_MLP(rank_pad(m.r),
-                    hipLaunchKernelGGL((k_mlp_fwd<RP>), dim3(grid), dim3(kThreads), 0, s, m, N, C,
-                                       row_scale, Y, bm, nullptr, 0, nullptr, nullptr, nullptr,
-                                       nullptr))
+                    mlp_fwd_go<RP>(grid, s, m, N, C, row_scale, Y, bm, nullptr, 0, nullptr, nullptr,
+                                   nullptr, nullptr))
 }
 
 void launch_mlp_train_step(const MlpDev& m, int64_t pool, int64_t B, const float* C,
@@ -789,9 +804,8 @@ void launch_mlp_train_step(const MlpDev& m, int64_t pool, int64_t B, const float
                            const MlpWork& w, hipStream_t s) {
   const int nparts = mlp_fwd_grid(B);
   SNMF_DISPATCH_MLP(rank_pad(m.r),
-                    hipLaunchKernelGGL((k_mlp_fwd<RP>), dim3(nparts), dim3(kThreads), 0, s, m, B,
-                                       C, nullptr, w.y, BMap{}, idx, pool, T, w.cache_a,
-                                       w.cache_o, w.part))
+                    mlp_fwd_go<RP>(nparts, s, m, B, C, nullptr, w.y, BMap{}, idx, pool, T, w.cache_a,
+                                   w.cache_o, w.part))
   // Row slabs of the gradient: as many as their FP64 partials fit the scratch (64 rows a
   // slab at r <= 16, 192 at r = 64) up to 128, whole 32-row tiles each.
   const int P = mlp_params(m.r);

@@ -351,3 +351,20 @@ def test_mlp_train_step_slabs(S, r, B):
         n = go[k].size
         assert nrel(g[at: at + n].reshape(go[k].shape), go[k]) <= 1e-4, k
         at += n
+
+
+@pytest.mark.parametrize("r", [33, 64])
+@pytest.mark.parametrize("N", [8192, 8193, 40000])
+def test_mlp_forward_many_rows(S, r, N):
+    """The forward of ranks above 32 on both sides of one 32-row tile per CU, and on more tiles
+    than workgroups.  A sum of at most 129 products in FP32 with BF16 weights as given."""
+    m = S.Mlp(_rand_init(r, 7 + r))
+    C = torch.from_numpy(np.random.default_rng(N).standard_normal((N, r))).to(DEV, torch.float32)
+    Y = m.forward(C).double().cpu().numpy()
+    prm = m.params()
+    bf = lambda a: torch.from_numpy(a).to(torch.bfloat16).double().numpy()
+    c = C.double().cpu().numpy()
+    o = c + np.maximum(c @ bf(prm["M1"]).T + prm["b1"], 0.0) @ bf(prm["M2"]).T + prm["b2"]
+    mag = np.abs(c) + (np.abs(c) @ np.abs(bf(prm["M1"])).T + np.abs(prm["b1"])) @ np.abs(
+        bf(prm["M2"])).T + np.abs(prm["b2"])
+    assert (np.abs(Y - np.maximum(o, 0.0)) <= (r + 128 + 4) * 2.0 ** -24 * mag).all()
