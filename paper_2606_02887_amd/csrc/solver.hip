@@ -506,7 +506,10 @@ snmf_status plan_init(snmf_plan* pl, const snmf_matrix* A, int32_t r, const snmf
   const bool fused = fused_inner_ok(*p);
   if (fused) add(&pl->gs, nr);
   pl->grid = inner_grid(n, r, (int)pl->esz, fused);
-  add(&pl->D, nr);
+  // D: only where a kernel stores it -- the Laplacian and naive H-steps, and step 1 of small
+  // problems (fused iterations form the direction again, and so does step 2 where the arrays
+  // are large).  The fixed array keeps its place, so that its limit stays where it is.
+  if (!fused || lap || p->naive || fixed_pool || (int64_t)nr < kRecomputeDBytes) add(&pl->D, nr);
   const int bpart = nreq;
   add(&pl->Bpart, nr * ksplit);
   if (lap) {

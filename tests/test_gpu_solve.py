@@ -587,3 +587,25 @@ def test_seconds_do_not_count_the_start_check(S, kind):
             with S.Plan(A, 3, prm) as pl:
                 best.append(min(pl.solve(W0)[2]["trace"][0][5] for _ in range(40)))
     assert best[1] <= 1.15 * best[0], best
+
+
+def test_plan_holds_no_direction_that_nothing_reads(S):
+    """A plan of fused iterations on large arrays keeps seven n x r arrays (W, Ht, C, g, Z, the
+    trial gradient, the product), and a half-step without fusing runs on it too."""
+    n, r, ell = 200000, 32, 8
+    g = torch.Generator(device="cpu").manual_seed(8)
+    U = torch.linalg.qr(torch.rand((n, ell), generator=g))[0].contiguous().to(DEV)
+    A = S.lowrank(U, torch.linspace(9.0, 1.0, ell, dtype=torch.float64).to(DEV))
+    X = torch.rand((n, r), generator=g).to(DEV)
+    S.Plan(A, 2, S.params(lam=1.0)).close()          # what the first use of the library allocates
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    with S.Plan(A, r, S.params(lam=1.0, max_outer=1)) as pl:
+        used = free - torch.cuda.mem_get_info()[0]
+        X1 = X.clone()
+        pl.half_step(X1, X, False)
+    assert used <= 7.6 * n * r * 4, used
+    with S.Plan(A, r, S.params(lam=1.0, max_outer=1, fuse_inner=0)) as pl:
+        X2 = X.clone()
+        pl.half_step(X2, X, False)
+    assert torch.equal(X1, X2)
