@@ -121,7 +121,10 @@ typedef struct snmf_params {
                                 (requires project_update = 0)                            [0] */
   int32_t project_update;    /* 1: W_{k+1} = max(0, Z + phi beta D); 0: no projection     [1] */
   int32_t validate;    /* 1: check A >= 0, finite, W0 >= 0 finite, CSR structure        [1] */
-  int32_t use_graph;   /* 1: replay one outer iteration as a captured hipGraph           [1] */
+  int32_t use_graph;   /* 1: replay one outer iteration as a captured hipGraph, in plans and
+                          batches and in snmf_solve from 65 outer iterations on (below, its
+                          capture takes longer than it saves: direct launches, the same
+                          results); 0: direct launches                                   [1] */
   int32_t check_symmetry; /* 1: dense A must satisfy |a_ij - a_ji| <= 2^-20 max(|a_ij|, |a_ji|)
                           for all i, j, else SNMF_E_NOT_SYMMETRIC (one O(n^2) pass over A at
                           plan or batch creation); 0: not checked (CSR symmetry is checked
@@ -161,8 +164,8 @@ typedef struct snmf_info {
   double pg_norm;        /* ||min(W, grad_W f)||^2 + ||min(Ht, grad_Ht f)||^2, square root:
                             zero exactly at first-order stationary points (Section 3.1) */
   double objective;      /* f(W, H) */
-  double seconds;        /* device time from solve start to the last completed outer
-                            iteration */
+  double seconds;        /* device time from solve start (after the copy and check of W0) to
+                            the last completed outer iteration */
   double seconds_to_target; /* device time to converged_at, or -1 */
   double normA2;         /* ||A||_F^2 (surrogate norm sum(lam^2) for LOWRANK) */
 } snmf_info;
@@ -174,7 +177,9 @@ snmf_status snmf_params_default(snmf_params* p);
  * trace: optional host array of max_outer * SNMF_TRACE_FIELDS doubles; record i holds
  * {res_WH, res_WWt, sym_gap, pg_norm, objective, device_ticks, ls_evals, ls_exhausted,
  *  alpha, inner_total} after outer iteration i+1 (device_ticks at the clock rate returned
- * by snmf_clock_rate_hz()). */
+ * by snmf_clock_rate_hz()).  A W0 that params.validate refuses leaves every output
+ * untouched; up to 64 outer iterations its error is found together with the results, the
+ * launches after the check returning at once. */
 snmf_status snmf_solve(const snmf_matrix* A, int32_t r, const void* W0, const snmf_params* p,
                        void* W_out, void* Ht_out, snmf_info* info, void* stream, double* trace);
 
@@ -185,7 +190,7 @@ snmf_status snmf_solve(const snmf_matrix* A, int32_t r, const void* W0, const sn
  * first use of the library on a device until the process ends), work on the caller's
  * stream, and no host heap allocation on success.  Limits: F64 or F32 (BF16X3:
  * E_UNSUPPORTED, its split copies of A would not fit); the scratch the problem needs must
- * fit 64 MiB (about 6 n r element sizes plus, for dense F32, the split-K partial panels;
+ * fit 64 MiB (about 8 n r element sizes plus, for dense F32, the split-K partial panels;
  * dense n = 8192, r = 64 in F32 needs 31 MiB), else E_SHAPE with the size in the message.
  * Every call on a GPU shares that GPU's array, and the library clears what must start at
  * zero on each call: calls that overlap on one GPU (several host threads, or streams that

@@ -355,7 +355,7 @@ __global__ __launch_bounds__(256) void k_apass_f32(const float* __restrict__ A, 
 // With rj.G set, the grid has one more workgroup (number rho_wg): it computes
 // rho = ||G||_2 (rho.hpp) beside the tiles.  The register bound of two waves per SIMD and
 // the 64 KB of LDS leave room on a CU for it next to a tile workgroup (the tiles take one
-// slot fewer than two per CU), so rho (56 us alone at r = 64) adds only the slowdown of
+// slot fewer than two per CU), so rho (52 us alone at r = 64) adds only the slowdown of
 // the tile workgroup that shares its CU.  With two workgroups per CU, workgroups i and
 // i + CUs are dispatched to the same CU, so the host places rho at the last index minus
 // the CU count, beside the last workgroup: a chunk of the rows after the bands, which

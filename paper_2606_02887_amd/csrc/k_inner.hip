@@ -1463,7 +1463,8 @@ __global__ __launch_bounds__(kThreads, (fused_occupancy<T, RP>())) void k_advanc
       next_tile(row0, xn, gn);
       // the trial of this workgroup's next tile loads while this one is worked on
       if (trial && t + nb < ntiles) load_trial(row0 + (int64_t)nb * TM);
-      // sm.a was last read before this tile's first barrier
+      // sm.a was last read before this tile's first barrier, or after a backtrack (next_tile)
+      // before its barrier behind sm.b
       tile_direction<T, RP>(sm, lr, cl, bo, row0, n, r, xn, gn, rinv, alpha, lam, step1,
                             kp.project, tile_ptr(Xc, tb), tile_ptr(gc, tb), ls, sp, xp);
     }

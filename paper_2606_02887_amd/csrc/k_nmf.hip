@@ -195,7 +195,7 @@ typedef float f32x16n __attribute__((ext_vector_type(16)));
 // With rj.G set the grid has one more row of workgroups, the first, whose first workgroup
 // computes rho = ||G||_2 (rho.hpp).  Skipped when the solve is done.
 // V 8192 x 4096, r = 64: V^T P 47, V P 59 us (FP32 matrix rate 28, V from memory 27, the
-// panels' stores 7 and more), up to 88 beside a rho of all r steps (56 alone); the general
+// panels' stores 7 and more), up to 88 beside a rho of all r steps (52 alone); the general
 // kernel took 74 and 97 us, the transposed copy 58 us and 134 MB per call.
 typedef float f32x4n __attribute__((ext_vector_type(4)));
 

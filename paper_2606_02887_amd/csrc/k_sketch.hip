@@ -331,7 +331,7 @@ __global__ __launch_bounds__(kThreads) void k_tsgram_reduce(const double* __rest
 // entries left of the diagonal collect values that nothing reads).  Back
 // substitution: X_ic = -(sum_{k > i} R_ik X_kc) / R_ii is one FMA chain over k in increasing
 // order, R_ik an LDS broadcast and X_kc a row of LDS (X in Rinv itself where both do not
-// fit, w > 92), eight terms at a time with the next eight requested across rows; R and X are
+// fit, w > 96), eight terms at a time with the next eight requested across rows; R and X are
 // padded with zeros, so no term is conditional.  Both phases are chains of w steps:
 // 93 us at w = 74 (492 us with R in global memory, three barriers per step).
 template <int NE, bool XL>

@@ -96,7 +96,7 @@ void launch_apass_f64(const double* A, int64_t lda, const double* P, int64_t n, 
                       const DenseSplit& d, double* Bpart, int64_t pstride, const State* st,
                       hipStream_t s, const RhoJob& rj = RhoJob{});
 DenseSplit plan_dense_f32(int64_t n, int64_t lda, int r, const void* A);
-// With rj.G set, rho is computed in the same launch (wide path) or just before it.
+// With rj.G set, rho is computed in the same launch.
 void launch_apass_f32(const float* A, int64_t lda, const float* P, int64_t n, int r,
                       const DenseSplit& d, float* Bpart, int64_t pstride, const State* st,
                       hipStream_t s, const RhoJob& rj = RhoJob{});

@@ -275,9 +275,8 @@ int ksplit_of(const snmf_plan* pl) {
   return pl->A.fmt == SNMF_DENSE ? pl->ds.ksplit : 1;
 }
 
-// Start of a half-step up to and including init: G, rho (in or just before the A-pass,
-// on the same stream: a second stream would cost more in cross-queue waits than rho
-// takes), the A-pass and the gradient.  The first reader of rho is the first inner kernel.
+// Start of a half-step up to and including init: G, the A-pass with rho in its launch (a
+// second stream would cost more in cross-queue waits than rho takes) and the gradient.  The first reader of rho is the first inner kernel.
 // Inner iterations of this half-step run as fused kernels, one per inner iteration
 // (fused_inner_ok), on every half-step without the Laplacian term except the H-step of
 // the naive variant.
