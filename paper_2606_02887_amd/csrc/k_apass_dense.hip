@@ -135,18 +135,16 @@ __global__ __launch_bounds__(256) void k_apass_f64(const double* __restrict__ A,
                                                               acc[mt][q], 0, 0, 0);
   };
   if (kb < ke) {
-    Batch x, y = {};
+    Batch x, y;
     load(x, kb);
     for (int64_t k0 = kb; k0 < ke; k0 += 32 * U) {
-      const bool two = k0 + 16 * U < ke;
+      const bool two = k0 + 16 * U < ke, last = k0 + 32 * U > ke;
       if (two) load(y, k0 + 16 * U);
-      if (k0 + 32 * U > ke) {  // the last two batches
-        trim(x, k0);
-        trim(y, k0 + 16 * U);
-      }
+      if (last) trim(x, k0);
       mma(x);
       if (!two) break;
       if (k0 + 32 * U < ke) load(x, k0 + 32 * U);
+      if (last) trim(y, k0 + 16 * U);
       mma(y);
     }
   }
